@@ -287,7 +287,8 @@ enum {
     BCM_PROF_UPDATE = 8,       /* the four fused vector updates + ||r||^2 */
     BCM_PROF_CYCLE_COARSE = 16, /* the coarsest-level solve */
     BCM_PROF_CYCLE_MID = 32,    /* every cycle kernel of levels 1 .. nl - 2 (several per cycle) */
-    /* setup classes, one bracket per pairwise sweep, timed during bcm_setup */
+    /* setup classes, one bracket per pairwise sweep, timed during bcm_setup (the
+       sweeps of star levels, one launch each, are not bracketed) */
     BCM_PROF_SETUP_MATCH = 64,     /* edge weights and Suitor candidate lists (long rows included) */
     BCM_PROF_SETUP_SUITOR = 128,   /* the Suitor matching kernel itself */
     BCM_PROF_SETUP_GALERKIN = 256  /* Galerkin product: count, row pointers, fill */

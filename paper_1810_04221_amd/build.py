@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libbcm.so")
-SOURCES = ["setup.hip", "scan.hip", "solve.hip", "api.hip"]
+SOURCES = ["setup.hip", "scan.hip", "star.hip", "solve.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = [
@@ -39,7 +39,7 @@ def _compile(src: str, outdir: str) -> str:
 def build(verbose: bool = False) -> str:
     outdir = os.path.join(HERE, "_build")
     os.makedirs(outdir, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
         objs = list(ex.map(lambda s: _compile(s, outdir), SOURCES))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]

@@ -162,84 +162,6 @@ int read_back_plain(hipStream_t s, const void *dev, size_t bytes, void *host) {
     return BCM_OK;
 }
 
-// The coarsest level's StarView when it is a star (one hub row, every other
-// row holding only its diagonal and the hub entry); otherwise L.star stays
-// unset and the coarse solve keeps its sweep kernels.  The matrix is read back
-// once; E's weights F_m are formed here in FP64, in the hub row's order.
-int build_star(bcm_handle *h, hipStream_t s, Level &L, int sweeps) {
-    const int n = L.A.n, nnz = L.A.nnz;
-    std::vector<int> rp(n + 1), ci(nnz);
-    std::vector<double> a(nnz), dinv(n);
-    int rc = read_back(s, L.A.rp, sizeof(int) * (n + 1), rp.data());
-    if (!rc) rc = read_back(s, L.A.ci, sizeof(int) * nnz, ci.data());
-    if (!rc) rc = read_back(s, L.A.v, sizeof(double) * nnz, a.data());
-    if (!rc) rc = read_back(s, L.dinv, sizeof(double) * n, dinv.data());
-    if (rc) return rc;
-    int hub = -1;
-    for (int i = 0; i < n; ++i)
-        if (rp[i + 1] - rp[i] > 2) {
-            if (hub >= 0) return BCM_OK;  // two rows beyond two entries: not a star
-            hub = i;
-        }
-    if (hub < 0) return BCM_OK;
-    // every other row: its diagonal, and at most the hub besides
-    std::vector<double> c(n, 0.0), f(n, 0.0);
-    for (int j = 0; j < n; ++j) {
-        if (j == hub) continue;
-        bool diag = false;
-        double ajj = 0.0, ajh = 0.0;
-        for (int q = rp[j]; q < rp[j + 1]; ++q) {
-            if (ci[q] == j) { diag = true; ajj = a[q]; }
-            else if (ci[q] == hub) ajh = a[q];
-            else return BCM_OK;
-        }
-        if (!diag) return BCM_OK;
-        c[j] = 1.0 - dinv[j] * ajj;
-        f[j] = dinv[j] * ajh;
-    }
-    std::vector<int> hj;
-    std::vector<double> ha;
-    double ahh = 0.0;
-    for (int q = rp[hub]; q < rp[hub + 1]; ++q) {
-        if (ci[q] == hub) ahh = a[q];
-        else { hj.push_back(ci[q]); ha.push_back(a[q]); }
-    }
-    const int M = sweeps - 1;
-    std::vector<double> F(std::max(M, 1), 0.0);
-    for (size_t q = 0; q < hj.size(); ++q) {
-        const int j = hj[q];
-        double t = ha[q] * f[j];
-        for (int m = 0; m < M; ++m) { F[m] += t; t *= c[j]; }
-    }
-    StarView &sv = L.star;
-    const int nh = (int)hj.size();
-    int *dhj = h->persist.get_n<int>(std::max(nh, 1));
-    double *dha = h->persist.get_n<double>(std::max(nh, 1));
-    double *dc = h->persist.get_n<double>(n);
-    double *dF = h->persist.get_n<double>(F.size());
-    double *dpart = h->persist.get_n<double>((size_t)(kStarMaxSweeps - 1) * kStarBlocks);
-    double *dxh = h->persist.get_n<double>(kStarMaxSweeps + 1);
-    NOMEM(dhj && dha && dc && dF && dpart && dxh);
-    if (nh) {
-        HIPCHK(hipMemcpyAsync(dhj, hj.data(), sizeof(int) * nh, hipMemcpyHostToDevice, s));
-        HIPCHK(hipMemcpyAsync(dha, ha.data(), sizeof(double) * nh, hipMemcpyHostToDevice, s));
-    }
-    HIPCHK(hipMemcpyAsync(dc, c.data(), sizeof(double) * n, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(dF, F.data(), sizeof(double) * F.size(), hipMemcpyHostToDevice, s));
-    HIPCHK(hipStreamSynchronize(s));
-    sv.hub = hub;
-    sv.nh = nh;
-    sv.hj = dhj;
-    sv.ha = dha;
-    sv.c = dc;
-    sv.F = dF;
-    sv.part = dpart;
-    sv.xh = dxh;
-    sv.ahh = ahh;
-    sv.dh = dinv[hub];
-    return BCM_OK;
-}
-
 struct SweepOut {
     int prof_gal = -1;  // setup profile bracket of this sweep's Galerkin product
     int nc = 0;
@@ -664,7 +586,7 @@ int autotune_lanes(bcm_handle *h) {
         return BCM_EHIP;
     }
     launch_fill_i32(s, 2 * (size_t)h->lv[0].A.n, (int *)h->r, 0);
-    const int last = h->kt > 0 ? h->kt : h->nl - 1;
+    const int last = h->kt > 0 ? h->kt : (h->kc > 0 ? h->kc : (h->kf > 0 ? h->kf : h->nl - 1));
     hipError_t err = hipSuccess;
     for (int l = 0; l < last && err == hipSuccess; ++l) {
         Level &L = h->lv[l];
@@ -701,6 +623,225 @@ int autotune_lanes(bcm_handle *h) {
     return BCM_OK;
 }
 
+// Device copies of host tables: the vectors live until the build's last
+// synchronisation, so that no copy needs a wait of its own.
+struct HostTables {
+    std::vector<std::vector<ChainLevel>> chains;
+};
+
+// The operator of a chain of star levels k0 .. nl - 1 (hubs: one per level)
+// into lv[k0].chain; its scratch comes from tmp.
+int build_chain(bcm_handle *h, hipStream_t s, Arena &tmp, HostTables &host, int k0, const std::vector<int> &hubs,
+                bool diagonals) {
+    const int L = (int)hubs.size() - 1, n = h->lv[k0].A.n, S = h->prm.coarse_sweeps;
+    host.chains.emplace_back();
+    std::vector<ChainLevel> &tab = host.chains.back();
+    for (int t = 0; t <= L; ++t) {
+        const Level &V = h->lv[k0 + t];
+        tab.push_back({V.A.n, hubs[t], V.A.rp, V.A.ci, V.A.v, V.dinv, t < L ? V.agg : nullptr, t < L ? V.p : nullptr});
+    }
+    ChainLevel *dt = static_cast<ChainLevel *>(tmp.get(sizeof(ChainLevel) * tab.size()));
+    NOMEM(dt);
+    HIPCHK(hipMemcpyAsync(dt, tab.data(), sizeof(ChainLevel) * tab.size(), hipMemcpyHostToDevice, s));
+    if (diagonals) {
+        double *part = tmp.get_n<double>((size_t)(L + 1) * star_blocks(n));
+        NOMEM(part);
+        launch_star_dinv(s, dt, L + 1, n, part);
+    }
+    ChainOp C;
+    C.n = n;
+    C.M = chain_sums(L, S);
+    C.hub = hubs[0];
+    const size_t nch = (n + kChainChunk - 1) / kChainChunk;
+    double *A = h->persist.get_n<double>((size_t)C.M * n), *V = h->persist.get_n<double>((size_t)(C.M + 1) * n);
+    double *delta = h->persist.get_n<double>(n), *scr = tmp.get_n<double>(chain_scratch(n, L, S));
+    C.E = h->persist.get_n<double>((size_t)C.M * nch);
+    NOMEM(A && V && delta && scr && C.E);
+    launch_chain_build(s, dt, n, L, S, scr, A, V, delta);
+    C.A = A;
+    C.V = V;
+    C.delta = delta;
+    h->lv[k0].chain = C;
+    return BCM_OK;
+}
+
+// Bytes of the chain operator of L star levels above the coarsest (n rows on
+// the first); beyond kChainBytes the levels keep their own kernels.
+constexpr size_t kChainBytes = size_t(4) << 30;
+bool chain_fits(int n, int L, int sweeps) {
+    return sweeps >= 1 && sweeps <= kStarMaxSweeps && 16 * (size_t)n * (chain_sums(L, sweeps) + 1) <= kChainBytes;
+}
+
+// The coarsest level's sweeps as a chain operator when it is a star (one hub
+// row, every other row holding only its diagonal and at most the hub entry).
+int build_coarsest_star(bcm_handle *h, hipStream_t s, Arena &tmp, HostTables &host) {
+    Level &L = h->lv[h->nl - 1];
+    if (!chain_fits(L.A.n, 0, h->prm.coarse_sweeps)) return BCM_OK;
+    int *ctl = tmp.get_n<int>(8);
+    NOMEM(ctl);
+    launch_fill_i32(s, 8, ctl, 0);
+    launch_star_find(s, L.A.n, L.A.rp, L.A.ci, ctl);
+    int f[4];
+    int rc = read_back(s, ctl, sizeof(f), f);
+    if (rc) return rc;
+    if (f[0] != 1 || f[2]) return BCM_OK;
+    launch_star_verify(s, L.A.n, L.A.rp, L.A.ci, L.A.v, f[1], ctl);
+    rc = read_back(s, ctl, sizeof(f), f);
+    if (rc) return rc;
+    if (f[2]) return BCM_OK;
+    return build_chain(h, s, tmp, host, h->nl - 1, std::vector<int>{f[1]}, false);
+}
+
+// Appends the levels of a chain of stars below level k, when level k is a star
+// whose hub is coupled to every row: `sweeps` launches per level, run ahead
+// without a read-back (every sweep forms one pair, so all sizes are known).
+// appended: levels added (0: not such a star, or it forms no pair); hubs: the
+// hub row of level k and of each level added.
+int star_levels(bcm_handle *h, hipStream_t s, Arena &tmp, Arena &keep, int k, int max_coarse, int &appended,
+                std::vector<int> &hubs) {
+    const bcm_params &P = h->prm;
+    constexpr int kStarMin = 16;  // rows: smaller stars take the general sweeps
+    Level &L0 = h->lv[k];
+    const int n0 = L0.A.n;
+    appended = 0;
+    hubs.clear();
+    tmp.rewind();
+    keep.rewind();
+    const int ms = 4 * kMaxLevels;
+    int *ctl = tmp.get_n<int>(16), *hubd = tmp.get_n<int>(ms + 1), *sel = tmp.get_n<int>(ms);
+    NOMEM(ctl && hubd && sel);
+    launch_fill_i32(s, 16, ctl, 0);
+    launch_star_find(s, n0, L0.A.rp, L0.A.ci, ctl);
+    if (L0.A.nnz_dev) HIPCHK(hipMemcpyAsync(ctl + 4, L0.A.nnz_dev, 2 * sizeof(int), hipMemcpyDeviceToDevice, s));
+    int f[8];
+    int rc = read_back(s, ctl, sizeof(f), f);
+    if (rc) return rc;
+    if (L0.A.nnz_dev) {
+        L0.A.nnz = f[4];
+        L0.A.dmax = f[5];
+        L0.A.nnz_dev = nullptr;
+    }
+    if (f[0] != 1 || f[2] || L0.A.dmax != n0 || (long long)L0.A.nnz != 3LL * n0 - 2) return BCM_OK;
+    const int hub0 = f[1];
+    launch_star_verify(s, n0, L0.A.rp, L0.A.ci, L0.A.v, hub0, ctl);
+    // scratch of the sweeps before a level's last (two sets in turn)
+    struct Inter {
+        int *rp, *ci, *agg, *mem;
+        double *v, *w, *p;
+    } in[2];
+    for (int t = 0; t < std::min(P.sweeps - 1, 2); ++t) {
+        in[t].rp = keep.get_n<int>((size_t)n0 + 2);
+        in[t].ci = keep.get_n<int>(3 * (size_t)n0);
+        in[t].v = keep.get_n<double>(3 * (size_t)n0);
+        in[t].w = keep.get_n<double>(n0);
+        in[t].agg = keep.get_n<int>(n0);
+        in[t].p = keep.get_n<double>(n0);
+        in[t].mem = keep.get_n<int>((size_t)n0 << (P.sweeps - 1));
+        NOMEM(in[t].rp && in[t].ci && in[t].v && in[t].w && in[t].agg && in[t].p && in[t].mem);
+    }
+    const int nb0 = star_blocks(n0);
+    double *pc[2] = {tmp.get_n<double>(nb0), tmp.get_n<double>(nb0)};
+    int *pi[2] = {tmp.get_n<int>(nb0), tmp.get_n<int>(nb0)};
+    NOMEM(pc[0] && pc[1] && pi[0] && pi[1]);
+    launch_star_best(s, n0, L0.A.v, L0.w, hub0, hubd, pc[0], pi[0]);
+    int np = nb0, it = 0, levels = 0;
+    for (;; ++levels) {
+        Level &L = h->lv[k + levels];
+        const int nk = L.A.n;
+        if (nk <= max_coarse || k + levels + 1 >= P.max_levels || k + levels + 1 >= kMaxLevels ||
+            nk - P.sweeps < kStarMin)
+            break;
+        Level &C = h->lv[k + levels + 1];
+        const int nc = nk - P.sweeps;
+        C.A.n = nc;
+        C.A.nnz = 3 * nc - 2;
+        C.A.dmax = nc;
+        C.A.rp = h->persist.get_n<int>((size_t)nc + 2);
+        C.A.ci = h->persist.get_n<int>(C.A.nnz);
+        C.A.v = h->persist.get_n<double>(C.A.nnz);
+        C.w = h->persist.get_n<double>(nc);
+        L.agg = h->persist.get_n<int>(nk);
+        L.p = h->persist.get_n<double>(nk);
+        L.mem = h->persist.get_n<int>((size_t)nc << P.sweeps);
+        NOMEM(C.A.rp && C.A.ci && C.A.v && C.w && L.agg && L.p && L.mem);
+        L.nc = nc;
+        L.mstride = 1 << P.sweeps;
+        const double *v = L.A.v, *w = L.w;
+        StarSweep S{};
+        S.nf = nk;
+        S.stride_prev = 1;
+        for (int sw = 0; sw < P.sweeps; ++sw, ++it) {
+            const bool last = sw == P.sweeps - 1;
+            const Inter &o = in[last ? 0 : sw & 1];
+            S.n = nk - sw;
+            S.v = v;
+            S.w = w;
+            S.hub = hubd + it;
+            S.pc = pc[it & 1];
+            S.pi = pi[it & 1];
+            S.np = np;
+            S.sel = sel + it;
+            S.flags = ctl + 6;
+            S.rp = last ? C.A.rp : o.rp;
+            S.ci = last ? C.A.ci : o.ci;
+            S.cv = last ? C.A.v : o.v;
+            S.cw = last ? C.w : o.w;
+            S.hub_out = hubd + it + 1;
+            S.pc_out = pc[(it + 1) & 1];
+            S.pi_out = pi[(it + 1) & 1];
+            S.agg = last ? L.agg : o.agg;
+            S.p = last ? L.p : o.p;
+            S.mem = last ? L.mem : o.mem;
+            launch_star_sweep(s, S);
+            np = star_blocks(nk);
+            v = S.cv;
+            w = S.cw;
+            S.agg_prev = S.agg;
+            S.p_prev = S.p;
+            S.mem_prev = S.mem;
+            S.stride_prev *= 2;
+        }
+    }
+    HIPCHK(hipGetLastError());
+    rc = read_back(s, ctl, sizeof(f), f);
+    if (rc) return rc;
+    std::vector<int> l(it);
+    if (it) rc = read_back(s, sel, sizeof(int) * it, l.data());
+    if (rc) return rc;
+    const bool star = !f[2] && !f[3];
+    if (star && f[6]) {
+        set_error("invalid coarse-level matrix:" + flag_text(f[6]));
+        return BCM_EINVAL;
+    }
+    int hub = hub0, done = 0;
+    std::vector<int> hv{hub0};
+    for (; star && done < levels; ++done) {
+        bool all = true;
+        for (int sw = 0; sw < P.sweeps && all; ++sw) {
+            const int lf = l[done * P.sweeps + sw];
+            all = lf >= 0;
+            hub = std::min(hub, lf);
+        }
+        if (!all) break;  // the general sweeps finish this level
+        hv.push_back(hub);
+        for (int sw = 0; sw < P.sweeps; ++sw) {
+            const double m = h->lv[k + done].A.n - sw;
+            h->setup_bytes += 72.0 * (3.0 * m - 2.0) + 80.0 * m;
+            h->sweeps_run += 1;
+        }
+    }
+    for (int t = done; t < levels; ++t) {  // levels past the last complete one
+        Level &L = h->lv[k + t];
+        L.nc = L.mstride = 0;
+        L.agg = L.mem = nullptr;
+        L.p = nullptr;
+        h->lv[k + t + 1] = Level();
+    }
+    appended = done;
+    hubs = hv;
+    return BCM_OK;
+}
+
 int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
     hipStream_t s = h->s;
     const bcm_params &P = h->prm;
@@ -713,6 +854,7 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
     keep.alloc = tmp.alloc = P.alloc;
     keep.dealloc = tmp.dealloc = P.dealloc;
     keep.ctx = tmp.ctx = P.alloc_ctx;
+    HostTables host;  // (outlives the guard below, whose wait ends the copies from it)
     keep.reserve((size_t)(16.0 * z + 96.0 * nn) + (size_t(1) << 20));
     tmp.reserve((size_t)(32.0 * z + 56.0 * nn) + (size_t(1) << 20));
     struct Guard {
@@ -776,10 +918,28 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
         int idx = -1;
         double m = 0, z = 0, nc = 0;
     } pend;
+    // a stalled hierarchy's star levels: the first, and the hubs of all of them
+    int ks = -1;
+    std::vector<int> hubs;
     for (;;) {
         Level &L = h->lv[k];
         const int nk = L.A.n;
         if (nk <= max_coarse || k + 1 >= P.max_levels || k + 1 >= kMaxLevels) break;
+        // the last level lost two rows a sweep at most: it may be a star from here on
+        if (ks < 0 && k > 0 && rmin <= 1.0 && h->lv[k - 1].A.n - nk <= 2 * P.sweeps) {
+            int added = 0;
+            const int rc = star_levels(h, s, tmp, keep, k, max_coarse, added, hubs);
+            if (rc) return rc;
+            if (pend.idx >= 0) {
+                sp.set_bytes(pend.idx, bytes_setup_galerkin(pend.m, pend.z, pend.nc, L.A.nnz));
+                pend.idx = -1;
+            }
+            if (added > 0) {
+                ks = k;
+                k += added;
+                continue;
+            }
+        }
         keep.rewind();
         Csr Acur = L.A;
         const double *wcur = L.w;
@@ -861,6 +1021,12 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
         if (rmin > 1.0 && (double)nk < rmin * (double)C.A.n) break;  // stalled coarsening: C is the coarsest
     }
     h->nl = k + 1;
+    // The star levels as one operator (V-cycle): on their own, or, when small,
+    // inside the folded operator of the small levels.
+    const bool chain = ks > 0 && P.cycle == BCM_VCYCLE && P.fold && ks + (int)hubs.size() == h->nl &&
+                       chain_fits(h->lv[ks].A.n, (int)hubs.size() - 1, P.coarse_sweeps);
+    // levels without kernels of their own
+    auto in_chain = [&](int l) { return chain && l >= ks; };
     {
         Csr &Ac = h->lv[h->nl - 1].A;  // the coarsest level ran no sweep: its entry count is still pending
         if (Ac.nnz_dev) {
@@ -884,6 +1050,10 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             L.G = lanes_for(P.group, L.A);
             const int lmin = long_min(L.G);
             if (L.A.dmax <= lmin) continue;
+            if (in_chain(l)) {
+                h->long_star += 1;  // the hub row
+                continue;
+            }
             SegList sg;
             Carver probe;
             probe.left = ~size_t(0);
@@ -937,6 +1107,15 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
         const int nl_ = L.A.n;
         if (!L.dinv) L.dinv = h->persist.get_n<double>(nl_);  // (the finest level's was allocated first)
         NOMEM(L.dinv);
+        if (in_chain(l)) {  // (the inverse diagonals: build_chain)
+            if (l == ks) {
+                const size_t es = fp32 ? sizeof(float) : sizeof(double);
+                L.b = h->persist.get(es * nl_);
+                L.x = h->persist.get(es * nl_);
+                NOMEM(L.b && L.x);
+            }
+            continue;
+        }
         if (fp32) {
             L.dinv32 = h->persist.get_n<float>(nl_);
             L.A.v32 = h->persist.get_n<float>(L.A.nnz);
@@ -977,7 +1156,7 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
         // level that runs the split up leg
         std::vector<int> lv_sell;
         for (int l = 0; l < h->nl && P.sell; ++l)
-            if ((l == 0 || h->lv[l].xp) && h->lv[l].lr.n == 0) lv_sell.push_back(l);
+            if ((l == 0 || h->lv[l].xp) && h->lv[l].lr.n == 0 && !in_chain(l)) lv_sell.push_back(l);
         // per level t: tot[t] = total slots, tot[32 + t] = largest |col - row|,
         // tot[64 + t] = 1 if some value is not exactly a float32, tot[96 + t] =
         // slots of the slices without uniform column offsets
@@ -1048,7 +1227,11 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
         }
         for (size_t t = 0; t < lv_sell.size(); ++t) h->lv[lv_sell[t]].E.stream = vb > kStreamSolve;
     }
-    {
+    if (chain) {
+        tmp.rewind();
+        const int rc = build_chain(h, s, tmp, host, ks, hubs, true);
+        if (rc) return rc;
+    } else {
         // coarsest level: precompute the sweep operator when it is small
         Level &C = h->lv[h->nl - 1];
         if (C.A.n <= kCoarseDense) {
@@ -1072,19 +1255,35 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             }
         }
     }
-    if (P.fold && h->nl >= 3 && h->lv[h->nl - 1].S) {
+    // Folding starts from the coarsest level's sweep operator, or from the dense
+    // form of a small star chain.  A chain with no other level to fold with it
+    // is applied as it is once its two passes cost less than the dense product
+    // (2 M n against n^2 entries; beyond 1024 rows with the default sweeps).
+    const int kb = chain ? ks : h->nl - 1;
+    bool fold = P.fold && kb >= 2 && (chain ? h->lv[ks].A.n <= kFoldRows : h->lv[kb].S != nullptr);
+    if (fold && chain && h->lv[ks - 1].A.n > kFoldRows && h->lv[ks].A.n > 1024) fold = false;
+    if (chain && !fold) h->kc = ks;
+    if (fold) {
         // The cycle from the first level k >= 1 with at most kFoldRows rows down to
         // the coarsest, formed once as one dense operator (built upwards from the
         // coarsest level's sweep operator): V- and W-cycles, and K-cycles whose
         // Krylov coarse solves all sit above that level.
-        int kf = h->nl - 1;
+        int kf = kb;
         while (kf > 1 && h->lv[kf - 1].A.n <= kFoldRows) --kf;
         const bool wcyc = P.cycle == BCM_WCYCLE;
         const bool linear = P.cycle != BCM_KCYCLE || (P.kcycle_levels > 0 && P.kcycle_levels <= kf);
         if (kf < h->nl - 1 && linear) {
-            tmp.rewind();
             const double *Tc = h->lv[h->nl - 1].S;
-            for (int k = h->nl - 2; k >= kf; --k) {
+            if (chain) {
+                const size_t nn2 = (size_t)h->lv[ks].A.n * h->lv[ks].A.n;
+                double *T = kf == ks ? h->persist.get_n<double>(nn2) : tmp.get_n<double>(nn2);
+                NOMEM(T);
+                launch_chain_dense(s, h->lv[ks].chain, T);
+                Tc = T;
+            } else {
+                tmp.rewind();
+            }
+            for (int k = kb - 1; k >= kf; --k) {
                 const Level &L = h->lv[k], &C = h->lv[k + 1];
                 const size_t nn2 = (size_t)L.A.n * L.A.n, nc2 = (size_t)C.A.n * C.A.n;
                 if (wcyc) {  // the coarse problem solved by two cycles of level k + 1
@@ -1103,7 +1302,7 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             h->fold = const_cast<double *>(Tc);
         }
     }
-    if (h->kf == 0) {
+    if (h->kf == 0 && !chain) {
         // tail kernel: the smallest levels (and the coarsest solve) in one workgroup
         // (levels with long rows stay out of it: it gives a row at most 16 lanes)
         int kt = h->nl - 1;
@@ -1153,13 +1352,14 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             h->kt = kt;
         }
     }
-    if (!h->lv[h->nl - 1].S &&
+    if (!chain && !h->lv[h->nl - 1].S &&
         !coarse_in_lds(h->lv[h->nl - 1].A.n, h->lv[h->nl - 1].A.nnz, h->lv[h->nl - 1].lr.n > 0)) {
         h->ctmp[0] = h->persist.get_n<double>(h->lv[h->nl - 1].A.n);
         h->ctmp[1] = h->persist.get_n<double>(h->lv[h->nl - 1].A.n);
         NOMEM(h->ctmp[0] && h->ctmp[1]);
-        if (P.coarse_sweeps >= 1 && P.coarse_sweeps <= kStarMaxSweeps && h->lv[h->nl - 1].lr.n == 1) {
-            const int rc = build_star(h, s, h->lv[h->nl - 1], P.coarse_sweeps);
+        if (h->lv[h->nl - 1].lr.n == 1) {
+            tmp.rewind();
+            const int rc = build_coarsest_star(h, s, tmp, host);
             if (rc) return rc;
         }
     }
@@ -1230,8 +1430,10 @@ double value_bytes(const Level &L, bool sell_path, bool f32) {
 }
 
 // levels 0 .. cycle_levels(h) - 1 run their own down and up legs in the
-// V-cycle; the rest are the folded operator, the tail kernel or the coarsest solve
-int cycle_levels(const bcm_handle *h) { return h->kf > 0 ? h->kf : (h->kt > 0 ? h->kt : h->nl - 1); }
+// V-cycle; the rest are the folded operator, the star chain, the tail kernel or the coarsest solve
+int cycle_levels(const bcm_handle *h) {
+    return h->kf > 0 ? h->kf : (h->kc > 0 ? h->kc : (h->kt > 0 ? h->kt : h->nl - 1));
+}
 // level k (>= 1) of the V-cycle gets its dinv o b from level k - 1's restriction
 bool y_by_restrict(const bcm_handle *h, int k) {
     return h->prm.cycle == BCM_VCYCLE && k >= 1 && k < cycle_levels(h) && h->lv[k].yb && down_on_sell(h->lv[k]) &&
@@ -1297,13 +1499,19 @@ double bytes_fold(const bcm_handle *h) {
     const double sb = h->prm.precision == BCM_FP32_CYCLE ? 4 : 8;
     return 8 * n * n + 2 * sb * n;
 }
+// the star chain: both factors once, b in and x out, the hub's sums
+double bytes_chain(const bcm_handle *h) {
+    const ChainOp &C = h->lv[h->kc].chain;
+    const double sb = h->prm.precision == BCM_FP32_CYCLE ? 4 : 8;
+    return 8.0 * (2.0 * C.M + 2.0) * C.n + 3 * sb * C.n;
+}
 // one preconditioner application: every level's legs times the number of
 // times the level is visited (doubling below each W- or K-accelerated level),
 // plus the W residual/add and the K-cycle products and combinations
 double bytes_cycle(const bcm_handle *h) {
     const double sv = h->prm.precision == BCM_FP32_CYCLE ? 4 : 8;
     double total = 0.0, visits = 1.0;
-    const int kend = h->kf > 0 ? h->kf : h->nl - 1;  // levels below kend: the folded operator
+    const int kend = h->kf > 0 ? h->kf : (h->kc > 0 ? h->kc : h->nl - 1);  // below: folded operator or star chain
     for (int k = 0; k < kend; ++k) {
         total += visits * (bytes_down(h, k) + bytes_up(h, k));
         const Level &C = h->lv[k + 1];
@@ -1316,7 +1524,7 @@ double bytes_cycle(const bcm_handle *h) {
             visits *= 2;
         }
     }
-    return total + visits * (h->kf > 0 ? bytes_fold(h) : bytes_coarse(h));
+    return total + visits * (h->kf > 0 ? bytes_fold(h) : (h->kc > 0 ? bytes_chain(h) : bytes_coarse(h)));
 }
 double bytes_spmv_dots(const bcm_handle *h) {
     const Level &L = h->lv[0];
@@ -1339,6 +1547,7 @@ double class_bytes(const bcm_handle *h, int cls) {
     case 3: return bytes_update(h);
     default: {
         if (h->kf > 0) return bytes_fold(h);
+        if (h->kc > 0) return bytes_chain(h);
         double by = bytes_coarse(h);
         const int kt = h->kt > 0 ? h->kt : h->nl - 1;
         for (int k = kt; k < h->nl - 1; ++k) by += bytes_down(h, k) + bytes_up(h, k);
@@ -1557,6 +1766,8 @@ void vcycle(bcm_handle *h, Prof &pf, const double *rin, double *wout, const doub
         int e = pf.begin(4);
         if (h->kf > 0) {
             launch_dense(s, h->lv[kt].A.n, h->fold, h->lv[kt].b, h->lv[kt].x, !fp32, !fp32, done);
+        } else if (h->kc > 0) {
+            launch_chain(s, h->lv[kt].chain, h->lv[kt].b, h->lv[kt].x, !fp32, !fp32, done);
         } else if (h->kt > 0) {
             launch_tail(s, fp32, kt, nl, h->tail, C, cs, h->tail_ops, h->n_tail_ops, h->lv[kt].x, done);
         } else {
@@ -1974,6 +2185,7 @@ int bcm_info(const bcm_handle *h, bcm_info_t *o) {
     o->iter_bytes = cyc + bytes_spmv_dots(h) + bytes_update(h);
     o->setup_bytes = h->setup_bytes;
     o->sweeps_run = h->sweeps_run;
+    o->long_rows = h->long_star;
     for (int k = 0; k < h->nl; ++k) o->long_rows += h->lv[k].lr.n;
     return BCM_OK;
 }

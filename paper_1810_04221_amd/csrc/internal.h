@@ -179,30 +179,48 @@ struct Sell {
 // keeps cached loads.
 constexpr long long kStreamSolve = 192LL << 20;
 
-// A coarsest level shaped as a star: one hub row coupled to every other row,
-// each of which holds only its diagonal and the hub entry.  The coarse solve's
-// sweeps from zero (the coarsest step of Algorithm 1: l1-Jacobi sweeps, 20 in
-// the Section 5 settings) are then a recurrence in the hub's value alone
-// (k_star_*), the same operator evaluated in another order:
-// with c_j = 1 - d_j a_jj, row j after k sweeps is
-//   sum_{t<k} c_j^(k-1-t) d_j (b_j - a_jh x_h^(t)),
-// so the hub row's product after k sweeps is
-//   sum_{t<k} (E_(k-1-t) - F_(k-1-t) x_h^(t)),
-//   E_m = sum_j a_hj c_j^m d_j b_j,  F_m = sum_j a_hj c_j^m d_j a_jh
-// (j over the hub row's columns off the diagonal).  F depends on the matrix
-// alone and is formed at setup; E takes one pass over the hub row.
-constexpr int kStarBlocks = 64;      // workgroups of the pass that forms E
-constexpr int kStarMaxSweeps = 32;   // sweeps beyond this keep the sweep kernels
-struct StarView {
-    int hub = -1;                  // -1: not a star
-    int nh = 0;                    // hub-row entries off the diagonal
-    const int *hj = nullptr;       // their columns
-    const double *ha = nullptr;    // their values a_hj
-    const double *c = nullptr;     // c_j = 1 - d_j a_jj per row
-    const double *F = nullptr;     // F_m, m < sweeps - 1
-    double *part = nullptr;        // E partials: (kStarMaxSweeps - 1) x kStarBlocks
-    double *xh = nullptr;          // x_h after t sweeps, t = 0 .. sweeps
-    double ahh = 0.0, dh = 0.0;    // the hub's diagonal and inverse l1 diagonal
+// The V-cycle from a star level down (star.hip): x = diag(delta) b + V E with
+// E_0 = b of the hub and E_m = sum_j A[m - 1][j] b_j, one row of A per sum over
+// the leaves that the hub's recurrence takes (M of them: two per star level
+// above the coarsest and one per coarsest sweep after the first).
+constexpr int kChainChunk = 4096;  // rows per workgroup of the pass that forms E
+constexpr int kStarMaxSweeps = 32;  // coarsest sweeps beyond this keep the sweep kernels
+struct ChainOp {
+    int n = 0, M = 0, hub = -1;  // hub -1: no such operator
+    const double *A = nullptr, *V = nullptr, *delta = nullptr;  // M x n, (M + 1) x n, n
+    double *E = nullptr;  // M x chunks partial sums
+};
+// One star level as the chain kernels see it (agg, p: null on the coarsest).
+struct ChainLevel {
+    int n, hub;
+    const int *rp, *ci;
+    const double *v;
+    double *dinv;
+    const int *agg;
+    const double *p;
+};
+// One pairwise sweep on a fully coupled star (k_star_sweep).
+struct StarSweep {
+    int n;                          // rows of the star
+    const double *v, *w;            // its values and smooth vector
+    const int *hub;                 // its hub row (device; -1: the chain has ended)
+    const double *pc;               // np candidate leaves for the hub: weight, row (-1: none)
+    const int *pi;
+    int np;
+    int *sel, *flags;               // the leaf chosen (-1: none); validation flags
+    int *rp, *ci;                   // the coarse star (n - 1 rows), its smooth vector and hub,
+    double *cv, *cw;                // and the candidates for its own sweep
+    int *hub_out;
+    double *pc_out;
+    int *pi_out;
+    int nf;                         // rows of the level this sweep belongs to
+    const int *agg_prev;            // its earlier sweeps' prolongator (null: none)
+    const double *p_prev;
+    const int *mem_prev;
+    int stride_prev;                // slots per aggregate in mem_prev (1 without)
+    int *agg;                       // composed prolongator and members
+    double *p;
+    int *mem;
 };
 
 // One level of the hierarchy.  Row i of A^k, its l1 inverse diagonal, the
@@ -229,7 +247,7 @@ struct Level {
     void *xs = nullptr;               // W/K-cycle: result of the second coarse cycle (cycle precision)
     void *kv = nullptr;               // K-cycle: A c1, the product of the first coarse direction
     double *S = nullptr;  // coarsest level only: dense sweep operator (n <= kCoarseDense)
-    StarView star;        // coarsest level only: the star recurrence (hub >= 0)
+    ChainOp chain;        // star levels: the V-cycle from this level down (coarsest: its sweeps), hub >= 0
 };
 
 // Device-side view of one level for the single-workgroup tail kernel
@@ -289,6 +307,8 @@ struct bcm_handle {
     int kf = 0;                            // first level of the folded dense operator (0: none):
                                            // the V- or W-cycle from level kf down, as one n_kf x n_kf map
     double *fold = nullptr;                // that operator, n_kf x n_kf row-major, float64
+    int kc = 0;                            // first level of a star chain applied as lv[kc].chain (0: none)
+    int long_star = 0;                     // long rows of the star levels that keep no long-row list
     int *tail_ops = nullptr;               // the tail kernel's program (device)
     int n_tail_ops = 0;
     double *partials = nullptr;
@@ -402,6 +422,30 @@ void launch_fill_i32(hipStream_t s, size_t n, int *dst, int val);
 void launch_fill_u64(hipStream_t s, size_t n, unsigned long long *dst, unsigned long long val);
 void launch_copy_f64(hipStream_t s, size_t n, const double *src, double *dst);
 // dst = src on the finest level's vector length; also a graph-safe fill (no memset node)
+
+// ---- star levels (star.hip) ----
+// out (4 ints, zero before): [0] rows of more than two entries [1] the largest
+// of them [2] != 0: another row is not {diagonal} or {diagonal, one column}
+void launch_star_find(hipStream_t s, int n, const int *rp, const int *ci, int *out);
+// raises out[2] where a leaf's other column is not the hub, out[3] where the
+// hub is not coupled to a leaf or the two values differ
+void launch_star_verify(hipStream_t s, int n, const int *rp, const int *ci, const double *v, int hub, int *out);
+int star_blocks(int n);  // workgroups (= candidates left) of a sweep on a level of n rows
+void launch_star_best(hipStream_t s, int n, const double *v, const double *w, int hub, int *hub_out, double *pc,
+                      int *pi);
+void launch_star_sweep(hipStream_t s, const StarSweep &S);
+// l1 inverse diagonals of nlev fully coupled star levels of at most nmax rows;
+// part: nlev * star_blocks(nmax) doubles
+void launch_star_dinv(hipStream_t s, const ChainLevel *tab, int nlev, int nmax, double *part);
+// The chain of L star levels above a coarsest star (tab: L + 1 levels on the
+// device, n rows on the first): A (chain_sums x n), V (chain_sums + 1) x n and
+// delta (n) of ChainOp.
+int chain_sums(int L, int sweeps);
+size_t chain_scratch(int n, int L, int sweeps);
+void launch_chain_build(hipStream_t s, const ChainLevel *tab, int n, int L, int sweeps, double *scratch, double *A,
+                        double *V, double *delta);
+void launch_chain_dense(hipStream_t s, const ChainOp &C, double *T);  // n x n row-major
+void launch_chain(hipStream_t s, const ChainOp &C, const void *b, void *x, int b_f64, int x_f64, const double *done);
 
 // ---- scan (scan.hip) ----
 size_t scan_tmp_bytes(int n);

@@ -955,135 +955,6 @@ k_jacobi_sweep(int n, const int *__restrict__ rp, const int *__restrict__ ci, co
     }
 }
 
-// block_sum with its final additions spread over the threads:
-// thread k (k < K, K <= blockDim.x) returns sum k, added in block_sum's order.
-template <int K>
-__device__ __forceinline__ double block_sum_spread(double (&v)[K], double *lds) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = group_sum<64>(v[k]);
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < K; ++k) lds[k * 16 + wid] = v[k];
-    __syncthreads();
-    double s = 0.0;
-    if (threadIdx.x < K) {
-        s = lds[threadIdx.x * 16];
-        for (int w = 1; w < nw; ++w) s += lds[threadIdx.x * 16 + w];
-    }
-    __syncthreads();
-    return s;
-}
-
-// The coarse solve on a star level (StarView): E_m over the hub row's
-// entries, m < sweeps - 1, one partial per workgroup and m.
-template <typename VB>
-__global__ void __launch_bounds__(kBlock)
-k_star_sums(StarView sv, int sweeps, const double *__restrict__ dinv, const VB *__restrict__ b,
-            const double *__restrict__ done) {
-    if (done && *done != 0.0) return;
-    constexpr int K = kStarMaxSweeps - 1;
-    __shared__ double lds[K * 16];
-    double acc[K];
-#pragma unroll
-    for (int m = 0; m < K; ++m) acc[m] = 0.0;
-    for (int q = blockIdx.x * kBlock + threadIdx.x; q < sv.nh; q += gridDim.x * kBlock) {
-        const int j = sv.hj[q];
-        const double cj = sv.c[j];
-        double t = sv.ha[q] * (dinv[j] * (double)b[j]);
-#pragma unroll
-        for (int m = 0; m < K; ++m)
-            if (m < sweeps - 1) {
-                acc[m] += t;
-                t *= cj;
-            }
-    }
-    // the workgroup's sums, each finished by its own thread
-    const double e = block_sum_spread<K>(acc, lds);
-    if (threadIdx.x < K) sv.part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = e;
-}
-
-// One workgroup: E_m from the partials (in workgroup order), then the hub's
-// values x_h^(t), t = 0 .. sweeps, by the recurrence; writes x at the hub.
-// The hub's recurrence for S sweeps known at compile time, every value in a
-// register; the same operations in the same order as the loop in k_star_hub.
-constexpr int kCoarseSweeps = 20;  // the coarse solve's default sweep count
-template <int S>
-__device__ __forceinline__ void star_recurrence(const double *se, const double *sf, double bh, const StarView &sv) {
-    double e[S], f[S], xh[S + 1];
-#pragma unroll
-    for (int m = 0; m < S - 1; ++m) { e[m] = se[m]; f[m] = sf[m]; }
-    xh[0] = 0.0;
-#pragma unroll
-    for (int k = 0; k < S; ++k) {
-        double sum = 0.0;
-#pragma unroll
-        for (int t = 0; t < k; ++t) sum += e[k - 1 - t] - f[k - 1 - t] * xh[t];
-        xh[k + 1] = xh[k] + sv.dh * (bh - (sv.ahh * xh[k] + sum));
-    }
-#pragma unroll
-    for (int t = 0; t <= S; ++t) sv.xh[t] = xh[t];
-}
-
-template <typename VB, typename VX>
-__global__ void __launch_bounds__(kBlock)
-k_star_hub(StarView sv, int sweeps, const VB *__restrict__ b, VX *__restrict__ x, const double *__restrict__ done) {
-    if (done && *done != 0.0) return;
-    constexpr int K = kStarMaxSweeps - 1;
-    __shared__ double lds[K * 16];
-    __shared__ double se[K], sf[K], xh[kStarMaxSweeps + 1];  // the recurrence reads these at run-time indices
-    if (threadIdx.x < K) sf[threadIdx.x] = threadIdx.x < sweeps - 1 ? sv.F[threadIdx.x] : 0.0;
-    double e[K];
-#pragma unroll
-    for (int m = 0; m < K; ++m) e[m] = 0.0;
-    add_partials<K, 1>(e, sv.part, kStarBlocks);
-    const double em = block_sum_spread<K>(e, lds);
-    if (threadIdx.x < K) se[threadIdx.x] = em;
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    const double bh = (double)b[sv.hub];
-    if (sweeps == kCoarseSweeps) {
-        star_recurrence<kCoarseSweeps>(se, sf, bh, sv);  // in registers: no LDS round trip per term
-    } else {
-        xh[0] = 0.0;
-        for (int k = 0; k < sweeps; ++k) {
-            double sum = 0.0;  // the hub row's product after k sweeps, off the diagonal
-            for (int t = 0; t < k; ++t) sum += se[k - 1 - t] - sf[k - 1 - t] * xh[t];
-            xh[k + 1] = xh[k] + sv.dh * (bh - (sv.ahh * xh[k] + sum));
-        }
-        for (int t = 0; t <= sweeps; ++t) sv.xh[t] = xh[t];
-    }
-    x[sv.hub] = (VX)sv.xh[sweeps];
-}
-
-// Every row but the hub: its sweeps with the hub's values x_h^(t), each in
-// the order and rounding of k_jacobi_sweep (the row's two products in column
-// order).
-template <typename VB, typename VX>
-__global__ void __launch_bounds__(kBlock)
-k_star_rows(StarView sv, int n, int sweeps, const int *__restrict__ rp, const int *__restrict__ ci,
-            const double *__restrict__ a, const double *__restrict__ dinv, const VB *__restrict__ b,
-            VX *__restrict__ x, const double *__restrict__ done) {
-    if (done && *done != 0.0) return;
-    const int j = blockIdx.x * kBlock + threadIdx.x;
-    if (j >= n || j == sv.hub) return;
-    const int s0 = rp[j], e0 = rp[j + 1];
-    double ajj = 0.0, ajh = 0.0;
-    bool hub_first = false;
-    for (int q = s0; q < e0; ++q) {
-        if (ci[q] == j) ajj = a[q];
-        else { ajh = a[q]; hub_first = q == s0; }
-    }
-    const double dj = dinv[j], bj = (double)b[j];
-    double xj = 0.0;
-    for (int t = 0; t < sweeps; ++t) {
-        const double xt = sv.xh[t];
-        const double rs = hub_first ? ajh * xt + ajj * xj : ajj * xj + ajh * xt;
-        xj = xj + dj * (bj - rs);
-    }
-    x[j] = (VX)xj;
-}
-
 // ----------------------------------------------------------------------------
 // Flexible CG kernels (Algorithm 3).  Fixed grid of nb blocks with a
 // grid-stride loop over row groups; every block stores its partial sums and a
@@ -1418,12 +1289,8 @@ void coarse_t(hipStream_t s, const Level &L, int sweeps, const VB *b, VX *x, dou
                            b, x, sweeps, 0, done);
         return;
     }
-    if (L.star.hub >= 0 && sweeps >= 1 && sweeps <= kStarMaxSweeps) {
-        // a star: the sweeps as the hub's recurrence (three launches instead of one per sweep)
-        hipLaunchKernelGGL((k_star_sums<VB>), dim3(kStarBlocks), dim3(kBlock), 0, s, L.star, sweeps, L.dinv, b, done);
-        hipLaunchKernelGGL((k_star_hub<VB, VX>), dim3(1), dim3(kBlock), 0, s, L.star, sweeps, b, x, done);
-        hipLaunchKernelGGL((k_star_rows<VB, VX>), dim3(blocks_for(n)), dim3(kBlock), 0, s, L.star, n, sweeps, L.A.rp,
-                           L.A.ci, L.A.v, L.dinv, b, x, done);
+    if (L.chain.hub >= 0) {  // a star: the sweeps as one linear map (two launches instead of one per sweep)
+        launch_chain(s, L.chain, b, x, std::is_same<VB, double>::value, std::is_same<VX, double>::value, done);
         return;
     }
     double *xo = ta, *xn = tb;
