@@ -152,6 +152,90 @@ k_weights(int n, const int *__restrict__ rp, const int *__restrict__ ci, const d
 // there; the rank of c_uv seen from v is counted over row v's weights (c_vu
 // is the same double as c_uv), all of whose loads are issued together.
 // ----------------------------------------------------------------------------
+// Rank of c_uv (u = row) seen from v: counted over row v, or read from rk at
+// the transposed position when v is a long row.
+__device__ __forceinline__ unsigned cand_rank(int row, int vtx, double cq, const int *__restrict__ rp,
+                                              const int *__restrict__ ci, const double *__restrict__ c,
+                                              const unsigned *__restrict__ rk, int lmin) {
+    const int b2 = rp[vtx], e2 = rp[vtx + 1];
+    if (lmin > 0 && e2 - b2 > lmin) {
+        int lo = b2, hi = e2;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (ci[mid] < row) lo = mid + 1; else hi = mid;
+        }
+        return (lo < e2 && ci[lo] == row) ? rk[lo] : 0u;
+    }
+    unsigned r = 0;
+#pragma unroll 8
+    for (int t = b2; t < e2; ++t) r += (c[t] < cq) ? 1u : 0u;
+    return r;
+}
+
+// One row by GL lanes (lane = 0 .. GL - 1), its d entries in the LDS arrays C, V.
+template <int GL>
+__device__ __forceinline__ void cand_row(int row, int lane, int s0, int d, const int *__restrict__ rp,
+                                         const int *__restrict__ ci, const double *__restrict__ c,
+                                         const unsigned *__restrict__ rk, unsigned long long *__restrict__ cand,
+                                         int lmin, double *C, int *V) {
+    const int e = s0 + d;
+    for (int k = lane; k < d; k += GL) {
+        C[k] = c[s0 + k];
+        V[k] = ci[s0 + k];
+    }
+    wave_sync();
+    int nelig = 0;
+    for (int k = lane; k < d; k += GL) {
+        const int vtx = V[k];
+        const double cq = C[k];
+        if (!(vtx != row && cq > 0.0 && cq < INFINITY)) continue;
+        ++nelig;
+        int before = 0;
+        for (int t = 0; t < d; ++t) {
+            const int vt = V[t];
+            const double ct = C[t];
+            const bool elig = vt != row && ct > 0.0 && ct < INFINITY;
+            before += (elig && (ct > cq || (ct == cq && vt > vtx))) ? 1 : 0;
+        }
+        if (before < d - 1)
+            cand[s0 + before] = ((unsigned long long)cand_rank(row, vtx, cq, rp, ci, c, rk, lmin) << 32) | (unsigned)vtx;
+    }
+    nelig = min(group_sum<GL>(nelig), max(d - 1, 0));
+    for (int q = s0 + nelig + lane; q < e; q += GL) cand[q] = ~0ull;
+}
+
+// A row that does not fit the LDS slots (lane groups of 32 and more): the same
+// with its entries in global memory, by the 64 lanes of a wave.
+__device__ __forceinline__ void cand_row_global(int row, int lane, int s0, int d, const int *__restrict__ rp,
+                                                const int *__restrict__ ci, const double *__restrict__ c,
+                                                const unsigned *__restrict__ rk,
+                                                unsigned long long *__restrict__ cand, int lmin) {
+    const int e = s0 + d;
+    int nelig = 0;
+    for (int k = s0 + lane; k < e; k += 64) {
+        const int vtx = ci[k];
+        const double cq = c[k];
+        if (!(vtx != row && cq > 0.0 && cq < INFINITY)) continue;
+        ++nelig;
+        int before = 0;
+        for (int t = s0; t < e; ++t) {
+            const int vt = ci[t];
+            const double ct = c[t];
+            const bool elig = vt != row && ct > 0.0 && ct < INFINITY;
+            before += (elig && (ct > cq || (ct == cq && vt > vtx))) ? 1 : 0;
+        }
+        if (before < d - 1)
+            cand[s0 + before] = ((unsigned long long)cand_rank(row, vtx, cq, rp, ci, c, rk, lmin) << 32) | (unsigned)vtx;
+    }
+    nelig = min(group_sum<64>(nelig), d - 1);
+    for (int q = s0 + nelig + lane; q < e; q += 64) cand[q] = ~0ull;
+}
+
+// Rows of up to 4 G entries: a group each.  The longer ones of a wave (up to
+// lmin = 16 G entries) then take all its 64 lanes in turn, in the LDS of the
+// whole wave (at least 256 entries): with one group of 8 lanes and their
+// entries in global memory, a few rows of 100 entries set the time of a level
+// whose other rows hold four (64^3 diffusion, 5,427 rows: 175 us a launch).
 template <int G>
 __global__ void __launch_bounds__(kBlock)
 k_candidates_direct(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ c,
@@ -164,57 +248,32 @@ k_candidates_direct(int n, const int *__restrict__ rp, const int *__restrict__ c
     // groups' slots one element apart (stride LS + 1): the groups of a wave
     // reading the same slot index hit different LDS banks
     constexpr int LSP = LS + 1;
+    constexpr int WS = (64 / G) * LSP;  // slots of a wave
     __shared__ double sc[NG * LSP];
     __shared__ int sv[NG * LSP];
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
     const int row = (xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x) / G;
-    if (row >= n) return;
-    const int s0 = rp[row], e = rp[row + 1], d = e - s0;
-    if (lmin > 0 && d > lmin) return;
-    auto rank_at = [&](int vtx, double cq) -> unsigned {
-        const int b2 = rp[vtx], e2 = rp[vtx + 1];
-        if (lmin > 0 && e2 - b2 > lmin) {
-            int lo = b2, hi = e2;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (ci[mid] < row) lo = mid + 1; else hi = mid;
-            }
-            return (lo < e2 && ci[lo] == row) ? rk[lo] : 0u;
-        }
-        unsigned r = 0;
-#pragma unroll 8
-        for (int t = b2; t < e2; ++t) r += (c[t] < cq) ? 1u : 0u;
-        return r;
-    };
-    const bool staged = d <= LS;
-    double *C = sc + g * LSP;
-    int *V = sv + g * LSP;
-    if (staged) {
-        for (int k = lane; k < d; k += G) {
-            C[k] = c[s0 + k];
-            V[k] = ci[s0 + k];
+    int s0 = 0, d = 0;
+    if (row < n) {
+        s0 = rp[row];
+        d = rp[row + 1] - s0;
+        if (lmin > 0 && d > lmin) d = 0;
+    }
+    if (d > 0 && d <= LS) cand_row<G>(row, lane, s0, d, rp, ci, c, rk, cand, lmin, sc + g * LSP, sv + g * LSP);
+    unsigned long long mid = __ballot(lane == 0 && d > LS);
+    if (mid == 0ull) return;
+    wave_sync();  // the groups' slots are free from here on
+    const int w0 = (threadIdx.x >> 6) * WS, wl = threadIdx.x & 63;
+    for (; mid; mid &= mid - 1) {
+        const int from = __ffsll(mid) - 1;
+        const int r2 = __shfl(row, from, 64), b2 = __shfl(s0, from, 64), d2 = __shfl(d, from, 64);
+        if (d2 <= WS) {
+            cand_row<64>(r2, wl, b2, d2, rp, ci, c, rk, cand, lmin, sc + w0, sv + w0);
+        } else {
+            cand_row_global(r2, wl, b2, d2, rp, ci, c, rk, cand, lmin);
         }
         wave_sync();
     }
-    const double *Cr = staged ? C : c + s0;
-    const int *Vr = staged ? V : ci + s0;
-    int nelig = 0;
-    for (int k = lane; k < d; k += G) {
-        const int vtx = Vr[k];
-        const double cq = Cr[k];
-        if (!(vtx != row && cq > 0.0 && cq < INFINITY)) continue;
-        ++nelig;
-        int before = 0;
-        for (int t = 0; t < d; ++t) {
-            const int vt = Vr[t];
-            const double ct = Cr[t];
-            const bool elig = vt != row && ct > 0.0 && ct < INFINITY;
-            before += (elig && (ct > cq || (ct == cq && vt > vtx))) ? 1 : 0;
-        }
-        if (before < d - 1) cand[s0 + before] = ((unsigned long long)rank_at(vtx, cq) << 32) | (unsigned)vtx;
-    }
-    nelig = min(group_sum<G>(nelig), max(d - 1, 0));
-    for (int q = s0 + nelig + lane; q < e; q += G) cand[q] = ~0ull;
 }
 
 // ----------------------------------------------------------------------------
@@ -1399,50 +1458,27 @@ void launch_aggfill(hipStream_t s, int n, const int *mate, const int *ofs, const
     hipLaunchKernelGGL(k_aggfill, dim3(blocks_for(n)), dim3(kBlock), 0, s, n, mate, ofs, w, agg, p, wc, mem2);
 }
 
-// Rows with at most 4 G candidates: each candidate's column F, key (m, M) and
-// term (p_m a_ij) p_M are formed once, with all loads of the row in flight
-// together, and kept in LDS; the distinct columns, their ranks and their (at
-// most four) terms are then found by comparing LDS entries only.  Longer rows
-// take gal_row's scratch path.
-template <int G>
-__global__ void __launch_bounds__(kBlock)
-k_gal(int pass, int nc, const int *__restrict__ rp, const int *__restrict__ ci,
-      const double *__restrict__ v, const int *__restrict__ agg, const double *__restrict__ p,
-      const int *__restrict__ mem2, int *__restrict__ cnt, const int *__restrict__ crp,
-      int *__restrict__ cci, double *__restrict__ cv, int *__restrict__ gF, int *__restrict__ gU, int lmin) {
+// One coarse row E by GL lanes, its L <= 4 GL candidates in the LDS arrays F,
+// first, K, T: each candidate's column F, key (m, M) and term (p_m a_ij) p_M are
+// formed once, with all loads of the row in flight together; the distinct
+// columns, their ranks and their (at most four) terms are then found by
+// comparing LDS entries only.
+struct GalRow {
+    int E, e0, e1, s0, L0, s1, L;
+};
+template <int GL>
+__device__ __forceinline__ void gal_staged(int pass, const GalRow &R, int lane, const int *__restrict__ ci,
+                                           const double *__restrict__ v, const int *__restrict__ agg,
+                                           const double *__restrict__ p, int *__restrict__ cnt,
+                                           const int *__restrict__ crp, int *__restrict__ cci,
+                                           double *__restrict__ cv, int *F, int *first, unsigned long long *K,
+                                           double *T) {
     constexpr int SL = 4;  // candidate slots per lane
-    constexpr int LS = SL * G;
-    constexpr int NG = kBlock / G;
-    // groups' slots one element apart (stride LS + 1): the groups of a wave
-    // reading the same slot index hit different LDS banks
-    constexpr int LSP = LS + 1;
-    __shared__ int sf[NG * LSP];
-    __shared__ int sfirst[NG * LSP];
-    __shared__ unsigned long long skey[NG * LSP];
-    __shared__ double st[NG * LSP];
-    const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int E = xcd_block(blockIdx.x, gridDim.x) * NG + g;
-    if (E >= nc) return;
-    const int e0 = mem2[2 * E], e1 = mem2[2 * E + 1];
-    const int s0 = rp[e0], L0 = rp[e0 + 1] - s0;
-    const int s1 = e1 >= 0 ? rp[e1] : 0;
-    const int L1 = e1 >= 0 ? rp[e1 + 1] - s1 : 0;
-    const int L = L0 + L1;
-    if (lmin > 0 && L > lmin) {  // a long coarse row: k_gal_long adds its count
-        if (pass == 0 && lane == 0) cnt[E] = 0;
-        return;
-    }
-    if (L > LS) {
-        gal_row<G>(pass, E, lane, rp, ci, v, agg, p, e0, e1, s0, L0, s1, L1, cnt, crp, cci, cv, gF, gU, false);
-        return;
-    }
-    int *F = sf + g * LSP, *first = sfirst + g * LSP;
-    unsigned long long *K = skey + g * LSP;
-    double *T = st + g * LSP;
+    const int L = R.L, L0 = R.L0, s0 = R.s0, s1 = R.s1, e0 = R.e0, e1 = R.e1;
     const double pe0 = pass ? p[e0] : 0.0, pe1 = (pass && e1 >= 0) ? p[e1] : 0.0;
 #pragma unroll
     for (int sl = 0; sl < SL; ++sl) {
-        const int k = lane + sl * G;
+        const int k = lane + sl * GL;
         if (k >= L) continue;
         const int q = k < L0 ? s0 + k : s1 + (k - L0);
         const int j = ci[q];
@@ -1462,7 +1498,7 @@ k_gal(int pass, int nc, const int *__restrict__ rp, const int *__restrict__ ci,
     int nu = 0;
 #pragma unroll
     for (int sl = 0; sl < SL; ++sl) {
-        const int k = lane + sl * G;
+        const int k = lane + sl * GL;
         if (k >= L) continue;
         const int f = F[k];
         int fk = 1;
@@ -1471,16 +1507,16 @@ k_gal(int pass, int nc, const int *__restrict__ rp, const int *__restrict__ ci,
         nu += fk;
     }
     if (pass == 0) {
-        nu = group_sum<G>(nu);
-        if (lane == 0) cnt[E] = nu;
+        nu = group_sum<GL>(nu);
+        if (lane == 0) cnt[R.E] = nu;
         return;
     }
     wave_sync();
-    const int base = crp[E];
+    const int base = crp[R.E];
     const unsigned long long NONE = ~0ull;
 #pragma unroll
     for (int sl = 0; sl < SL; ++sl) {
-        const int k = lane + sl * G;
+        const int k = lane + sl * GL;
         if (k >= L || !(first[k] & 1)) continue;
         const int f = F[k];
         // rank among the distinct columns; the (at most four) candidates of
@@ -1515,6 +1551,60 @@ k_gal(int pass, int nc, const int *__restrict__ rp, const int *__restrict__ ci,
             if (key[r] != NONE) sum = sum + t[r];
         cci[base + rank] = f;
         cv[base + rank] = sum;
+    }
+}
+
+// Rows with at most 4 G candidates: a group each.  The longer ones of a wave (up
+// to lmin = 16 G candidates) then take all its 64 lanes in turn, in the LDS of
+// the whole wave (at least 256 candidates): with one group of 8 lanes and the
+// columns in global scratch they set the launch's time (64^3 diffusion, levels
+// of about 5,000 rows: 218 us a launch on average).  More candidates than that
+// take gal_row's scratch path.
+template <int G>
+__global__ void __launch_bounds__(kBlock)
+k_gal(int pass, int nc, const int *__restrict__ rp, const int *__restrict__ ci,
+      const double *__restrict__ v, const int *__restrict__ agg, const double *__restrict__ p,
+      const int *__restrict__ mem2, int *__restrict__ cnt, const int *__restrict__ crp,
+      int *__restrict__ cci, double *__restrict__ cv, int *__restrict__ gF, int *__restrict__ gU, int lmin) {
+    constexpr int LS = 4 * G;
+    constexpr int NG = kBlock / G;
+    // groups' slots one element apart (stride LS + 1): the groups of a wave
+    // reading the same slot index hit different LDS banks
+    constexpr int LSP = LS + 1;
+    constexpr int WS = (64 / G) * LSP;  // slots of a wave
+    __shared__ int sf[NG * LSP];
+    __shared__ int sfirst[NG * LSP];
+    __shared__ unsigned long long skey[NG * LSP];
+    __shared__ double st[NG * LSP];
+    const int g = threadIdx.x / G, lane = threadIdx.x % G;
+    GalRow R{xcd_block((int)blockIdx.x, (int)gridDim.x) * NG + g, -1, -1, 0, 0, 0, 0};
+    if (R.E < nc) {
+        R.e0 = mem2[2 * R.E];
+        R.e1 = mem2[2 * R.E + 1];
+        R.s0 = rp[R.e0];
+        R.L0 = rp[R.e0 + 1] - R.s0;
+        R.s1 = R.e1 >= 0 ? rp[R.e1] : 0;
+        R.L = R.L0 + (R.e1 >= 0 ? rp[R.e1 + 1] - R.s1 : 0);
+        if (lmin > 0 && R.L > lmin) R.L = 0;  // a long coarse row: k_gal_long adds its count
+        if (R.L == 0 && pass == 0 && lane == 0) cnt[R.E] = 0;
+    }
+    if (R.L > 0 && R.L <= LS)
+        gal_staged<G>(pass, R, lane, ci, v, agg, p, cnt, crp, cci, cv, sf + g * LSP, sfirst + g * LSP,
+                      skey + g * LSP, st + g * LSP);
+    unsigned long long mid = __ballot(lane == 0 && R.L > LS);
+    if (mid == 0ull) return;
+    wave_sync();  // the groups' slots are free from here on
+    const int w0 = (threadIdx.x >> 6) * WS, wl = threadIdx.x & 63;
+    for (; mid; mid &= mid - 1) {
+        const int from = __ffsll(mid) - 1;
+        const GalRow W{__shfl(R.E, from, 64),  __shfl(R.e0, from, 64), __shfl(R.e1, from, 64), __shfl(R.s0, from, 64),
+                       __shfl(R.L0, from, 64), __shfl(R.s1, from, 64), __shfl(R.L, from, 64)};
+        if (W.L <= 256)
+            gal_staged<64>(pass, W, wl, ci, v, agg, p, cnt, crp, cci, cv, sf + w0, sfirst + w0, skey + w0, st + w0);
+        else
+            gal_row<64>(pass, W.E, wl, rp, ci, v, agg, p, W.e0, W.e1, W.s0, W.L0, W.s1, W.L - W.L0, cnt, crp, cci, cv,
+                        gF, gU, false);
+        wave_sync();
     }
 }
 
