@@ -1238,19 +1238,20 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             const size_t nn2 = (size_t)C.A.n * C.A.n;
             C.S = h->persist.get_n<double>(nn2);
             NOMEM(C.S);
-            if (C.A.n <= kCoarseBuildSweeps && C.lr.n == 0) {
-                // one workgroup per unit vector runs the sweeps
+            if (coarse_in_lds(C.A.n, C.A.nnz, C.lr.n > 0)) {
+                // one workgroup per unit vector runs the sweeps on the matrix in
+                // its LDS (without it, each would stream the matrix through one
+                // CU: 866 rows with 362,762 entries took 55 ms)
                 launch_coarse_build(s, C, P.coarse_sweeps, C.S);
             } else {
-                // S_{t+1} = D + (I - DA) S_t from S_0 = 0 on the whole matrix at once
                 tmp.rewind();
-                double *W = tmp.get_n<double>(nn2);
-                NOMEM(W);
-                double *cur = (P.coarse_sweeps % 2) ? W : C.S, *nxt = (P.coarse_sweeps % 2) ? C.S : W;
-                launch_fill_i32(s, 2 * nn2, (int *)cur, 0);
-                for (int t = 0; t < P.coarse_sweeps; ++t) {
-                    launch_fold_left(s, C, cur, nxt);
-                    std::swap(cur, nxt);
+                double *W = tmp.get_n<double>(nn2), *M = tmp.get_n<double>(nn2), *Ad = tmp.get_n<double>(nn2);
+                NOMEM(W && M && Ad);
+                if (P.coarse_sweeps > 1) {
+                    launch_sweep_operator(s, C, P.coarse_sweeps, P.check != 0, C.S, W, M, Ad);
+                } else {  // one sweep from zero: D
+                    launch_fill_i32(s, 2 * nn2, (int *)W, 0);
+                    launch_fold_left(s, C, W, C.S);
                 }
             }
         }
@@ -1289,7 +1290,7 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
                 if (wcyc) {  // the coarse problem solved by two cycles of level k + 1
                     double *M = tmp.get_n<double>(nc2), *W = tmp.get_n<double>(nc2);
                     NOMEM(M && W);
-                    launch_fold_w(s, C, Tc, M, W);
+                    launch_fold_w(s, C, Tc, M, W, P.check != 0);
                     Tc = W;
                 }
                 double *T = k == kf ? h->persist.get_n<double>(nn2) : tmp.get_n<double>(nn2);

@@ -35,7 +35,6 @@ inline void launch_k(F kernel, dim3 grid, dim3 block, hipStream_t s, Args... arg
 constexpr int kMaxLevels = 64;
 constexpr int kCoarseLds = 8192;   // largest coarsest level solved inside one workgroup
 constexpr int kCoarseDense = 2048; // largest coarsest level applied as a precomputed dense operator
-constexpr int kCoarseBuildSweeps = 1024;  // up to this size S is built by sweeps on unit vectors
 constexpr int kFoldRows = 2048;    // V-cycle: levels from the first this small on form one dense operator
 constexpr int kSplitUp = 65536;    // levels at least this large run the up leg as prolong + smooth
 constexpr int kGatherRow = 16;     // sliced-ELL levels averaging this many entries per row gather dinv o b
@@ -502,7 +501,12 @@ void launch_coarse_build(hipStream_t s, const Level &L, int sweeps, double *S);
 void launch_fold_level(hipStream_t s, const Level &L, const double *Tc, int nc, double *H, double *T);
 // W-cycle coarse solve of the level above L by two cycles of L: W = 2T - T A T
 // (T, W n x n row-major; M n x n scratch)
-void launch_fold_w(hipStream_t s, const Level &L, const double *T, double *M, double *W);
+// sym: A (and so T) is known to be exactly symmetric
+void launch_fold_w(hipStream_t s, const Level &L, const double *T, double *M, double *W, bool sym);
+// S = sum_{t < sweeps} (I - D A)^t D of the coarsest level, n x n, sweeps >= 2
+// (W, M, Ad: n x n scratch)
+void launch_sweep_operator(hipStream_t s, const Level &L, int sweeps, bool sym, double *S, double *W, double *M,
+                           double *Ad);
 // T = D + (I - D A) H for dense n x n row-major H and T (level L's matrix)
 void launch_fold_left(hipStream_t s, const Level &L, const double *H, double *T);
 // x = T b with a dense n x n row-major float64 operator (float64 accumulation)

@@ -725,64 +725,164 @@ k_fold_h(int n, int nc, const int *__restrict__ rp, const int *__restrict__ ci, 
 
 // W-cycle: the coarse problem of a level is solved by two cycles of the level
 // below, the second on the residual of the first: W = T + T (I - A T) = 2T - T A T.
-// M = A T (sparse rows of A against the dense columns of T):
+// M = A T: k_fold_t<true>; T M: k_gemm.
+
+// Dense products of the operators above, float64 on the matrix cores:
+// P = X Y for row-major n x n X and Y, then
+//   kGemmPlain   out = P
+//   kGemmTwice   out = 2 X - P   (with sym: X Y symmetric, only the tiles on and
+//                below the diagonal are formed and each is written twice)
+//   kGemmSweep   out = D + Y - D P
+// One 64 x 64 tile per workgroup, 32 x 32 per wave as 2 x 2 MFMA 16x16x4 tiles, 64
+// columns of X and rows of Y per step staged in LDS while the next step's loads
+// are in flight.  A few hundred tiles are one or two workgroups per CU, so a
+// step lasts as long as its loads: 16 columns a step made 55 of them at 866 rows
+// (83 us), 64 make 14 (63 us; 1749 rows, symmetric: 245 -> 174 us, 31 TFLOP/s of
+// the products formed).
+enum : int { kGemmPlain = 0, kGemmTwice = 1, kGemmSweep = 2 };
+constexpr int kGemmTile = 64, kGemmK = 64;
+constexpr int kGemmX = kGemmK + 4, kGemmY = kGemmTile + 16;  // LDS strides: a wave's fragment hits every bank equally
+typedef double v4d __attribute__((ext_vector_type(4)));
+template <int Mode>
 __global__ void __launch_bounds__(kBlock)
-k_fold_at(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
-          const double *__restrict__ T, double *__restrict__ M) {
-    const long long idx = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= (long long)n * n) return;
-    const int i = (int)(idx / n), j = (int)(idx % n);
-    double s = 0.0;
-    for (int q = rp[i]; q < rp[i + 1]; ++q) s += a[q] * T[(size_t)ci[q] * n + j];
-    M[idx] = s;
+k_gemm(int n, int sym, const double *__restrict__ X, const double *__restrict__ Y, const double *__restrict__ dinv,
+       double *__restrict__ out) {
+    __shared__ double xs[kGemmTile][kGemmX], ys[kGemmK][kGemmY];
+    const int nt = (n + kGemmTile - 1) / kGemmTile;
+    int ti, tj;
+    if (sym) {  // tile index t = ti (ti + 1) / 2 + tj, tj <= ti
+        const int t = blockIdx.x;
+        ti = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+        while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
+        while (ti * (ti + 1) / 2 > t) --ti;
+        tj = t - ti * (ti + 1) / 2;
+    } else {
+        ti = blockIdx.x / nt;
+        tj = blockIdx.x % nt;
+    }
+    const int i0 = ti * kGemmTile, j0 = tj * kGemmTile;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int wi = (wv >> 1) * 32, wj = (wv & 1) * 32;
+    // this thread's entries of each staged block: one column of X and of Y, every fourth row
+    constexpr int U = kGemmTile * kGemmK / kBlock;
+    double xv[U], yv[U];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + wv + 4 * u, kx = k0 + lane;
+            xv[u] = i < n && kx < n ? X[(size_t)i * n + kx] : 0.0;
+            const int j = j0 + lane, ky = k0 + wv + 4 * u;
+            yv[u] = j < n && ky < n ? Y[(size_t)ky * n + j] : 0.0;
+        }
+    };
+    v4d acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
+    load(0);
+    for (int k0 = 0; k0 < n; k0 += kGemmK) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            xs[wv + 4 * u][lane] = xv[u];
+            ys[wv + 4 * u][lane] = yv[u];
+        }
+        __syncthreads();
+        if (k0 + kGemmK < n) load(k0 + kGemmK);
+#pragma unroll 4
+        for (int kk = 0; kk < kGemmK; kk += 4) {
+            const int k = kk + (lane >> 4), c = lane & 15;
+            const double a0 = xs[wi + c][k], a1 = xs[wi + 16 + c][k], b0 = ys[k][wj + c], b1 = ys[k][wj + 16 + c];
+            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                // accumulator r of lane l: row 4 r + l / 16, column l % 16
+                const int i = i0 + wi + 16 * a + 4 * r + (lane >> 4), j = j0 + wj + 16 * b + (lane & 15);
+                if (i >= n || j >= n) continue;
+                const size_t o = (size_t)i * n + j;
+                const double p = acc[a][b][r];
+                if (Mode == kGemmPlain) {
+                    out[o] = p;
+                } else if (Mode == kGemmSweep) {
+                    out[o] = (i == j ? dinv[i] : 0.0) + Y[o] - dinv[i] * p;
+                } else {
+                    if (sym && j > i) continue;  // (a diagonal tile: its lower half)
+                    const double w = 2.0 * X[o] - p;
+                    out[o] = w;
+                    if (sym && i != j) out[(size_t)j * n + i] = w;
+                }
+            }
 }
 
-// W_ij = 2 T_ij - sum_k T_ik M_kj (one thread per entry; the row of T is
-// shared by the wave, the column of M read coalesced)
+// A as a dense matrix (zeroed before)
 __global__ void __launch_bounds__(kBlock)
-k_fold_w(int n, const double *__restrict__ T, const double *__restrict__ M, double *__restrict__ W) {
-    const long long idx = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= (long long)n * n) return;
-    const int i = (int)(idx / n), j = (int)(idx % n);
-    const double *ti = T + (size_t)i * n;
-    double s = 0.0;
-    for (int k = 0; k < n; ++k) s += ti[k] * M[(size_t)k * n + j];
-    W[idx] = 2.0 * T[idx] - s;
+k_dense_scatter(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
+                double *__restrict__ out) {
+    const int i = (blockIdx.x * kBlock + threadIdx.x) / 64, lane = threadIdx.x & 63;
+    if (i >= n) return;
+    for (int q = rp[i] + lane; q < rp[i + 1]; q += 64) out[(size_t)i * n + ci[q]] = a[q];
 }
 
-// T = D + (I - D A) H:  T_ij = [i = j] dinv_i + H_ij - dinv_i sum_{k in row i} a_ik H_kj
+// Two l1-Jacobi sweeps from zero, S_2 = 2 D - D A D (zeroed before)
+__global__ void __launch_bounds__(kBlock)
+k_sweep2(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
+         const double *__restrict__ dinv, double *__restrict__ out) {
+    const int i = (blockIdx.x * kBlock + threadIdx.x) / 64, lane = threadIdx.x & 63;
+    if (i >= n) return;
+    const double di = dinv[i];
+    for (int q = rp[i] + lane; q < rp[i + 1]; q += 64) {
+        const int j = ci[q];
+        out[(size_t)i * n + j] = (i == j ? 2.0 * di : 0.0) - (di * a[q]) * dinv[j];
+    }
+}
+
+// T = D + (I - D A) H:  T_ij = [i = j] dinv_i + H_ij - dinv_i sum_{k in row i} a_ik H_kj,
+// or (At) T = A H.
 // One wave per row i and 64 consecutive columns j: row i's entries are the
 // same for the whole wave (scalar loads), each H load is one contiguous
-// access, and four entries' loads are issued per step.  The sum runs over
-// row i in order, as with one thread per entry.
+// access, and eight entries' loads are issued per step.  The sum runs over
+// row i in order, as with one thread per entry.  The rows of one panel of 64
+// columns go to one XCD after the other's: the panel (n x 512 B, 1 MB at 2048
+// rows) then stays in that XCD's L2, where rows first streamed all of H from
+// beyond it for every entry of A.
 constexpr int kFoldCols = 64;
 inline long long fold_t_threads(int n) { return (long long)n * ((n + kFoldCols - 1) / kFoldCols) * kFoldCols; }
+template <bool At>
 __global__ void __launch_bounds__(kBlock)
 k_fold_t(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
          const double *__restrict__ dinv, const double *__restrict__ H, double *__restrict__ T) {
+    constexpr int U = 8;
     const int nch = (n + kFoldCols - 1) / kFoldCols;
-    const long long wv = ((long long)blockIdx.x * kBlock + threadIdx.x) / kFoldCols;
-    if (wv >= (long long)n * nch) return;
-    const int i = __builtin_amdgcn_readfirstlane((int)(wv / nch));
-    const int jc = __builtin_amdgcn_readfirstlane((int)(wv % nch));
+    const int wv = xcd_block(blockIdx.x, gridDim.x) * (kBlock / kFoldCols) + (int)threadIdx.x / kFoldCols;
+    if (wv >= n * nch) return;
+    const int i = __builtin_amdgcn_readfirstlane(wv % n);
+    const int jc = __builtin_amdgcn_readfirstlane(wv / n);
     const int j = jc * kFoldCols + (int)(threadIdx.x % kFoldCols);
     const int jj = j < n ? j : n - 1;  // lanes past the last column read a valid one and store nothing
     const int e = rp[i + 1];
     int q = rp[i];
+    const size_t idx = (size_t)i * n + jj;
+    const double di = At ? 0.0 : dinv[i], hi = At ? 0.0 : H[idx];
     double s = 0.0;
-    for (; q + 4 <= e; q += 4) {
-        const double h0 = H[(size_t)ci[q] * n + jj], h1 = H[(size_t)ci[q + 1] * n + jj];
-        const double h2 = H[(size_t)ci[q + 2] * n + jj], h3 = H[(size_t)ci[q + 3] * n + jj];
-        s += a[q] * h0;
-        s += a[q + 1] * h1;
-        s += a[q + 2] * h2;
-        s += a[q + 3] * h3;
+    for (; q + U <= e; q += U) {
+        double h[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) h[u] = H[(size_t)ci[q + u] * n + jj];
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += a[q + u] * h[u];
     }
     for (; q < e; ++q) s += a[q] * H[(size_t)ci[q] * n + jj];
-    if (j < n) {
-        const size_t idx = (size_t)i * n + j;
-        T[idx] = (i == j ? dinv[i] : 0.0) + H[idx] - dinv[i] * s;
-    }
+    if (j < n) T[idx] = At ? s : (i == j ? di : 0.0) + hi - di * s;
 }
 
 // ----------------------------------------------------------------------------
@@ -1461,20 +1561,79 @@ void launch_fold_level(hipStream_t s, const Level &L, const double *Tc, int nc, 
     const int n = L.A.n;
     const int nb = blocks_for((long long)n * n);
     hipLaunchKernelGGL(k_fold_h, dim3(nb), dim3(kBlock), 0, s, n, nc, L.A.rp, L.A.ci, L.A.v, L.dinv, L.p, L.agg, Tc, H);
-    hipLaunchKernelGGL(k_fold_t, dim3(blocks_for(fold_t_threads(n))), dim3(kBlock), 0, s, n, L.A.rp, L.A.ci, L.A.v,
+    hipLaunchKernelGGL(k_fold_t<false>, dim3(blocks_for(fold_t_threads(n))), dim3(kBlock), 0, s, n, L.A.rp, L.A.ci, L.A.v,
                        L.dinv, H, T);
 }
 
-void launch_fold_w(hipStream_t s, const Level &L, const double *T, double *M, double *W) {
+namespace {
+// M = A T
+void launch_fold_at(hipStream_t s, const Level &L, const double *T, double *M) {
     const int n = L.A.n;
-    const int nb = blocks_for((long long)n * n);
-    hipLaunchKernelGGL(k_fold_at, dim3(nb), dim3(kBlock), 0, s, n, L.A.rp, L.A.ci, L.A.v, T, M);
-    hipLaunchKernelGGL(k_fold_w, dim3(nb), dim3(kBlock), 0, s, n, T, M, W);
+    hipLaunchKernelGGL(k_fold_t<true>, dim3(blocks_for(fold_t_threads(n))), dim3(kBlock), 0, s, n, L.A.rp, L.A.ci,
+                       L.A.v, (const double *)nullptr, T, M);
+}
+
+inline int gemm_tiles(int n, bool sym) {
+    const int nt = (n + kGemmTile - 1) / kGemmTile;
+    return sym ? nt * (nt + 1) / 2 : nt * nt;
+}
+}  // namespace
+
+void launch_fold_w(hipStream_t s, const Level &L, const double *T, double *M, double *W, bool sym) {
+    const int n = L.A.n;
+    launch_fold_at(s, L, T, M);
+    hipLaunchKernelGGL(k_gemm<kGemmTwice>, dim3(gemm_tiles(n, sym)), dim3(kBlock), 0, s, n, sym ? 1 : 0, T, M,
+                       (const double *)nullptr, W);
+}
+
+// S_k = sum_{t < k} (I - D A)^t D = (I - (I - D A)^k) A^-1, so S_(2k) = 2 S_k - S_k A S_k
+// and S_(k+1) = D + (I - D A) S_k: k is reached from 2 by the bits of `sweeps`
+// (20: 2, 4, 5, 10, 20), where one launch per sweep took 20 products with A.
+void launch_sweep_operator(hipStream_t s, const Level &L, int sweeps, bool sym, double *S, double *W, double *M,
+                           double *Ad) {
+    const int n = L.A.n;
+    const size_t nn2 = (size_t)n * n;
+    const dim3 all(gemm_tiles(n, false)), rows(blocks_for((long long)n * 64)), t(kBlock);
+    // A S_k with A dense on the matrix cores, or row by row: 0.06 ps per
+    // multiply-add (n^3 of them) against 0.5 (n nnz)
+    const bool dense = 8LL * L.A.nnz > (long long)n * n;
+    int top = 0;
+    while ((sweeps >> (top + 1)) > 1) ++top;  // sweeps >> top is 2 or 3 (sweeps >= 2)
+    int steps = top + ((sweeps >> top) == 3 ? 1 : 0);
+    for (int b = top - 1; b >= 0; --b) steps += (sweeps >> b) & 1;
+    double *cur = (steps & 1) ? W : S, *nxt = (steps & 1) ? S : W;
+    launch_fill_i32(s, 2 * nn2, (int *)cur, 0);
+    hipLaunchKernelGGL(k_sweep2, rows, t, 0, s, n, L.A.rp, L.A.ci, L.A.v, L.dinv, cur);
+    if (dense) {
+        launch_fill_i32(s, 2 * nn2, (int *)Ad, 0);
+        hipLaunchKernelGGL(k_dense_scatter, rows, t, 0, s, n, L.A.rp, L.A.ci, L.A.v, Ad);
+    }
+    auto inc = [&]() {
+        if (dense)
+            hipLaunchKernelGGL(k_gemm<kGemmSweep>, all, t, 0, s, n, 0, Ad, cur, L.dinv, nxt);
+        else
+            launch_fold_left(s, L, cur, nxt);
+        std::swap(cur, nxt);
+    };
+    auto twice = [&]() {
+        if (dense)
+            hipLaunchKernelGGL(k_gemm<kGemmPlain>, all, t, 0, s, n, 0, Ad, cur, (const double *)nullptr, M);
+        else
+            launch_fold_at(s, L, cur, M);
+        hipLaunchKernelGGL(k_gemm<kGemmTwice>, dim3(gemm_tiles(n, sym)), t, 0, s, n, sym ? 1 : 0, cur, M,
+                           (const double *)nullptr, nxt);
+        std::swap(cur, nxt);
+    };
+    if ((sweeps >> top) == 3) inc();
+    for (int b = top - 1; b >= 0; --b) {
+        twice();
+        if ((sweeps >> b) & 1) inc();
+    }
 }
 
 void launch_fold_left(hipStream_t s, const Level &L, const double *H, double *T) {
     const int n = L.A.n;
-    hipLaunchKernelGGL(k_fold_t, dim3(blocks_for(fold_t_threads(n))), dim3(kBlock), 0, s, n, L.A.rp, L.A.ci, L.A.v,
+    hipLaunchKernelGGL(k_fold_t<false>, dim3(blocks_for(fold_t_threads(n))), dim3(kBlock), 0, s, n, L.A.rp, L.A.ci, L.A.v,
                        L.dinv, H, T);
 }
 
