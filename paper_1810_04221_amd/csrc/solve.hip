@@ -159,6 +159,37 @@ struct FGather {  // a vector entry
     __device__ V operator()(int j) const { return (V)x[j]; }
 };
 
+// The lane's entries q, q + G, ... < end of a row, added to s in that order.
+// From three entries on, four are loaded before any is used: a row of up to
+// 16 G entries (rows beyond that are long rows) would otherwise be a chain of
+// up to 15 column-then-gather round trips, and the level's longest row sets the
+// launch's time (64^3 diffusion, 5,427 rows of up to 71 entries, 8 lanes: down leg
+// 13.9 -> 9.0 us, up leg 10.1 -> 6.4).  One or two entries go one at a time:
+// there the clamped loads of a batch cost more (elasticity, 64 lanes: up leg
+// 7.2 -> 10.3 us with them).
+template <int G, typename V, typename F>
+__device__ __forceinline__ V row_rest(const int *__restrict__ ci, const V *__restrict__ a, int q, int end, V s, F f) {
+    constexpr int U = 4;
+    while (q + 2 * G < end) {
+        int j[U];
+        V av[U], fv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int qu = q + u * G < end ? q + u * G : q;
+            j[u] = ci[qu];
+            av[u] = a[qu];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) fv[u] = f(j[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (q + u * G < end) s += av[u] * fv[u];
+        q += U * G;
+    }
+    for (; q < end; q += G) s += a[q] * f(ci[q]);
+    return s;
+}
+
 // R rows per group of G lanes.  All loads of the first pass over the R rows
 // are issued before any result is used (out-of-row lanes read entry beg[k] and
 // discard it), which keeps R times more memory requests in flight per lane than
@@ -192,8 +223,7 @@ __device__ __forceinline__ void rows_dot(const int *__restrict__ rp, const int *
         s[k] = in ? t : V(0);
     }
 #pragma unroll
-    for (int k = 0; k < R; ++k)
-        for (int q = beg[k] + lane + G; q < end[k]; q += G) s[k] += a[q] * f(ci[q]);
+    for (int k = 0; k < R; ++k) s[k] = row_rest<G>(ci, a, beg[k] + lane + G, end[k], s[k], f);
 #pragma unroll
     for (int k = 0; k < R; ++k) s[k] = group_sum<G>(s[k]);
 #pragma unroll
