@@ -842,6 +842,68 @@ int star_levels(bcm_handle *h, hipStream_t s, Arena &tmp, Arena &keep, int k, in
     return BCM_OK;
 }
 
+int cycle_levels(const bcm_handle *h);
+
+// Mid rows (MidRows) of the levels whose down or up leg runs a fused CSR kernel,
+// and of a coarsest level that runs its sweeps one launch each; one read-back,
+// and none where no level holds such a row or a long one.
+int find_mid_rows(bcm_handle *h, hipStream_t s, Arena &tmp) {
+    const int kc = cycle_levels(h);
+    std::vector<int> lv;
+    for (int l = 0; l < h->nl; ++l) {
+        const Level &L = h->lv[l];
+        const bool legs = l < kc && !down_on_sell(L);
+        const bool sweeps = l == h->nl - 1 && h->ctmp[0] && L.chain.hub < 0;
+        const int tm = L.G < 32 ? kMidFactor * L.G : long_min(L.G);
+        if ((legs || sweeps) && (L.lr.n > 0 || L.A.dmax > 2 * tm)) lv.push_back(l);
+    }
+    if (lv.empty()) return BCM_OK;
+    tmp.rewind();
+    int *cnt = tmp.get_n<int>(2 * lv.size());
+    NOMEM(cnt);
+    launch_fill_i32(s, 2 * lv.size(), cnt, 0);
+    for (size_t t = 0; t < lv.size(); ++t) {
+        Level &L = h->lv[lv[t]];
+        MidRows &M = L.mid;
+        const int lmin = L.lr.n > 0 ? L.lr.lmin : long_min(L.G);
+        M.tm = L.G < 32 ? std::min(kMidFactor * L.G, lmin) : lmin;
+        if (L.lr.n > 0) {
+            ChunkInfo *ch = static_cast<ChunkInfo *>(h->persist.get(sizeof(ChunkInfo) * (size_t)L.lr.nchunks));
+            AggInfo *ag = nullptr;
+            if (L.mem && L.mstride <= 4) {
+                ag = static_cast<AggInfo *>(h->persist.get(sizeof(AggInfo) * (size_t)L.lr.n));
+                NOMEM(ag);
+            }
+            NOMEM(ch);
+            launch_long_info(s, L.lr, L.A.rp, L.agg, L.mem, L.mstride, ch, ag);
+            L.lr.chunk = ch;
+            L.lr.agg = ag;
+        }
+        if (M.tm == lmin) continue;
+        int *rows = h->persist.get_n<int>((size_t)L.A.nnz / (M.tm + 1) + 1), *aggs = nullptr;
+        if (L.mem) aggs = h->persist.get_n<int>((size_t)L.A.nnz / (M.tm + 1) + 1);
+        NOMEM(rows && (aggs || !L.mem));
+        launch_find_mid(s, L.A.n, L.nc, L.mstride, L.mem, L.A.rp, M.tm, lmin, rows, aggs, cnt + 2 * t);
+        M.rows = rows;
+        M.aggs = aggs;
+    }
+    std::vector<int> c(2 * lv.size());
+    const int rc = read_back(s, cnt, sizeof(int) * c.size(), c.data());
+    if (rc) return rc;
+    for (size_t t = 0; t < lv.size(); ++t) {
+        Level &L = h->lv[lv[t]];
+        MidRows &M = L.mid;
+        M.nrow = c[2 * t];
+        M.nagg = c[2 * t + 1];
+        if (M.nrow > L.A.n / 4) {  // most work sits in such rows: the groups keep them
+            M = MidRows();
+            if (L.lr.n > 0) M.tm = L.lr.lmin;
+        }
+        if (L.lr.n == 0 && M.nrow == 0) M = MidRows();
+    }
+    return BCM_OK;
+}
+
 int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
     hipStream_t s = h->s;
     const bcm_params &P = h->prm;
@@ -1364,6 +1426,7 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             if (rc) return rc;
         }
     }
+    if (const int rc = find_mid_rows(h, s, tmp)) return rc;
     // flexible CG state
     h->r = h->persist.get_n<double>(n);
     h->w = h->persist.get_n<double>(n);

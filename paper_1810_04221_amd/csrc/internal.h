@@ -71,6 +71,21 @@ struct SegList {
     int cap = 0;
 };
 
+// What the block of one long-row chunk needs, and what the down leg needs of the
+// aggregate of one long row, each in one load: found from the lists by searches
+// and index chains they cost a chunk block half its time (39,287 rows with 23 long
+// ones: down leg 9.9 -> 7.9 us).
+struct ChunkInfo {
+    int row, q0, q1, t;  // the long row, the chunk's entries, the row's place in the list
+    int c0, c1, pad[2];  // the row's chunks
+};
+struct AggInfo {
+    int m[4];             // member rows (-1: none)
+    int beg[4], end[4];   // a member's entries; of a long member its chunks
+    int lg[4];            // 1: a long member
+    int E, total, lead, pad;  // the aggregate, its long members' chunks, the first long member's place
+};
+
 // Long rows of one level for the solve kernels: rows longer than lmin, with
 // idx[i] = position of row i in rows (or -1) and cb their first chunks.  The
 // row kernels take such a row's dot product from the chunk partial sums that
@@ -84,6 +99,21 @@ struct LongRows {
     // Row-wise cycle legs in one launch (chunk blocks after the row blocks):
     // per long row, an arrival counter of its chunks (zero between launches).
     int *cnt = nullptr;
+    const ChunkInfo *chunk = nullptr;  // nchunks (levels on the single-launch legs)
+    const AggInfo *agg = nullptr;      // n (aggregates of up to four rows)
+};
+
+// Rows of a level whose cycle legs run the fused CSR kernels that are too long
+// for their group of G lanes but no long rows: more than tm = kMidFactor * G
+// entries.  Each takes a wave of its own (the up leg and the coarsest sweeps
+// by rows, the down leg by aggregates holding such a row), in the same launch.
+// From 32 lanes on a wave is no gain.  A level with more of them than a quarter of
+// its rows keeps them in the groups (tm = the long rows' bound).
+constexpr int kMidFactor = 2;
+struct MidRows {
+    int tm = 0;  // 0: no lists
+    int nrow = 0, nagg = 0;
+    const int *rows = nullptr, *aggs = nullptr;
 };
 
 // Error flags raised by the validation kernel.
@@ -229,6 +259,7 @@ struct StarSweep {
 struct Level {
     Csr A;
     LongRows lr;  // rows longer than long_min(G) of the rule (set at the end of setup)
+    MidRows mid;   // rows between the groups' and the long rows' (levels on the fused CSR legs)
     Sell E;  // sliced ELL copy (finest level, and levels that run the split up leg)
     double *w = nullptr;
     double *dinv = nullptr;
@@ -359,6 +390,14 @@ void launch_candidates(hipStream_t s, int G, int n, bool sorted, const int *rp, 
 void launch_find_long(hipStream_t s, int n, const int *rp, int lmin, const SegList &seg, int *idx);
 // Galerkin coarse rows with more than lmin candidate entries (members' rows)
 void launch_find_long_gal(hipStream_t s, int nc, const int *mem2, const int *rp, int lmin, const SegList &seg);
+// rows of tm < length <= lmin into rows (cnt[0] of them), and the aggregates
+// whose longest member row is one (cnt[1]; mem null: none)
+// the chunk and aggregate infos of a level's long rows (mem null or mstride > 4:
+// no aggregates)
+void launch_long_info(hipStream_t s, const LongRows &lr, const int *rp, const int *agg, const int *mem, int mstride,
+                      ChunkInfo *ch, AggInfo *ag);
+void launch_find_mid(hipStream_t s, int n, int nc, int mstride, const int *mem, const int *rp, int tm, int lmin,
+                     int *rows, int *aggs, int *cnt);
 // offsets, chunk bases and totals of seg (one workgroup)
 void launch_seg_fix(hipStream_t s, const SegList &seg);
 // per-entry checks of the long rows in seg (as the validation kernel does)

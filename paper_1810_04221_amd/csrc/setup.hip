@@ -1073,6 +1073,55 @@ k_find_long(int n, const int *__restrict__ rp, int lmin, SegList sg, int *__rest
     if (idx) idx[i] = t;
 }
 
+// One thread per long row.
+__global__ void __launch_bounds__(kBlock)
+k_long_info(LongRows lr, const int *__restrict__ rp, const int *__restrict__ agg, const int *__restrict__ mem,
+            int mstride, ChunkInfo *__restrict__ ch, AggInfo *__restrict__ ag) {
+    const int t = blockIdx.x * kBlock + threadIdx.x;
+    if (t >= lr.n) return;
+    const int row = lr.rows[t], b = rp[row], e = rp[row + 1], c0 = lr.cb[t], c1 = lr.cb[t + 1];
+    for (int c = c0; c < c1; ++c)
+        ch[c] = ChunkInfo{row, b + (c - c0) * kSegChunk, min(b + (c - c0 + 1) * kSegChunk, e), t, c0, c1, {0, 0}};
+    if (!ag) return;
+    AggInfo A;
+    A.E = agg[row];
+    A.total = 0;
+    A.lead = -1;
+    A.pad = 0;
+    for (int u = 0; u < 4; ++u) {
+        const int m = u < mstride ? mem[(size_t)A.E * mstride + u] : -1, k = m >= 0 ? lr.idx[m] : -1;
+        A.m[u] = m;
+        A.lg[u] = k >= 0 ? 1 : 0;
+        A.beg[u] = k >= 0 ? lr.cb[k] : (m >= 0 ? rp[m] : 0);
+        A.end[u] = k >= 0 ? lr.cb[k + 1] : (m >= 0 ? rp[m + 1] : 0);
+        if (k >= 0) {
+            A.total += A.end[u] - A.beg[u];
+            if (A.lead < 0) A.lead = k;
+        }
+    }
+    ag[t] = A;
+}
+
+// Rows of tm < length <= lmin (i < n), and aggregates whose longest member row
+// is one (nc of them, mem null: none).
+__global__ void __launch_bounds__(kBlock)
+k_find_mid(int n, int nc, int mstride, const int *__restrict__ mem, const int *__restrict__ rp, int tm, int lmin,
+           int *__restrict__ rows, int *__restrict__ aggs, int *__restrict__ cnt) {
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) {
+        const int d = rp[i + 1] - rp[i];
+        if (d > tm && d <= lmin) rows[atomicAdd(&cnt[0], 1)] = i;
+    }
+    if (mem && i < nc) {
+        int mx = 0;
+        for (int t = 0; t < mstride; ++t) {
+            const int r = mem[(size_t)i * mstride + t];
+            if (r >= 0) mx = max(mx, rp[r + 1] - rp[r]);
+        }
+        if (mx > tm && mx <= lmin) aggs[atomicAdd(&cnt[1], 1)] = i;
+    }
+}
+
 // Coarse rows E of a pairwise sweep whose member rows hold more than lmin
 // entries together (the candidates of E's Galerkin row).
 __global__ void __launch_bounds__(kBlock)
@@ -1788,6 +1837,17 @@ constexpr int kSegGrid = 1024;
 
 void launch_find_long(hipStream_t s, int n, const int *rp, int lmin, const SegList &seg, int *idx) {
     hipLaunchKernelGGL(k_find_long, dim3(blocks_for(n)), dim3(kBlock), 0, s, n, rp, lmin, seg, idx);
+}
+
+void launch_long_info(hipStream_t s, const LongRows &lr, const int *rp, const int *agg, const int *mem, int mstride,
+                      ChunkInfo *ch, AggInfo *ag) {
+    hipLaunchKernelGGL(k_long_info, dim3(blocks_for(lr.n)), dim3(kBlock), 0, s, lr, rp, agg, mem, mstride, ch, ag);
+}
+
+void launch_find_mid(hipStream_t s, int n, int nc, int mstride, const int *mem, const int *rp, int tm, int lmin,
+                     int *rows, int *aggs, int *cnt) {
+    hipLaunchKernelGGL(k_find_mid, dim3(blocks_for(n)), dim3(kBlock), 0, s, n, nc, mstride, mem, rp, tm, lmin, rows,
+                       aggs, cnt);
 }
 
 void launch_find_long_gal(hipStream_t s, int nc, const int *mem2, const int *rp, int lmin, const SegList &seg) {

@@ -238,64 +238,91 @@ __device__ __forceinline__ void rows_dot(const int *__restrict__ rp, const int *
 }
 
 // ----------------------------------------------------------------------------
-// Row-wise cycle legs (up leg, coarsest sweeps) of levels with long rows in
-// one launch.  The blocks after the row kernel's nrb row blocks take the long
-// rows' chunks: each sums its chunk exactly as k_long_dot, stores the partial
-// and counts its arrival on the row; the block that brings a row's last chunk
-// adds the row's partials (all loaded at once, in a fixed order) and writes
-// the row's output (fin).  The row blocks leave the long rows alone.  The partial stores and the
-// arrival count are ordered by device-scope fences (release before the count,
-// acquire after it in the finishing block): a few dozen blocks per launch do
-// this.  The counter is back at zero for the next launch.
+// Cycle legs of levels with mid or long rows, in one launch.  The first blocks
+// take the long rows' chunks, the next ones the mid rows (or the aggregates
+// holding one), a wave each, the others the remaining rows by groups.  Started
+// first, the few slow ones overlap the many short ones.
+//
+// A chunk block stores its partial sum and counts its arrival on the row (down
+// leg: on the aggregate); the block that brings the last one adds the partials
+// in a fixed order and writes the result.  A row of one chunk needs neither.
+// Partials go past the XCD's L2 (device-scope stores and loads), each waited
+// for before its arrival is counted, so no fence has to write the L2 back.  The
+// counter is back at zero for the next launch.
 // ----------------------------------------------------------------------------
-struct LongFused {
-    int nrb = 0;  // row blocks; 0: no chunk blocks (long rows summed by a pre-pass)
+struct Tiers {
+    int tm = 0x7fffffff;  // longest row of the groups
+    int nch = 0;          // chunk blocks
+    int nmid = 0;         // mid rows or aggregates
+    int off = 0;          // blocks before the group blocks (a multiple of the 8 XCDs)
+    const int *mid = nullptr;
     LongRows lr;
 };
+constexpr int kWaves = kBlock / 64;
 
-template <typename V, typename F, typename Fin>
-__device__ __forceinline__ void long_chunk(int c, const LongRows &lr, const int *__restrict__ rp,
-                                           const int *__restrict__ ci, const V *__restrict__ a, F f, Fin fin) {
+template <typename V>
+__device__ __forceinline__ void part_store(V *p, V v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // performed before the arrival is counted
+}
+
+// this thread's share of a chunk, all loads issued before any is used
+template <typename V, typename F>
+__device__ __forceinline__ double chunk_share(const ChunkInfo &C, const int *__restrict__ ci,
+                                              const V *__restrict__ a, F f) {
     constexpr int U = kSegChunk / kBlock;
-    __shared__ double lds[16];
-    __shared__ int last;
-    __shared__ V srow;
-    const int t = chunk_owner(lr.cb, lr.n, c);
-    const int row = lr.rows[t];
-    const int q0 = rp[row] + (c - lr.cb[t]) * kSegChunk, q1 = min(q0 + kSegChunk, rp[row + 1]);
     int j[U];
     V av[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int q = q0 + (int)threadIdx.x + u * kBlock;
-        const bool in = q < q1;
-        j[u] = in ? ci[q] : row;
+        const int q = C.q0 + (int)threadIdx.x + u * kBlock;
+        const bool in = q < C.q1;
+        j[u] = in ? ci[q] : C.row;
         av[u] = in ? a[q] : V(0);
     }
     V sum = V(0);
 #pragma unroll
     for (int u = 0; u < U; ++u) sum += av[u] * f(j[u]);
-    double d[1] = {(double)sum};
+    return (double)sum;
+}
+
+// True (in every thread) when this block brings the last of `total` arrivals at
+// counter cnt; its partial p = v is stored first.
+template <typename V>
+__device__ __forceinline__ bool arrive(int *cnt, int total, V *p, V v) {
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        part_store(p, v);
+        last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1 ? 1 : 0;
+    }
+    __syncthreads();
+    if (last && threadIdx.x == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last != 0;
+}
+
+// sum of the partials [c0, c1), in a fixed order (valid in thread 0)
+template <typename V>
+__device__ __forceinline__ double chunk_total(V *part, int c0, int c1, double *lds) {
+    double r[1] = {0.0};
+    for (int k = c0 + (int)threadIdx.x; k < c1; k += kBlock) r[0] += (double)load_agent(part + k);
+    block_sum<1>(r, lds);
+    return r[0];
+}
+
+// Chunk c of the long rows: fin(row, product) in thread 0 of the row's last block.
+template <typename V, typename F, typename Fin>
+__device__ __forceinline__ void long_chunk(int c, const LongRows &lr, const int *__restrict__ ci,
+                                           const V *__restrict__ a, F f, Fin fin) {
+    __shared__ double lds[16];
+    const ChunkInfo C = lr.chunk[c];
+    double d[1] = {chunk_share<V>(C, ci, a, f)};
     block_sum<1>(d, lds);
     V *part = static_cast<V *>(lr.part);
-    if (threadIdx.x == 0) {
-        part[c] = (V)d[0];
-        __threadfence();  // the partial before the arrival
-        last = atomicAdd(&lr.cnt[t], 1) == lr.cb[t + 1] - lr.cb[t] - 1 ? 1 : 0;
+    if (C.c1 - C.c0 > 1) {
+        if (!arrive(&lr.cnt[C.t], C.c1 - C.c0, part + c, (V)d[0])) return;
+        d[0] = chunk_total(part, C.c0, C.c1, lds);
     }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();  // every chunk's partial after its arrival
-    // the row's partials, all loads at once, added in a fixed order
-    double r[1] = {0.0};
-    for (int k = lr.cb[t] + (int)threadIdx.x; k < lr.cb[t + 1]; k += kBlock) r[0] += (double)part[k];
-    block_sum<1>(r, lds);
-    if (threadIdx.x == 0) {
-        srow = (V)r[0];
-        lr.cnt[t] = 0;
-    }
-    __syncthreads();
-    fin(row, srow);
+    if (threadIdx.x == 0) fin(C.row, (V)d[0]);
 }
 
 
@@ -310,24 +337,56 @@ __device__ __forceinline__ void long_chunk(int c, const LongRows &lr, const int 
 // One group of G lanes per aggregate; the member rows are processed together
 // (k_down_seq, S = 1, 2 or 4 members) or one after the other (k_down_loop).
 // ----------------------------------------------------------------------------
+// Down-leg chunk c of the long rows: the block that brings the last chunk of an
+// aggregate's long rows writes b_c.  Every block of the aggregate sums its other
+// members' rows itself, one wave each, beside its own chunk.
+template <int S, typename V, typename VB>
+__device__ __forceinline__ void down_chunk(int c, const LongRows &lr, const int *__restrict__ ci,
+                                           const V *__restrict__ a, const V *__restrict__ dinv,
+                                           const V *__restrict__ p, const VB *__restrict__ b, V *__restrict__ bc) {
+    __shared__ double lds[16];
+    __shared__ V ms[S];
+    static_assert(S <= kWaves && S <= 4, "one wave per member");
+    const FScaled<V, VB> f{dinv, b};
+    const ChunkInfo C = lr.chunk[c];
+    const AggInfo A = lr.agg[C.t];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double d[1] = {chunk_share<V>(C, ci, a, f)};
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        if (u != wv || A.m[u] < 0 || A.lg[u]) continue;
+        V s = row_rest<64>(ci, a, A.beg[u] + lane, A.end[u], V(0), f);
+        s = group_sum<64>(s);
+        if (lane == 0) ms[u] = s;
+    }
+    block_sum<1>(d, lds);  // (its barriers also publish ms)
+    V *part = static_cast<V *>(lr.part);
+    if (A.total > 1 && !arrive(&lr.cnt[A.lead], A.total, part + c, (V)d[0])) return;
+    V acc = V(0);
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        if (A.m[u] < 0) continue;
+        V s;
+        if (!A.lg[u]) s = ms[u];
+        else if (A.total > 1) s = (V)chunk_total(part, A.beg[u], A.end[u], lds);
+        else s = (V)d[0];
+        acc += p[A.m[u]] * ((V)b[A.m[u]] - s);
+    }
+    if (threadIdx.x == 0) bc[A.E] = acc;
+}
+
 // S members (template) of one aggregate, all rows in flight at once; summed
 // in ascending member order.
 template <int G, int S, typename V, typename VB>
-__global__ void __launch_bounds__(kBlock)
-k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, const int *__restrict__ ci,
-           const V *__restrict__ a, const V *__restrict__ dinv, const V *__restrict__ p,
-           const VB *__restrict__ b, V *__restrict__ bc, const double *__restrict__ done, LongView<V> lv) {
-    // small levels: the solve-ended flag is only tested before the store, so
-    // its load overlaps the row loads instead of preceding them
-    const int lane = threadIdx.x % G;
-    int E = (xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x) / G;
-    const bool live = E < nc;
-    if (!live) E = nc - 1;
+__device__ __forceinline__ V down_members(int E, const int *__restrict__ mem, const int *__restrict__ rp,
+                                          const int *__restrict__ ci, const V *__restrict__ a,
+                                          const V *__restrict__ dinv, const V *__restrict__ p,
+                                          const VB *__restrict__ b, const LongView<V> &lv, int *lgm) {
     int rows[S];
 #pragma unroll
     for (int t = 0; t < S; ++t) rows[t] = mem[(size_t)E * S + t];
     V s[S];
-    rows_dot<G, S, V>(rp, ci, a, rows, s, FScaled<V, VB>{dinv, b}, lv);
+    rows_dot<G, S, V>(rp, ci, a, rows, s, FScaled<V, VB>{dinv, b}, lv, lgm);
     V acc = V(0);
 #pragma unroll
     for (int t = 0; t < S; ++t) {
@@ -335,7 +394,43 @@ k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, cons
         const V c = p[i] * ((V)b[i] - s[t]);
         acc += rows[t] < 0 ? V(0) : c;
     }
-    if (lane == 0 && live && !(done && *done != 0.0)) bc[E] = acc;
+    return acc;
+}
+
+template <int G, int S, typename V, typename VB, bool Tier>
+__global__ void __launch_bounds__(kBlock)
+k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, const int *__restrict__ ci,
+           const V *__restrict__ a, const V *__restrict__ dinv, const V *__restrict__ p,
+           const VB *__restrict__ b, V *__restrict__ bc, const double *__restrict__ done, Tiers T) {
+    // small levels: the solve-ended flag is only tested before the store, so
+    // its load overlaps the row loads instead of preceding them
+    LongView<V> lv;
+    int blk = blockIdx.x, nb = gridDim.x;
+    if (Tier) {
+        if (blk < T.nch) {
+            if (done && *done != 0.0) return;
+            down_chunk<S>(blk, T.lr, ci, a, dinv, p, b, bc);
+            return;
+        }
+        if (blk < T.off) {
+            const int t = (blk - T.nch) * kWaves + (int)(threadIdx.x >> 6);
+            if (t >= T.nmid) return;
+            const int E = T.mid[t];
+            const V acc = down_members<64, S>(E, mem, rp, ci, a, dinv, p, b, lv, nullptr);
+            if ((threadIdx.x & 63) == 0 && !(done && *done != 0.0)) bc[E] = acc;
+            return;
+        }
+        blk -= T.off;
+        nb -= T.off;
+        lv.lmin = T.tm;
+    }
+    const int lane = threadIdx.x % G;
+    int E = (xcd_block(blk, nb) * kBlock + threadIdx.x) / G;
+    const bool live = E < nc;
+    if (!live) E = nc - 1;
+    int lgm = 0;
+    const V acc = down_members<G, S>(E, mem, rp, ci, a, dinv, p, b, lv, &lgm);
+    if (lane == 0 && live && !(Tier && lgm) && !(done && *done != 0.0)) bc[E] = acc;
 }
 
 // Any number of members (wide composed aggregates): one member row at a time.
@@ -402,44 +497,53 @@ k_restrict(int nc, const int *__restrict__ mem, const V *__restrict__ pr, V *__r
 //   x_j = dinv_j b_j + p_j xc[agg_j]          (pre-smoothed x plus P x_c)
 //   x_i <- x_i + dinv_i (b_i - sum_j a_ij x_j)
 // ----------------------------------------------------------------------------
-template <int G, int R, typename V, typename VB, typename VX, bool LF>
+template <int G, int R, typename V, typename VB, typename VX, bool Tier>
 __global__ void __launch_bounds__(kBlock)
 k_up(int n, const int *__restrict__ rp, const int *__restrict__ ci, const V *__restrict__ a,
      const V *__restrict__ dinv, const V *__restrict__ p, const int *__restrict__ agg,
-     const VB *__restrict__ b, const V *__restrict__ xc, VX *__restrict__ x, const double *__restrict__ done,
-     LongView<V> lv, LongFused lf) {
-    if (LF && (int)blockIdx.x >= lf.nrb) {  // a chunk of a long row (see long_chunk)
-        if (done && *done != 0.0) return;
-        long_chunk<V>((int)blockIdx.x - lf.nrb, lf.lr, rp, ci, a, FProlonged<V, VB>{dinv, p, agg, b, xc},
-                      [&](int i, V sl) {
-                          if (threadIdx.x != 0) return;
-                          const V bi = (V)b[i];
-                          const V di = dinv[i];
-                          const V xi = di * bi + p[i] * xc[agg[i]];
-                          x[i] = (VX)(xi + di * (bi - sl));
-                      });
-        return;
+     const VB *__restrict__ b, const V *__restrict__ xc, VX *__restrict__ x, const double *__restrict__ done, Tiers T) {
+    const FProlonged<V, VB> f{dinv, p, agg, b, xc};
+    auto put = [&](int i, V s) {
+        const V bi = (V)b[i];
+        const V di = dinv[i];
+        const V xi = di * bi + p[i] * xc[agg[i]];
+        x[i] = (VX)(xi + di * (bi - s));
+    };
+    LongView<V> lv;
+    int blk = blockIdx.x, nb = gridDim.x;
+    if (Tier) {
+        if (blk < T.nch) {
+            if (done && *done != 0.0) return;
+            long_chunk<V>(blk, T.lr, ci, a, f, put);
+            return;
+        }
+        if (blk < T.off) {
+            const int t = (blk - T.nch) * kWaves + (int)(threadIdx.x >> 6);
+            if (t >= T.nmid) return;
+            const int row[1] = {T.mid[t]};
+            V s[1];
+            rows_dot<64, 1, V>(rp, ci, a, row, s, f, lv);
+            if ((threadIdx.x & 63) == 0 && !(done && *done != 0.0)) put(row[0], s[0]);
+            return;
+        }
+        blk -= T.off;
+        nb -= T.off;
+        lv.lmin = T.tm;
     }
     // the solve-ended flag is tested before the stores only (as in k_down_seq)
     constexpr int NG = kBlock / G;
     const int lane = threadIdx.x % G;
-    const int base = xcd_block(blockIdx.x, LF ? lf.nrb : gridDim.x) * NG * R + threadIdx.x / G;
+    const int base = xcd_block(blk, nb) * NG * R + threadIdx.x / G;
     int rows[R];
 #pragma unroll
     for (int k = 0; k < R; ++k) rows[k] = base + k * NG < n ? base + k * NG : -1;
     V s[R];
     int lgm = 0;
-    rows_dot<G, R, V>(rp, ci, a, rows, s, FProlonged<V, VB>{dinv, p, agg, b, xc}, lv, &lgm);
+    rows_dot<G, R, V>(rp, ci, a, rows, s, f, lv, &lgm);
     if (lane == 0 && !(done && *done != 0.0)) {
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            const int i = rows[k];
-            if (i < 0 || (LF && ((lgm >> k) & 1))) continue;
-            const V bi = (V)b[i];
-            const V di = dinv[i];
-            const V xi = di * bi + p[i] * xc[agg[i]];
-            x[i] = (VX)(xi + di * (bi - s[k]));
-        }
+        for (int k = 0; k < R; ++k)
+            if (rows[k] >= 0 && !(Tier && ((lgm >> k) & 1))) put(rows[k], s[k]);
     }
 }
 
@@ -1043,25 +1147,40 @@ k_tail(int kt, int nl, const TailLevel *__restrict__ tl, const double *__restric
 // rows per group, as in the cycle kernels.  The last sweep of a solve writes
 // the caller's x (type VX) instead of xn.  The solve-ended flag is tested
 // before the stores only (as in k_down_seq).
-template <int G, int R, typename VB, typename VX, bool LF>
+template <int G, int R, typename VB, typename VX, bool Tier>
 __global__ void __launch_bounds__(kBlock)
 k_jacobi_sweep(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
                const double *__restrict__ dinv, const VB *__restrict__ b, const double *__restrict__ xo,
-               double *__restrict__ xn, VX *__restrict__ xout, int first, const double *__restrict__ done,
-               LongView<double> lv, LongFused lf) {
-    if (LF && (int)blockIdx.x >= lf.nrb) {  // a chunk of a long row (see long_chunk); never the first sweep
-        if (done && *done != 0.0) return;
-        long_chunk<double>((int)blockIdx.x - lf.nrb, lf.lr, rp, ci, a, FGather<double, double>{xo},
-                           [&](int i, double sl) {
-                               if (threadIdx.x != 0) return;
-                               const double v = xo[i] + dinv[i] * ((double)b[i] - sl);
-                               if (xout) xout[i] = (VX)v;
-                               else xn[i] = v;
-                           });
-        return;
+               double *__restrict__ xn, VX *__restrict__ xout, int first, const double *__restrict__ done, Tiers T) {
+    const FGather<double, double> f{xo};
+    auto put = [&](int i, double s) {
+        const double v = (first ? 0.0 : xo[i]) + dinv[i] * ((double)b[i] - s);
+        if (xout) xout[i] = (VX)v;
+        else xn[i] = v;
+    };
+    LongView<double> lv;
+    int blk = blockIdx.x, nb = gridDim.x;
+    if (Tier) {  // (never the first sweep)
+        if (blk < T.nch) {
+            if (done && *done != 0.0) return;
+            long_chunk<double>(blk, T.lr, ci, a, f, put);
+            return;
+        }
+        if (blk < T.off) {
+            const int t = (blk - T.nch) * kWaves + (int)(threadIdx.x >> 6);
+            if (t >= T.nmid) return;
+            const int row[1] = {T.mid[t]};
+            double s[1];
+            rows_dot<64, 1, double>(rp, ci, a, row, s, f, lv);
+            if ((threadIdx.x & 63) == 0 && !(done && *done != 0.0)) put(row[0], s[0]);
+            return;
+        }
+        blk -= T.off;
+        nb -= T.off;
+        lv.lmin = T.tm;
     }
     const int lane = threadIdx.x % G;
-    const int g = (xcd_block(blockIdx.x, LF ? lf.nrb : gridDim.x) * kBlock + threadIdx.x) / G;
+    const int g = (xcd_block(blk, nb) * kBlock + threadIdx.x) / G;
     int rows[R];
 #pragma unroll
     for (int k = 0; k < R; ++k) rows[k] = g * R + k < n ? g * R + k : -1;
@@ -1071,18 +1190,12 @@ k_jacobi_sweep(int n, const int *__restrict__ rp, const int *__restrict__ ci, co
 #pragma unroll
         for (int k = 0; k < R; ++k) s[k] = 0.0;
     } else {
-        rows_dot<G, R, double>(rp, ci, a, rows, s, FGather<double, double>{xo}, lv, &lgm);
+        rows_dot<G, R, double>(rp, ci, a, rows, s, f, lv, &lgm);
     }
     const bool live = !(done && *done != 0.0);
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const int i = rows[k];
-        if (lane == k % G && i >= 0 && live && !(LF && ((lgm >> k) & 1))) {
-            const double v = (first ? 0.0 : xo[i]) + dinv[i] * ((double)b[i] - s[k]);
-            if (xout) xout[i] = (VX)v;
-            else xn[i] = v;
-        }
-    }
+    for (int k = 0; k < R; ++k)
+        if (lane == k % G && rows[k] >= 0 && live && !(Tier && ((lgm >> k) & 1))) put(rows[k], s[k]);
 }
 
 // ----------------------------------------------------------------------------
@@ -1264,37 +1377,45 @@ void long_pre(hipStream_t s, const Level &L, const V *a, F f, const double *done
                            static_cast<V *>(L.lr.part), done);
 }
 
-// The long rows of a level in the row kernel's own launch (LongFused), when
-// the level has their arrival counters.
-LongFused long_fused(const Level &L, int nrb) {
-    LongFused lf;
-    if (L.lr.n > 0 && L.lr.cnt) {
-        lf.nrb = nrb;
-        lf.lr = L.lr;
-    }
-    return lf;
+// The level's mid rows (or aggregates) and long rows for a leg in one launch;
+// off = 0: it has neither.
+Tiers tiers_of(const Level &L, bool aggregates) {
+    Tiers T;
+    if (L.mid.tm <= 0) return T;
+    T.tm = L.mid.tm;
+    T.nch = L.lr.n > 0 ? L.lr.nchunks : 0;
+    T.nmid = aggregates ? L.mid.nagg : L.mid.nrow;
+    T.mid = aggregates ? L.mid.aggs : L.mid.rows;
+    T.off = (T.nch + (T.nmid + kWaves - 1) / kWaves + 7) / 8 * 8;
+    T.lr = L.lr;
+    return T;
 }
 
 template <int G, typename V, typename VB>
 void down_dispatch(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p, const VB *b, V *bc,
                    const double *done) {
     const int S = L.mstride;
-    const dim3 grid(blocks_for((long long)L.nc * G));
-    const LongView<V> lv = long_view<V>(L.lr);
-    // (the down leg keeps the pre-pass: its finishing block would have to
-    // build a whole aggregate, which measured slower than the separate launch)
-    long_pre(s, L, a, FScaled<V, VB>{dinv, b}, done);
+    dim3 grid(blocks_for((long long)L.nc * G));
     auto seq = [&](auto sc) {
         constexpr int SS = decltype(sc)::value;
-        launch_k((k_down_seq<G, SS, V, VB>), grid, dim3(kBlock), s, L.nc, L.mem, L.A.rp, L.A.ci, a, dinv, p, b, bc,
-                 done, lv);
+        const Tiers T = tiers_of(L, true);
+        grid.x += T.off;
+        if (T.off > 0)
+            launch_k((k_down_seq<G, SS, V, VB, true>), grid, dim3(kBlock), s, L.nc, L.mem, L.A.rp, L.A.ci, a, dinv, p,
+                     b, bc, done, T);
+        else
+            launch_k((k_down_seq<G, SS, V, VB, false>), grid, dim3(kBlock), s, L.nc, L.mem, L.A.rp, L.A.ci, a, dinv, p,
+                     b, bc, done, T);
     };
     if (S == 1) seq(std::integral_constant<int, 1>{});
     else if (S == 2) seq(std::integral_constant<int, 2>{});
     else if (S == 4) seq(std::integral_constant<int, 4>{});
-    else
+    else {
+        const LongView<V> lv = long_view<V>(L.lr);
+        long_pre(s, L, a, FScaled<V, VB>{dinv, b}, done);
         launch_k((k_down_loop<G, V, VB>), grid, dim3(kBlock), s, L.nc, L.mstride, L.mem, L.A.rp,
                            L.A.ci, a, dinv, p, b, bc, done, lv);
+    }
 }
 
 // part: 0 = the whole leg, 1 = its first kernel, 2 = its second kernel (a
@@ -1389,20 +1510,14 @@ void up_t(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p, 
         constexpr int g = decltype(gc)::value;
         constexpr int R = 2;
         dim3 grid(blocks_for(((long long)L.A.n * g + R - 1) / R));
-        LongView<V> lv = long_view<V>(L.lr);
-        const LongFused lf = long_fused(L, (int)grid.x);
-        if (lf.nrb > 0) {
-            grid.x += L.lr.nchunks;
-            lv.part = nullptr;
-        } else {
-            long_pre(s, L, a, FProlonged<V, VB>{dinv, p, L.agg, b, xc}, done);
-        }
-        if (lf.nrb > 0)
+        const Tiers T = tiers_of(L, false);
+        grid.x += T.off;
+        if (T.off > 0)
             launch_k((k_up<g, R, V, VB, VX, true>), grid, dim3(kBlock), s, L.A.n, L.A.rp, L.A.ci, a, dinv, p, L.agg, b,
-                     xc, x, done, lv, lf);
+                     xc, x, done, T);
         else
             launch_k((k_up<g, R, V, VB, VX, false>), grid, dim3(kBlock), s, L.A.n, L.A.rp, L.A.ci, a, dinv, p, L.agg,
-                     b, xc, x, done, lv, lf);
+                     b, xc, x, done, T);
     });
 }
 
@@ -1429,22 +1544,16 @@ void coarse_t(hipStream_t s, const Level &L, int sweeps, const VB *b, VX *x, dou
         constexpr int R = 2;
         for (int t = 0; t < sweeps; ++t) {
             dim3 grid(blocks_for(((long long)n + R - 1) / R * g));
-            LongView<double> lv = long_view<double>(L.lr);
             // (the first sweep, from zero, has no products)
-            const LongFused lf = t > 0 ? long_fused(L, (int)grid.x) : LongFused();
-            if (lf.nrb > 0) {
-                grid.x += L.lr.nchunks;
-                lv.part = nullptr;
-            } else if (t > 0) {
-                long_pre(s, L, (const double *)L.A.v, FGather<double, double>{xo}, done);
-            }
-            if (lf.nrb > 0)
+            const Tiers T = t > 0 ? tiers_of(L, false) : Tiers();
+            grid.x += T.off;
+            VX *xl = t == sweeps - 1 ? x : (VX *)nullptr;
+            if (T.off > 0)
                 hipLaunchKernelGGL((k_jacobi_sweep<g, R, VB, VX, true>), grid, dim3(kBlock), 0, s, n, L.A.rp, L.A.ci,
-                                   L.A.v, L.dinv, b, xo, xn, t == sweeps - 1 ? x : (VX *)nullptr, 0, done, lv, lf);
+                                   L.A.v, L.dinv, b, xo, xn, xl, 0, done, T);
             else
                 hipLaunchKernelGGL((k_jacobi_sweep<g, R, VB, VX, false>), grid, dim3(kBlock), 0, s, n, L.A.rp, L.A.ci,
-                                   L.A.v, L.dinv, b, xo, xn, t == sweeps - 1 ? x : (VX *)nullptr, t == 0 ? 1 : 0, done,
-                                   lv, lf);
+                                   L.A.v, L.dinv, b, xo, xn, xl, t == 0 ? 1 : 0, done, T);
             double *tmp = xo; xo = xn; xn = tmp;
         }
     });

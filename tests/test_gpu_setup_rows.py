@@ -38,11 +38,11 @@ def _spokes(n, degrees, base, seed):
     return A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data.copy()
 
 
-# mean row length -> lanes per row G; degrees around 4 G, the wave's slots (256)
-# and 16 G, the bound of the long rows
-ROWS = [(4, 0, (11, 12, 13, 14, 30, 59, 60, 61, 62, 63, 64, 200)),
-        (8, 1, (25, 26, 27, 28, 29, 60, 120, 121, 122, 123, 124, 125, 300)),
-        (16, 5, (50, 51, 52, 53, 54, 120, 200, 240, 241, 242, 243, 244, 245, 500)),
+# mean row length -> lanes per row G; degrees around 2 G (the cycle legs' mid
+# rows), 4 G, the wave's slots (256) and 16 G, the bound of the long rows
+ROWS = [(4, 0, (5, 6, 7, 11, 12, 13, 14, 30, 59, 60, 61, 62, 63, 64, 200)),
+        (8, 1, (10, 11, 12, 13, 25, 26, 27, 28, 29, 60, 120, 121, 122, 123, 124, 125, 300)),
+        (16, 5, (17, 18, 19, 20, 21, 50, 51, 52, 53, 54, 120, 200, 240, 241, 242, 243, 244, 245, 500)),
         (32, 10, (100, 105, 106, 107, 108, 200, 230, 234, 235, 236, 240, 400, 489, 490, 491, 492, 900))]
 
 
