@@ -1505,9 +1505,14 @@ bool y_by_restrict(const bcm_handle *h, int k) {
 }
 
 double bytes_down(const bcm_handle *h, int k) {
+    if (fp32 && h->nl > 1) {  // (a single level's cycle is the coarsest solve, in float64)
+        h->r32 = h->persist.get_n<float>(n);
+        h->w32 = h->persist.get_n<float>(n);
+        NOMEM(h->r32 && h->w32);
+    }
     const Level &L = h->lv[k];
     const bool f32 = h->prm.precision == BCM_FP32_CYCLE;
-    const double sv = f32 ? 4 : 8, sb = (k == 0 || !f32) ? 8 : 4;
+    const double sv = f32 ? 4 : 8, sb = sv;
     const double n = L.A.n, z = L.A.nnz, nc = L.nc;
     const bool sell = down_on_sell(L);
     const double base = 4 * (n + 1) + (index_bytes(L, sell) + value_bytes(L, sell, f32)) * z + sb * n + 2 * sv * n +
@@ -1525,7 +1530,7 @@ double bytes_down(const bcm_handle *h, int k) {
 double bytes_up(const bcm_handle *h, int k) {
     const Level &L = h->lv[k];
     const bool f32 = h->prm.precision == BCM_FP32_CYCLE;
-    const double sv = f32 ? 4 : 8, sb = (k == 0 || !f32) ? 8 : 4;
+    const double sv = f32 ? 4 : 8, sb = sv;
     const double n = L.A.n, z = L.A.nnz, nc = L.nc;
     if (L.xp)
         return (sb * n + 2 * sv * n + 4 * n + sv * nc + sv * n) +
@@ -1538,7 +1543,7 @@ double bytes_up(const bcm_handle *h, int k) {
 double bytes_down_main(const bcm_handle *h, int k) {
     const Level &L = h->lv[k];
     const bool f32 = h->prm.precision == BCM_FP32_CYCLE;
-    const double sv = f32 ? 4 : 8, sb = (k == 0 || !f32) ? 8 : 4, n = L.A.n, z = L.A.nnz;
+    const double sv = f32 ? 4 : 8, sb = sv, n = L.A.n, z = L.A.nnz;
     if (!down_on_sell(L)) return bytes_down(h, k);
     // b read; p read and p r written; dinv read unless the values are those of A D
     return 4 * (n + 1) + (index_bytes(L, true) + value_bytes(L, true, f32)) * z + sb * n + (L.E.svd ? 2 : 3) * sv * n;
@@ -1546,7 +1551,7 @@ double bytes_down_main(const bcm_handle *h, int k) {
 double bytes_up_main(const bcm_handle *h, int k) {
     const Level &L = h->lv[k];
     const bool f32 = h->prm.precision == BCM_FP32_CYCLE;
-    const double sv = f32 ? 4 : 8, sb = (k == 0 || !f32) ? 8 : 4, n = L.A.n, z = L.A.nnz;
+    const double sv = f32 ? 4 : 8, sb = sv, n = L.A.n, z = L.A.nnz;
     if (!L.xp) return bytes_up(h, k);
     return 4 * (n + 1) + (index_bytes(L, L.E.sp != nullptr) + value_bytes(L, L.E.sp != nullptr, f32)) * z +
            2 * sv * n + 2 * sb * n;
@@ -1594,9 +1599,11 @@ double bytes_spmv_dots(const bcm_handle *h) {
     const Level &L = h->lv[0];
     const double n = L.A.n, z = L.A.nnz;
     // algorithmic: every stored entry once (ELL padding not counted)
-    return 4 * (n + 1) + (index_bytes(L, L.E.sp != nullptr) + value_bytes(L, L.E.sp != nullptr, false)) * z + 32 * n;
+    return 4 * (n + 1) + (index_bytes(L, L.E.sp != nullptr) + value_bytes(L, L.E.sp != nullptr, false)) * z +
+           (h->w32 ? 28 : 32) * n;
 }
-// ten float64 vector streams; with y0, dinv read and y0 written in the cycle's type
+// ten float64 vector streams (FP32 cycle: w of half the size, and r32 written);
+// with y0, dinv read and y0 written in the cycle's type
 double bytes_update(const bcm_handle *h) {
     const double sv = h->prm.precision == BCM_FP32_CYCLE ? 4 : 8;
     return (80.0 + (h->y0 ? 2 * sv : 0.0)) * h->lv[0].A.n;
@@ -1780,7 +1787,8 @@ void cycle_level(bcm_handle *h, Prof &pf, int k, const double *done, int iter) {
 // y0: dinv o r of the finest level already formed (the update's h->y0), or null.
 // st: the stop test of the flexible-CG update before this cycle, taken by the
 // finest level's first kernel (only where cycle_takes_stop(h)); default none.
-void vcycle(bcm_handle *h, Prof &pf, const double *rin, double *wout, const double *done, int iter,
+// io64: rin and wout are float64 (else both in the cycle's float32).
+void vcycle(bcm_handle *h, Prof &pf, const void *rin, void *wout, int io64, const double *done, int iter,
             const void *y0 = nullptr, StopTest st = {}) {
     hipStream_t s = h->s;
     const int fp32 = h->prm.precision == BCM_FP32_CYCLE;
@@ -1794,16 +1802,16 @@ void vcycle(bcm_handle *h, Prof &pf, const double *rin, double *wout, const doub
         return;
     }
     if (h->prm.cycle != BCM_VCYCLE) {
-        // finest level here (f64 in/out), coarse levels recursively
+        // finest level here, coarse levels recursively
         Level &L = h->lv[0], &N = h->lv[1];
         int e = pf.begin(0);
-        launch_down(s, L, fp32, rin, N.b, 1, done, 1, y0, nullptr, st);
+        launch_down(s, L, fp32, rin, N.b, io64, done, 1, y0, nullptr, st);
         pf.end(0, e, class_bytes(h, 0), iter);
-        launch_down(s, L, fp32, rin, N.b, 1, done, 2);
+        launch_down(s, L, fp32, rin, N.b, io64, done, 2);
         coarse_solve(h, pf, 0, done, iter);
-        launch_up(s, L, fp32, rin, N.x, wout, 1, 1, done, 1);
+        launch_up(s, L, fp32, rin, N.x, wout, io64, io64, done, 1);
         e = pf.begin(1);
-        launch_up(s, L, fp32, rin, N.x, wout, 1, 1, done, 2);
+        launch_up(s, L, fp32, rin, N.x, wout, io64, io64, done, 2);
         pf.end(1, e, class_bytes(h, 1), iter);
         return;
     }
@@ -1811,8 +1819,8 @@ void vcycle(bcm_handle *h, Prof &pf, const double *rin, double *wout, const doub
     const int kt = cycle_levels(h);
     for (int k = 0; k < kt; ++k) {
         Level &L = h->lv[k];
-        const void *bk = k == 0 ? (const void *)rin : L.b;
-        const int io = (k == 0 || !fp32) ? 1 : 0;
+        const void *bk = k == 0 ? rin : L.b;
+        const int io = k == 0 ? io64 : !fp32;
         // the restriction forms the coarser level's dinv o b when that level gathers it
         const Level *next = y_by_restrict(h, k + 1) ? &h->lv[k + 1] : nullptr;
         if (k == 0) {  // the finest level's main kernel alone is class 0
@@ -1841,9 +1849,9 @@ void vcycle(bcm_handle *h, Prof &pf, const double *rin, double *wout, const doub
     }
     for (int k = kt - 1; k >= 0; --k) {
         Level &L = h->lv[k];
-        const int f64io = (k == 0 || !fp32) ? 1 : 0;
-        const void *bk = k == 0 ? (const void *)rin : L.b;
-        void *xk = k == 0 ? (void *)wout : L.x;
+        const int f64io = k == 0 ? io64 : !fp32;
+        const void *bk = k == 0 ? rin : L.b;
+        void *xk = k == 0 ? wout : L.x;
         if (k == 0) {  // the finest level's main kernel alone is class 1
             launch_up(s, L, fp32, bk, h->lv[1].x, xk, f64io, f64io, done, 1);
             int e = pf.begin(1);
@@ -1901,16 +1909,16 @@ int capture_iteration(bcm_handle *h, int prof_cls) {
     hipStream_t keep = h->s;
     h->s = h->cap;
     sc.begin();
-    vcycle(h, gp, h->r, h->w, h->scal + 10, 0, h->y0, stop_test_of(h));
+    vcycle(h, gp, cycle_in(h), cycle_out(h), !h->w32, h->scal + 10, 0, h->y0, stop_test_of(h));
     int e = gp.begin(2);
     const int nbs = spmv_dots_grid(L0, nb);
-    launch_spmv_dots(h->cap, L0, nbs, 0, h->w, h->r, h->q, h->v, h->spart, h->scal);
+    launch_spmv_dots(h->cap, L0, nbs, cycle_out(h), h->w32 != nullptr, h->r, h->q, h->v, h->spart, h->scal);
     gp.end(2, e, 0.0, 0);
     const bool fuse = update_takes_dots(nbs);
     if (!fuse) launch_finalize(h->cap, 1, nbs, 0, h->spart, h->scal);
     e = gp.begin(3);
-    launch_update(h->cap, n, nb, 0, h->w, h->v, h->d, h->u, h->q, h->r, h->partials, h->scal, y0_dinv(h), h->y0,
-                  h->prm.precision == BCM_FP32_CYCLE, fuse ? h->spart : nullptr, nbs);
+    launch_update(h->cap, n, nb, 0, cycle_out(h), h->w32 != nullptr, h->v, h->d, h->u, h->q, h->r, h->r32, h->partials,
+                  h->scal, y0_dinv(h), h->y0, h->prm.precision == BCM_FP32_CYCLE, fuse ? h->spart : nullptr, nbs);
     gp.end(3, e, 0.0, 0);
     if (!cycle_takes_stop(h)) launch_finalize(h->cap, 2, nb, 0, h->partials, h->scal);
     sc.end();
@@ -1940,6 +1948,10 @@ int fcg_run(bcm_handle *h, const double *b, double *x_user, double tol) {
     const int n = L0.A.n, nb = h->red_blocks, nbs = spmv_dots_grid(L0, nb);
     Prof pf{h, h->prm.profile};
     // graph mode: a profile mask of one class bracketed once per iteration
+// The cycle's input and output in the flexible-CG loop.
+const void *cycle_in(const bcm_handle *h) { return h->r32 ? (const void *)h->r32 : (const void *)h->r; }
+void *cycle_out(const bcm_handle *h) { return h->w32 ? (void *)h->w32 : (void *)h->w; }
+
     // (down0, up0, spmv_dots, update, coarse) is timed by events recorded
     // around that class's own graph; other masks launch every iteration eagerly
     int gcls = -1;
@@ -1957,7 +1969,7 @@ int fcg_run(bcm_handle *h, const double *b, double *x_user, double tol) {
     h->ev_bytes.clear();
     h->ev_iter.clear();
     double hs[16];
-    launch_resid(s, L0, nb, b, x, h->r, h->partials, h->scal);
+    launch_resid(s, L0, nb, b, x, h->r, h->r32, h->partials, h->scal);
     launch_finalize(s, 0, nb, 0, h->partials, h->scal);
     int rc = read_back(s, h->scal, 16 * sizeof(double), hs);
     if (rc) return rc;
@@ -2004,15 +2016,17 @@ int fcg_run(bcm_handle *h, const double *b, double *x_user, double tol) {
                     continue;
                 }
                 // the first iteration's r comes from the residual kernel: no y0 yet
-                vcycle(h, pf, h->r, h->w, done, launched, first ? nullptr : h->y0, stop_test_of(h));
+                vcycle(h, pf, cycle_in(h), cycle_out(h), !h->w32, done, launched, first ? nullptr : h->y0,
+                       stop_test_of(h));
                 int e = pf.begin(2);
-                launch_spmv_dots(s, L0, nbs, first, h->w, h->r, h->q, h->v, h->spart, h->scal);
+                launch_spmv_dots(s, L0, nbs, cycle_out(h), h->w32 != nullptr, h->r, h->q, h->v, h->spart, h->scal);
                 pf.end(2, e, bytes_spmv_dots(h), launched);
                 const bool fuse = update_takes_dots(nbs);
                 if (!fuse) launch_finalize(s, 1, nbs, first, h->spart, h->scal);
                 e = pf.begin(3);
-                launch_update(s, n, nb, first, h->w, h->v, h->d, x, h->q, h->r, h->partials, h->scal, y0_dinv(h),
-                              h->y0, h->prm.precision == BCM_FP32_CYCLE, fuse ? h->spart : nullptr, nbs);
+                launch_update(s, n, nb, first, cycle_out(h), h->w32 != nullptr, h->v, h->d, x, h->q, h->r, h->r32,
+                              h->partials, h->scal, y0_dinv(h), h->y0, h->prm.precision == BCM_FP32_CYCLE,
+                              fuse ? h->spart : nullptr, nbs);
                 pf.end(3, e, bytes_update(h), launched);
                 if (!cycle_takes_stop(h)) launch_finalize(s, 2, nb, 0, h->partials, h->scal);
                 first = 0;
@@ -2040,7 +2054,7 @@ int fcg_run(bcm_handle *h, const double *b, double *x_user, double tol) {
             it_prev = it;
         }
         // true residual b - A x
-        launch_resid(s, L0, nb, b, x, h->r, h->partials, h->scal);
+        launch_resid(s, L0, nb, b, x, h->r, h->r32, h->partials, h->scal);
         launch_finalize(s, 0, nb, 0, h->partials, h->scal);
         rc = read_back(s, h->scal, 16 * sizeof(double), hs);
         if (rc) return rc;
@@ -2198,7 +2212,7 @@ int bcm_precond(bcm_handle *h, const double *r, double *z) {
     g_err.clear();
     if (!h || !r || !z) { set_error("NULL handle or vector"); return BCM_EINVAL; }
     Prof pf{h, 0};
-    vcycle(h, pf, r, z, nullptr, 0);
+    vcycle(h, pf, r, z, 1, nullptr, 0);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(h->s));
     return BCM_OK;

@@ -336,6 +336,9 @@ struct bcm_handle {
     int kt = -1;                           // first level handled by the tail kernel (-1: none)
     int kf = 0;                            // first level of the folded dense operator (0: none):
                                            // the V- or W-cycle from level kf down, as one n_kf x n_kf map
+    // FP32 cycle of two or more levels: the cycle's input r rounded to float32 (written
+    // beside r) and its result, which is then not kept in w; else null
+    float *r32 = nullptr, *w32 = nullptr;
     double *fold = nullptr;                // that operator, n_kf x n_kf row-major, float64
     int kc = 0;                            // first level of a star chain applied as lv[kc].chain (0: none)
     int long_star = 0;                     // long rows of the star levels that keep no long-row list
@@ -551,7 +554,8 @@ void launch_fold_left(hipStream_t s, const Level &L, const double *H, double *T)
 // x = T b with a dense n x n row-major float64 operator (float64 accumulation)
 void launch_dense(hipStream_t s, int n, const double *T, const void *b, void *x, int b_f64, int x_f64,
                   const double *done);
-void launch_resid(hipStream_t s, const Level &L, int nb, const double *b, const double *u, double *r,
+// r32 (or null): r also rounded to float32
+void launch_resid(hipStream_t s, const Level &L, int nb, const double *b, const double *u, double *r, float *r32,
                   double *partials, double *scal);
 // workgroups of the flexible-CG product on level L (nb: the reduction grid of
 // the vector kernels): one per slice on the levels whose rows it splits, else nb.
@@ -559,14 +563,15 @@ void launch_resid(hipStream_t s, const Level &L, int nb, const double *b, const 
 int spmv_dots_grid(const Level &L, int nb);
 // level L's sliced-ELL legs take the slot-split kernels (wide slices, at most 2^19 rows)
 bool slot_split_level(const Level &L);
-void launch_spmv_dots(hipStream_t s, const Level &L, int nb, int first, const double *w, const double *r,
+// w_f32: w is stored as float32 (the FP32 cycle's result)
+void launch_spmv_dots(hipStream_t s, const Level &L, int nb, const void *w, int w_f32, const double *r,
                       const double *q, double *v, double *partials, double *scal);
 // with y: also y = dinv o r (float when y_f32, else double; dinv of that type).
 // with dots: the update adds the product's ndots partials and forms the step
 // scalars itself (no mode-1 finalize before it); allowed when
 // update_takes_dots(ndots).
-void launch_update(hipStream_t s, int n, int nb, int first, const double *w, const double *v,
-                   double *d, double *u, double *q, double *r, double *partials, double *scal,
+void launch_update(hipStream_t s, int n, int nb, int first, const void *w, int w_f32, const double *v, double *d,
+                   double *u, double *q, double *r, float *r32, double *partials, double *scal,
                    const void *dinv = nullptr, void *y = nullptr, int y_f32 = 0, const double *dots = nullptr,
                    int ndots = 0);
 bool update_takes_dots(int nbs);

@@ -145,7 +145,7 @@ k_resid_sell(int n, const int *__restrict__ sp, const int *__restrict__ uni,
                 const int *__restrict__ su, const I *__restrict__ sc,
              const S *__restrict__ sv,
              const double *__restrict__ b, const double *__restrict__ u, double *__restrict__ r,
-             double *__restrict__ partials) {
+             float *__restrict__ r32, double *__restrict__ partials) {
     const int blk = xcd_block(blockIdx.x, gridDim.x);
     double acc[2] = {0.0, 0.0};
     for (int i = blk * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
@@ -153,6 +153,7 @@ k_resid_sell(int n, const int *__restrict__ sp, const int *__restrict__ uni,
         const double s = sell_row<double, S, I, kB>(n, sp, uni, su, sc, sv, i, [&](int j) { return u[j]; });
         const double ri = bi - s;
         r[i] = ri;
+        if (r32) r32[i] = (float)ri;
         acc[0] += ri * ri;
         acc[1] += bi * bi;
     }
@@ -180,21 +181,22 @@ __device__ __forceinline__ XcdRows xcd_rows(int n, int blk, int nb) {
 }
 
 // NT: the matrix values streamed non-temporally (Sell::stream: the gathered
-// w then stays in each XCD's L2).
-template <typename I, typename S, int kB, bool NT>
+// w then stays in each XCD's L2).  W: the type w is stored in, float when the
+// cycle is (every value of w is then a float32, widened exactly on load).
+template <typename I, typename S, typename W, int kB, bool NT>
 __global__ void __launch_bounds__(kBlock)
 k_spmv_dots_sell(int n, const int *__restrict__ sp, const int *__restrict__ uni,
                 const int *__restrict__ su, const I *__restrict__ sc,
                  const S *__restrict__ sv,
-                 const double *__restrict__ w, const double *__restrict__ r, const double *__restrict__ q,
+                 const W *__restrict__ w, const double *__restrict__ r, const double *__restrict__ q,
                  double *__restrict__ v, double *__restrict__ partials, const double *__restrict__ done) {
     if (done && *done != 0.0) return;
     const XcdRows xr = xcd_rows(n, xcd_block(blockIdx.x, gridDim.x), gridDim.x);
     double acc[3] = {0.0, 0.0, 0.0};
     for (int i = xr.first + threadIdx.x; i < xr.end; i += xr.stride) {
         // the row's own entries are loaded first, to overlap the product's loads
-        const double wi = w[i], ri = r[i], qi = q[i];
-        auto g = [&](int j) { return w[j]; };
+        const double wi = (double)w[i], ri = r[i], qi = q[i];
+        auto g = [&](int j) { return (double)w[j]; };
         const double s = sell_row<double, S, I, kB, decltype(g), NT>(n, sp, uni, su, sc, sv, i, g);
         v[i] = s;
         acc[0] += wi * ri;
@@ -212,6 +214,10 @@ k_spmv_dots_sell(int n, const int *__restrict__ sp, const int *__restrict__ uni,
 // finest level's pre-smoothed iterate (the first Jacobi step of Algorithm 1
 // from a zero guess) for the next preconditioner application, whose down-leg
 // residual then gathers one array instead of dinv and r.
+// FP32 cycle (WT = float): w is stored as float32 (the cycle's result, exactly),
+// and r is also written rounded to float32 (r32), the cycle's right-hand side as
+// its kernels round it: 12 bytes a row less in the product and the smoother and
+// 4 more here, against 8 less in the residual, prolongation and smoother.
 // Vectors of at least four entries per thread of the grid go in pairs of
 // entries with 16-byte accesses (the vectors are 256-byte aligned; with n odd,
 // thread 0 of the grid also takes entry n - 1); shorter ones one entry at a
@@ -226,20 +232,21 @@ __device__ __forceinline__ void update_pair(double wi, double vi, double &di, do
     acc += ri * ri;
 }
 
-template <bool First, typename YV>
-__device__ __forceinline__ void update_range1(int n, const double *__restrict__ w, const double *__restrict__ v,
+template <bool First, typename YV, typename WT>
+__device__ __forceinline__ void update_range1(int n, const WT *__restrict__ w, const double *__restrict__ v,
                                               double *__restrict__ d, double *__restrict__ u,
                                               double *__restrict__ q, double *__restrict__ r,
-                                              const YV *__restrict__ dinv, YV *__restrict__ y, double g, double an,
-                                              double &acc) {
+                                              float *__restrict__ r32, const YV *__restrict__ dinv,
+                                              YV *__restrict__ y, double g, double an, double &acc) {
     const int blk = xcd_block(blockIdx.x, gridDim.x);
     for (int i = blk * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         double di = First ? 0.0 : d[i], qi = First ? 0.0 : q[i], ui = u[i], ri = r[i];
-        update_pair<First>(w[i], v[i], di, qi, ui, ri, g, an, acc);
+        update_pair<First>((double)w[i], v[i], di, qi, ui, ri, g, an, acc);
         d[i] = di;
         q[i] = qi;
         u[i] = ui;
         r[i] = ri;
+        if (r32) r32[i] = (float)ri;
         if (y) y[i] = dinv[i] * (YV)ri;
     }
 }
@@ -248,30 +255,41 @@ template <typename YV> struct Pair2;
 template <> struct Pair2<float> { using T = float2; };
 template <> struct Pair2<double> { using T = double2; };
 
-template <bool First, typename YV>
-__device__ __forceinline__ void update_range(int n, const double *__restrict__ w, const double *__restrict__ v,
+template <bool First, typename YV, typename WT>
+__device__ __forceinline__ void update_range(int n, const WT *__restrict__ w, const double *__restrict__ v,
                                              double *__restrict__ d, double *__restrict__ u, double *__restrict__ q,
-                                             double *__restrict__ r, const YV *__restrict__ dinv,
-                                             YV *__restrict__ y, double g, double an, double &acc) {
+                                             double *__restrict__ r, float *__restrict__ r32,
+                                             const YV *__restrict__ dinv, YV *__restrict__ y, double g, double an,
+                                             double &acc) {
     using Y2 = typename Pair2<YV>::T;
+    using W2 = typename Pair2<WT>::T;
     const int blk = xcd_block(blockIdx.x, gridDim.x);
     const int n2 = n / 2;
-    const double2 *w2 = reinterpret_cast<const double2 *>(w), *v2 = reinterpret_cast<const double2 *>(v);
+    const W2 *w2 = reinterpret_cast<const W2 *>(w);
+    const double2 *v2 = reinterpret_cast<const double2 *>(v);
+    float2 *r322 = reinterpret_cast<float2 *>(r32);
     double2 *d2 = reinterpret_cast<double2 *>(d), *u2 = reinterpret_cast<double2 *>(u);
     double2 *q2 = reinterpret_cast<double2 *>(q), *r2 = reinterpret_cast<double2 *>(r);
     const Y2 *dinv2 = reinterpret_cast<const Y2 *>(dinv);
     Y2 *y2 = reinterpret_cast<Y2 *>(y);
     for (int i = blk * kBlock + threadIdx.x; i < n2; i += gridDim.x * kBlock) {
-        const double2 wi = w2[i], vi = v2[i];
+        const W2 wi = w2[i];
+        const double2 vi = v2[i];
         double2 di, qi;
         if (!First) { di = d2[i]; qi = q2[i]; }
         double2 ui = u2[i], ri = r2[i];
-        update_pair<First>(wi.x, vi.x, di.x, qi.x, ui.x, ri.x, g, an, acc);
-        update_pair<First>(wi.y, vi.y, di.y, qi.y, ui.y, ri.y, g, an, acc);
+        update_pair<First>((double)wi.x, vi.x, di.x, qi.x, ui.x, ri.x, g, an, acc);
+        update_pair<First>((double)wi.y, vi.y, di.y, qi.y, ui.y, ri.y, g, an, acc);
         d2[i] = di;
         q2[i] = qi;
         u2[i] = ui;
         r2[i] = ri;
+        if (r32) {
+            float2 rf;
+            rf.x = (float)ri.x;
+            rf.y = (float)ri.y;
+            r322[i] = rf;
+        }
         if (y) {
             const Y2 dv = dinv2[i];
             Y2 yv;
@@ -283,11 +301,12 @@ __device__ __forceinline__ void update_range(int n, const double *__restrict__ w
     if ((n & 1) && blk == 0 && threadIdx.x == 0) {
         const int i = n - 1;
         double di = First ? 0.0 : d[i], qi = First ? 0.0 : q[i], ui = u[i], ri = r[i];
-        update_pair<First>(w[i], v[i], di, qi, ui, ri, g, an, acc);
+        update_pair<First>((double)w[i], v[i], di, qi, ui, ri, g, an, acc);
         d[i] = di;
         q[i] = qi;
         u[i] = ui;
         r[i] = ri;
+        if (r32) r32[i] = (float)ri;
         if (y) y[i] = dinv[i] * (YV)ri;
     }
 }
@@ -325,10 +344,11 @@ __device__ __forceinline__ bool fcg_scalars(const double (&s)[3], int first, dou
 // dots set: every workgroup first adds the product's ndots block partials in
 // the order the one-block finalize takes with kBlock threads (bit-identical
 // sums) and forms the scalars itself; workgroup 0 stores them.
-template <typename YV>
+template <typename YV, typename WT>
 __global__ void __launch_bounds__(kBlock)
-k_update(int n, int first, const double *__restrict__ w, const double *__restrict__ v, double *__restrict__ d,
-         double *__restrict__ u, double *__restrict__ q, double *__restrict__ r, const YV *__restrict__ dinv,
+k_update(int n, int first, const WT *__restrict__ w, const double *__restrict__ v, double *__restrict__ d,
+         double *__restrict__ u, double *__restrict__ q, double *__restrict__ r, float *__restrict__ r32,
+         const YV *__restrict__ dinv,
          YV *__restrict__ y, double *__restrict__ scal, double *__restrict__ partials,
          const double *__restrict__ dots, int ndots) {
     if (scal[10] != 0.0) return;
@@ -358,10 +378,10 @@ k_update(int n, int first, const double *__restrict__ w, const double *__restric
     double acc[1] = {0.0};
     if (ok) {
         const bool pairs = (long long)n >= 4LL * gridDim.x * kBlock;
-        if (pairs && first) update_range<true>(n, w, v, d, u, q, r, dinv, y, g, an, acc[0]);
-        else if (pairs) update_range<false>(n, w, v, d, u, q, r, dinv, y, g, an, acc[0]);
-        else if (first) update_range1<true>(n, w, v, d, u, q, r, dinv, y, g, an, acc[0]);
-        else update_range1<false>(n, w, v, d, u, q, r, dinv, y, g, an, acc[0]);
+        if (pairs && first) update_range<true>(n, w, v, d, u, q, r, r32, dinv, y, g, an, acc[0]);
+        else if (pairs) update_range<false>(n, w, v, d, u, q, r, r32, dinv, y, g, an, acc[0]);
+        else if (first) update_range1<true>(n, w, v, d, u, q, r, r32, dinv, y, g, an, acc[0]);
+        else update_range1<false>(n, w, v, d, u, q, r, r32, dinv, y, g, an, acc[0]);
     }
     block_partials<1>(acc, partials);
     if (blockIdx.x == 0 && threadIdx.x == 0) scal[7] = 1.0;  // partials for the stop test

@@ -416,7 +416,7 @@ k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, cons
             const int t = (blk - T.nch) * kWaves + (int)(threadIdx.x >> 6);
             if (t >= T.nmid) return;
             const int E = T.mid[t];
-            const V acc = down_members<64, S>(E, mem, rp, ci, a, dinv, p, b, lv, nullptr);
+            const V acc = down_members<64, S, true>(E, mem, rp, ci, a, dinv, p, b, lv, nullptr);
             if ((threadIdx.x & 63) == 0 && !(done && *done != 0.0)) bc[E] = acc;
             return;
         }
@@ -1190,7 +1190,7 @@ k_jacobi_sweep(int n, const int *__restrict__ rp, const int *__restrict__ ci, co
 #pragma unroll
         for (int k = 0; k < R; ++k) s[k] = 0.0;
     } else {
-        rows_dot<G, R, double>(rp, ci, a, rows, s, f, lv, &lgm);
+        rows_dot<G, R, double>(rp, ci, a, rows, s, f, lv, Tier ? &lgm : nullptr);
     }
     const bool live = !(done && *done != 0.0);
 #pragma unroll
@@ -1215,7 +1215,7 @@ template <int G>
 __global__ void __launch_bounds__(kBlock)
 k_resid(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
         const double *__restrict__ b, const double *__restrict__ u, double *__restrict__ r,
-        double *__restrict__ partials, LongView<double> lv) {
+        float *__restrict__ r32, double *__restrict__ partials, LongView<double> lv) {
     constexpr int NG = kBlock / G, R = kRows;
     const int lane = threadIdx.x % G;
     const int blk = xcd_block(blockIdx.x, gridDim.x);
@@ -1242,10 +1242,11 @@ k_resid(int n, const int *__restrict__ rp, const int *__restrict__ ci, const dou
 }
 
 // v = A w with partials of alpha = w.r, beta = w.v, gamma = w.q in the same pass
-template <int G>
+template <int G, typename W>
 __global__ void __launch_bounds__(kBlock)
+                if (r32) r32[rows[k]] = (float)ri;
 k_spmv_dots(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
-            const double *__restrict__ w, const double *__restrict__ r, const double *__restrict__ q,
+            const W *__restrict__ w, const double *__restrict__ r, const double *__restrict__ q,
             double *__restrict__ v, double *__restrict__ partials, const double *__restrict__ done,
             LongView<double> lv) {
     if (done && *done != 0.0) return;
@@ -1258,13 +1259,13 @@ k_spmv_dots(int n, const int *__restrict__ rp, const int *__restrict__ ci, const
 #pragma unroll
         for (int k = 0; k < R; ++k) rows[k] = base + k * NG < n ? base + k * NG : -1;
         double s[R];
-        rows_dot<G, R, double>(rp, ci, a, rows, s, FGather<double, double>{w}, lv);
+        rows_dot<G, R, double>(rp, ci, a, rows, s, FGather<double, W>{w}, lv);
         if (lane == 0) {
 #pragma unroll
             for (int k = 0; k < R; ++k) {
                 const int i = rows[k];
                 if (i < 0) continue;
-                const double wi = w[i];
+                const double wi = (double)w[i];
                 v[i] = s[k];
                 acc[0] += wi * r[i];
                 acc[1] += wi * s[k];
@@ -1792,13 +1793,13 @@ void launch_coarse_build(hipStream_t s, const Level &L, int sweeps, double *S) {
 }
 
 void launch_resid(hipStream_t s, const Level &L, int nb, const double *b, const double *u, double *r,
-                  double *partials, double *scal) {
+                  float *r32, double *partials, double *scal) {
     if (L.E.sp) {
         with_sell<double>(L.E, [&](auto *ix, auto *vals, auto kb) {
             using I = std::remove_const_t<std::remove_pointer_t<decltype(ix)>>;
             using S = std::remove_const_t<std::remove_pointer_t<decltype(vals)>>;
             hipLaunchKernelGGL((k_resid_sell<I, S, decltype(kb)::value>), dim3(nb), dim3(kBlock), 0, s, L.A.n, L.E.sp, L.E.uni, L.E.su, ix, vals, b, u, r,
-                               partials);
+                               r32, partials);
         });
         return;
     }
@@ -1806,7 +1807,7 @@ void launch_resid(hipStream_t s, const Level &L, int nb, const double *b, const 
     with_G(L.G, [&](auto gc) {
         constexpr int g = decltype(gc)::value;
         hipLaunchKernelGGL(k_resid<g>, dim3(nb), dim3(kBlock), 0, s, L.A.n, L.A.rp, L.A.ci, L.A.v, b, u, r,
-                           partials, long_view<double>(L.lr));
+                           r32, partials, long_view<double>(L.lr));
     });
 }
 
@@ -1821,8 +1822,9 @@ int spmv_dots_grid(const Level &L, int nb) {
     return L.E.sp && split_slots(L, L.E.wide ? 16 : 8) ? L.E.nslices : std::min(nb, kSpmvBlocks);
 }
 
-void launch_spmv_dots(hipStream_t s, const Level &L, int nb, int first, const double *w, const double *r,
-                      const double *q, double *v, double *partials, double *scal) {
+template <typename W>
+static void spmv_dots_t(hipStream_t s, const Level &L, int nb, const W *w, const double *r, const double *q, double *v,
+                        double *partials, double *scal) {
     if (L.E.sp) {
         with_sell<double>(L.E, [&](auto *ix, auto *vals, auto kb) {
             using I = std::remove_const_t<std::remove_pointer_t<decltype(ix)>>;
@@ -1832,10 +1834,10 @@ void launch_spmv_dots(hipStream_t s, const Level &L, int nb, int first, const do
             auto go = [&](auto nt) {  // NT: the values streamed non-temporally (Sell::stream)
                 constexpr bool NT = decltype(nt)::value;
                 if (split_slots(L, decltype(kb)::value))
-                    launch_k((k_spmv_dots_sell_p<I, S, 4, NT>), dim3(nb), dim3(kBlock), s, L.A.n, L.E.sp, L.E.uni,
+                    launch_k((k_spmv_dots_sell_p<I, S, W, 4, NT>), dim3(nb), dim3(kBlock), s, L.A.n, L.E.sp, L.E.uni,
                              L.E.su, ix, vals, w, r, q, v, partials, scal + 10);
                 else
-                    launch_k((k_spmv_dots_sell<I, S, decltype(kb)::value, NT>), dim3(nb), dim3(kBlock), s, L.A.n,
+                    launch_k((k_spmv_dots_sell<I, S, W, decltype(kb)::value, NT>), dim3(nb), dim3(kBlock), s, L.A.n,
                              L.E.sp, L.E.uni, L.E.su, ix, vals, w, r, q, v, partials, scal + 10);
             };
             if (L.E.stream) go(std::true_type{});
@@ -1843,10 +1845,10 @@ void launch_spmv_dots(hipStream_t s, const Level &L, int nb, int first, const do
         });
         return;
     }
-    long_pre(s, L, (const double *)L.A.v, FGather<double, double>{w}, scal + 10);
+    long_pre(s, L, (const double *)L.A.v, FGather<double, W>{w}, scal + 10);
     with_G(L.G, [&](auto gc) {
         constexpr int g = decltype(gc)::value;
-        launch_k((k_spmv_dots<g>), dim3(nb), dim3(kBlock), s, L.A.n, L.A.rp, L.A.ci, L.A.v, w, r, q, v,
+        launch_k((k_spmv_dots<g, W>), dim3(nb), dim3(kBlock), s, L.A.n, L.A.rp, L.A.ci, L.A.v, w, r, q, v,
                            partials, scal + 10, long_view<double>(L.lr));
     });
 }
@@ -1856,15 +1858,18 @@ void launch_spmv_dots(hipStream_t s, const Level &L, int nb, int first, const do
 // one-workgroup-per-slice product's thousands of partials keep that launch.
 bool update_takes_dots(int nbs) { return nbs <= kSpmvBlocks; }
 
-void launch_update(hipStream_t s, int n, int nb, int first, const double *w, const double *v, double *d,
-                   double *u, double *q, double *r, double *partials, double *scal, const void *dinv, void *y,
-                   int y_f32, const double *dots, int ndots) {
-    if (y && y_f32)
-        launch_k((k_update<float>), dim3(nb), dim3(kBlock), s, n, first, w, v, d, u, q, r, (const float *)dinv,
-                 (float *)y, scal, partials, dots, ndots);
+void launch_update(hipStream_t s, int n, int nb, int first, const void *w, int w_f32, const double *v, double *d,
+                   double *u, double *q, double *r, float *r32, double *partials, double *scal, const void *dinv,
+                   void *y, int y_f32, const double *dots, int ndots) {
+    if (w_f32)  // (then y, if any, is float32 too)
+        launch_k((k_update<float, float>), dim3(nb), dim3(kBlock), s, n, first, (const float *)w, v, d, u, q, r, r32,
+                 (const float *)dinv, (float *)y, scal, partials, dots, ndots);
+    else if (y && y_f32)
+        launch_k((k_update<float, double>), dim3(nb), dim3(kBlock), s, n, first, (const double *)w, v, d, u, q, r, r32,
+                 (const float *)dinv, (float *)y, scal, partials, dots, ndots);
     else
-        launch_k((k_update<double>), dim3(nb), dim3(kBlock), s, n, first, w, v, d, u, q, r, (const double *)dinv,
-                 (double *)y, scal, partials, dots, ndots);
+        launch_k((k_update<double, double>), dim3(nb), dim3(kBlock), s, n, first, (const double *)w, v, d, u, q, r,
+                 r32, (const double *)dinv, (double *)y, scal, partials, dots, ndots);
 }
 
 void launch_finalize(hipStream_t s, int mode, int nb, int first, const double *partials, double *scal) {
@@ -1877,6 +1882,12 @@ void launch_finalize(hipStream_t s, int mode, int nb, int first, const double *p
 void launch_sampled_outer(hipStream_t s, const Level &L, const double *lam, const double *x, double *G) {
     with_G(L.G, [&](auto gc) {
         constexpr int g = decltype(gc)::value;
+void launch_spmv_dots(hipStream_t s, const Level &L, int nb, const void *w, int w_f32, const double *r,
+                      const double *q, double *v, double *partials, double *scal) {
+    if (w_f32) spmv_dots_t(s, L, nb, (const float *)w, r, q, v, partials, scal);
+    else spmv_dots_t(s, L, nb, (const double *)w, r, q, v, partials, scal);
+}
+
         constexpr int R = 4;
         hipLaunchKernelGGL((k_sampled_outer<g, R>), dim3(blocks_for(((long long)L.A.n + R - 1) / R * g)),
                            dim3(kBlock), 0, s, L.A.n, L.A.rp, L.A.ci, lam, x, G,
