@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libbcm.so")
-SOURCES = ["setup.hip", "scan.hip", "star.hip", "solve.hip", "api.hip"]
+SOURCES = ["setup.hip", "scan.hip", "star.hip", "power.hip", "solve.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = [

@@ -692,6 +692,65 @@ int build_coarsest_star(bcm_handle *h, hipStream_t s, Arena &tmp, HostTables &ho
     return build_chain(h, s, tmp, host, h->nl - 1, std::vector<int>{f[1]}, false);
 }
 
+// Powers of the coarsest level's sweep matrix, while they stay sparse enough
+// (PowerOp); the sweeps must be a multiple of the power.
+int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
+    Level &L = h->lv[h->nl - 1];
+    const int n = L.A.n, sweeps = h->prm.coarse_sweeps;
+    if (sweeps % 2 || L.lr.n > 0 || L.A.dmax > power_row_limit() || n > (1 << 17)) return BCM_OK;
+    tmp.rewind();
+    int *ctl = tmp.get_n<int>(2), *cnt = tmp.get_n<int>(n), *pre = tmp.get_n<int>(n);
+    void *stmp = tmp.get(scan_tmp_bytes(n));
+    NOMEM(ctl && cnt && pre && stmp);
+    // sum and maximum of n counts
+    int r[2];
+    auto totals = [&](const int *in) {
+        scan_exclusive(s, in, pre, n, ctl, stmp, ctl + 1);
+        return read_back(s, ctl, sizeof(r), r);
+    };
+    auto matrix = [&](Arena &a, int longest, PowerMat &M) {
+        M.W = power_stride(longest);
+        M.col = a.get_n<int>((size_t)n * M.W);
+        M.val = a.get_n<double>((size_t)n * M.W);
+        return M.col && M.val;
+    };
+    PowerOp P;
+    P.m[0].len = h->persist.get_n<int>(n);
+    P.m[0].nnz = L.A.nnz;
+    NOMEM(P.m[0].len && matrix(h->persist, L.A.dmax, P.m[0]));
+    launch_power_first(s, L, P.m[0]);
+    for (int t = 0; t < (sweeps % 4 ? 1 : 2); ++t) {
+        const PowerMat &M = P.m[t];
+        const long long most = t == 0 ? kPower2 : kPower4;
+        if (t > 0 && r[1] > power_row_limit()) break;  // (r: M's entries and longest row)
+        launch_power_products(s, n, M, cnt);
+        int rc = totals(cnt);
+        if (rc) return rc;
+        // (a square keeps about 6 of 10 products of a first power, 1 of 5 of a second)
+        const int cand = r[1];
+        if (cand > power_cand_limit() || r[0] > (t == 0 ? 5 * most / 2 : 8 * most)) break;
+        PowerMat Q;
+        Q.len = h->persist.get_n<int>(n);
+        NOMEM(Q.len);
+        launch_power_square(s, 0, n, M, Q, cnt, cand);
+        rc = totals(Q.len);
+        if (rc) return rc;
+        if (r[0] > most || (long long)n * power_stride(r[1]) > 8 * most) break;
+        Q.nnz = r[0];
+        NOMEM(matrix(h->persist, r[1], Q));
+        launch_power_square(s, 1, n, M, Q, cnt, cand);
+        P.m[t + 1] = Q;
+        P.p = 2 << t;
+    }
+    if (P.p == 0) return BCM_OK;
+    for (auto &b : P.buf) {
+        b = h->persist.get_n<double>(n);
+        NOMEM(b);
+    }
+    L.power = P;
+    return BCM_OK;
+}
+
 // Appends the levels of a chain of stars below level k, when level k is a star
 // whose hub is coupled to every row: `sweeps` launches per level, run ahead
 // without a read-back (every sweep forms one pair, so all sizes are known).
@@ -853,7 +912,7 @@ int find_mid_rows(bcm_handle *h, hipStream_t s, Arena &tmp) {
     for (int l = 0; l < h->nl; ++l) {
         const Level &L = h->lv[l];
         const bool legs = l < kc && !down_on_sell(L);
-        const bool sweeps = l == h->nl - 1 && h->ctmp[0] && L.chain.hub < 0;
+        const bool sweeps = l == h->nl - 1 && h->ctmp[0] && L.chain.hub < 0 && L.power.p == 0;
         const int tm = L.G < 32 ? kMidFactor * L.G : long_min(L.G);
         if ((legs || sweeps) && (L.lr.n > 0 || L.A.dmax > 2 * tm)) lv.push_back(l);
     }
@@ -1309,11 +1368,15 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
                 tmp.rewind();
                 double *W = tmp.get_n<double>(nn2), *M = tmp.get_n<double>(nn2), *Ad = tmp.get_n<double>(nn2);
                 NOMEM(W && M && Ad);
-                if (P.coarse_sweeps > 1) {
+                if (P.coarse_sweeps > 1 && sweep_doubling(C)) {
                     launch_sweep_operator(s, C, P.coarse_sweeps, P.check != 0, C.S, W, M, Ad);
-                } else {  // one sweep from zero: D
-                    launch_fill_i32(s, 2 * nn2, (int *)W, 0);
-                    launch_fold_left(s, C, W, C.S);
+                } else {  // S_(t+1) = D + (I - D A) S_t from S_0 = 0
+                    double *cur = (P.coarse_sweeps % 2) ? W : C.S, *nxt = (P.coarse_sweeps % 2) ? C.S : W;
+                    launch_fill_i32(s, 2 * nn2, (int *)cur, 0);
+                    for (int t = 0; t < P.coarse_sweeps; ++t) {
+                        launch_fold_left(s, C, cur, nxt);
+                        std::swap(cur, nxt);
+                    }
                 }
             }
         }
@@ -1425,6 +1488,10 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             const int rc = build_coarsest_star(h, s, tmp, host);
             if (rc) return rc;
         }
+        if (h->lv[h->nl - 1].chain.hub < 0) {
+            const int rc = build_power(h, s, tmp);
+            if (rc) return rc;
+        }
     }
     if (const int rc = find_mid_rows(h, s, tmp)) return rc;
     // flexible CG state
@@ -1438,6 +1505,11 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
     h->red_blocks = reduce_blocks(n);
     h->partials = h->persist.get_n<double>(4 * (size_t)h->red_blocks);
     NOMEM(h->r && h->w && h->d && h->v && h->q && h->u && h->scal && h->partials);
+    if (fp32 && h->nl > 1) {  // (a single level's cycle is the coarsest solve, in float64)
+        h->r32 = h->persist.get_n<float>(n);
+        h->w32 = h->persist.get_n<float>(n);
+        NOMEM(h->r32 && h->w32);
+    }
     {
         const Level &F = h->lv[0];
         // levels whose down leg gathers dinv o b (long rows) get it from the
@@ -1505,11 +1577,6 @@ bool y_by_restrict(const bcm_handle *h, int k) {
 }
 
 double bytes_down(const bcm_handle *h, int k) {
-    if (fp32 && h->nl > 1) {  // (a single level's cycle is the coarsest solve, in float64)
-        h->r32 = h->persist.get_n<float>(n);
-        h->w32 = h->persist.get_n<float>(n);
-        NOMEM(h->r32 && h->w32);
-    }
     const Level &L = h->lv[k];
     const bool f32 = h->prm.precision == BCM_FP32_CYCLE;
     const double sv = f32 ? 4 : 8, sb = sv;
@@ -1881,6 +1948,10 @@ const void *y0_dinv(const bcm_handle *h) {
     return h->prm.precision == BCM_FP32_CYCLE ? (const void *)h->lv[0].dinv32 : (const void *)h->lv[0].dinv;
 }
 
+// The cycle's input and output in the flexible-CG loop.
+const void *cycle_in(const bcm_handle *h) { return h->r32 ? (const void *)h->r32 : (const void *)h->r; }
+void *cycle_out(const bcm_handle *h) { return h->w32 ? (void *)h->w32 : (void *)h->w; }
+
 // The flexible-CG stop test after an update is taken by workgroup 0 of the
 // next cycle's first kernel where that is a sliced-ELL residual kernel (it
 // hides behind the other workgroups); elsewhere a one-block finalize launch
@@ -1948,10 +2019,6 @@ int fcg_run(bcm_handle *h, const double *b, double *x_user, double tol) {
     const int n = L0.A.n, nb = h->red_blocks, nbs = spmv_dots_grid(L0, nb);
     Prof pf{h, h->prm.profile};
     // graph mode: a profile mask of one class bracketed once per iteration
-// The cycle's input and output in the flexible-CG loop.
-const void *cycle_in(const bcm_handle *h) { return h->r32 ? (const void *)h->r32 : (const void *)h->r; }
-void *cycle_out(const bcm_handle *h) { return h->w32 ? (void *)h->w32 : (void *)h->w; }
-
     // (down0, up0, spmv_dots, update, coarse) is timed by events recorded
     // around that class's own graph; other masks launch every iteration eagerly
     int gcls = -1;

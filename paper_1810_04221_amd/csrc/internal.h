@@ -252,6 +252,23 @@ struct StarSweep {
     int *mem;
 };
 
+// A power of the coarsest level's sweep matrix (power.hip): row i's len[i] entries
+// from i W, padded to W with (i, 0).
+struct PowerMat {
+    int W = 0;
+    int *len = nullptr, *col = nullptr;
+    double *val = nullptr;
+    long long nnz = 0;
+};
+struct PowerOp {
+    int p = 0;          // sweeps per application of the highest power (0: none)
+    PowerMat m[3];      // M, M^2, M^4
+    double *buf[3] = {nullptr, nullptr, nullptr};
+};
+// Entries of M^2 and of M^4 up to which they are applied: one application then
+// costs little more than the launch that it saves (12 B an entry: 24 and 12 MB).
+constexpr long long kPower2 = 2LL << 20, kPower4 = 1LL << 20;
+
 // One level of the hierarchy.  Row i of A^k, its l1 inverse diagonal, the
 // composed prolongator P^k (one nonzero per row: column agg[i], value p[i]),
 // and the members of every coarse aggregate (P^k transposed) in ascending
@@ -277,6 +294,7 @@ struct Level {
     void *xs = nullptr;               // W/K-cycle: result of the second coarse cycle (cycle precision)
     void *kv = nullptr;               // K-cycle: A c1, the product of the first coarse direction
     double *S = nullptr;  // coarsest level only: dense sweep operator (n <= kCoarseDense)
+    PowerOp power;        // coarsest level only: its sweeps by powers (p > 0)
     ChainOp chain;        // star levels: the V-cycle from this level down (coarsest: its sweeps), hub >= 0
 };
 
@@ -318,6 +336,9 @@ struct bcm_handle {
     bcm::Arena persist, scratch;
     // flexible CG vectors (float64, n of the finest level)
     double *r = nullptr, *w = nullptr, *d = nullptr, *v = nullptr, *q = nullptr;
+    // FP32 cycle of two or more levels: the cycle's input r rounded to float32 (written
+    // beside r) and its result, which is then not kept in w; else null
+    float *r32 = nullptr, *w32 = nullptr;
     double *u = nullptr;                  // iterate of the solve (the caller's x is copied in and out)
     void *y0 = nullptr;  // dinv o r of the finest level in the cycle's type, written by the update
                          // (finest levels whose sliced-ELL down leg gathers dinv o b; else null)
@@ -336,9 +357,6 @@ struct bcm_handle {
     int kt = -1;                           // first level handled by the tail kernel (-1: none)
     int kf = 0;                            // first level of the folded dense operator (0: none):
                                            // the V- or W-cycle from level kf down, as one n_kf x n_kf map
-    // FP32 cycle of two or more levels: the cycle's input r rounded to float32 (written
-    // beside r) and its result, which is then not kept in w; else null
-    float *r32 = nullptr, *w32 = nullptr;
     double *fold = nullptr;                // that operator, n_kf x n_kf row-major, float64
     int kc = 0;                            // first level of a star chain applied as lv[kc].chain (0: none)
     int long_star = 0;                     // long rows of the star levels that keep no long-row list
@@ -464,6 +482,20 @@ void launch_fill_u64(hipStream_t s, size_t n, unsigned long long *dst, unsigned 
 void launch_copy_f64(hipStream_t s, size_t n, const double *src, double *dst);
 // dst = src on the finest level's vector length; also a graph-safe fill (no memset node)
 
+// ---- powers of the coarsest sweep matrix (power.hip) ----
+int power_row_limit();   // longest row of a matrix that is squared
+int power_cand_limit();  // most products that form one row of the square
+int power_stride(int longest);
+void launch_power_first(hipStream_t s, const Level &L, const PowerMat &M);
+// cnt[i] = products that form row i of M M
+void launch_power_products(hipStream_t s, int n, const PowerMat &M, int *cnt);
+// pass 0: Q.len (the columns of each row of M M); pass 1: Q's entries
+// (products: launch_power_products' counts, most: their maximum)
+void launch_power_square(hipStream_t s, int pass, int n, const PowerMat &M, const PowerMat &Q, const int *products,
+                         int most);
+void launch_power(hipStream_t s, const PowerOp &P, int n, int sweeps, const double *dinv, const void *b, void *x,
+                  int b_f64, int x_f64, const double *done);
+
 // ---- star levels (star.hip) ----
 // out (4 ints, zero before): [0] rows of more than two entries [1] the largest
 // of them [2] != 0: another row is not {diagonal} or {diagonal, one column}
@@ -545,6 +577,8 @@ void launch_fold_level(hipStream_t s, const Level &L, const double *Tc, int nc, 
 // (T, W n x n row-major; M n x n scratch)
 // sym: A (and so T) is known to be exactly symmetric
 void launch_fold_w(hipStream_t s, const Level &L, const double *T, double *M, double *W, bool sym);
+// true when the sweep operator is formed by doubling (launch_sweep_operator)
+bool sweep_doubling(const Level &L);
 // S = sum_{t < sweeps} (I - D A)^t D of the coarsest level, n x n, sweeps >= 2
 // (W, M, Ad: n x n scratch)
 void launch_sweep_operator(hipStream_t s, const Level &L, int sweeps, bool sym, double *S, double *W, double *M,

@@ -197,7 +197,8 @@ __device__ __forceinline__ V row_rest(const int *__restrict__ ci, const V *__res
 // than lv.lmin take their chunk sums instead.
 // s[k] = sum_q a[q] * f(ci[q]) over row rows[k] (rows[k] < 0: empty).
 // *lgm (when given) gets bit k set when row rows[k] is long.
-template <int G, int R, typename V, typename F>
+// Rest = false: no row holds more than G entries.
+template <int G, int R, typename V, bool Rest = true, typename F>
 __device__ __forceinline__ void rows_dot(const int *__restrict__ rp, const int *__restrict__ ci,
                                          const V *__restrict__ a, const int (&rows)[R], V (&s)[R], F f,
                                          const LongView<V> &lv = LongView<V>(), int *lgm = nullptr) {
@@ -223,7 +224,8 @@ __device__ __forceinline__ void rows_dot(const int *__restrict__ rp, const int *
         s[k] = in ? t : V(0);
     }
 #pragma unroll
-    for (int k = 0; k < R; ++k) s[k] = row_rest<G>(ci, a, beg[k] + lane + G, end[k], s[k], f);
+    for (int k = 0; k < R; ++k)
+        if (Rest) s[k] = row_rest<G>(ci, a, beg[k] + lane + G, end[k], s[k], f);
 #pragma unroll
     for (int k = 0; k < R; ++k) s[k] = group_sum<G>(s[k]);
 #pragma unroll
@@ -377,7 +379,7 @@ __device__ __forceinline__ void down_chunk(int c, const LongRows &lr, const int 
 
 // S members (template) of one aggregate, all rows in flight at once; summed
 // in ascending member order.
-template <int G, int S, typename V, typename VB>
+template <int G, int S, bool Rest, typename V, typename VB>
 __device__ __forceinline__ V down_members(int E, const int *__restrict__ mem, const int *__restrict__ rp,
                                           const int *__restrict__ ci, const V *__restrict__ a,
                                           const V *__restrict__ dinv, const V *__restrict__ p,
@@ -386,7 +388,7 @@ __device__ __forceinline__ V down_members(int E, const int *__restrict__ mem, co
 #pragma unroll
     for (int t = 0; t < S; ++t) rows[t] = mem[(size_t)E * S + t];
     V s[S];
-    rows_dot<G, S, V>(rp, ci, a, rows, s, FScaled<V, VB>{dinv, b}, lv, lgm);
+    rows_dot<G, S, V, Rest>(rp, ci, a, rows, s, FScaled<V, VB>{dinv, b}, lv, lgm);
     V acc = V(0);
 #pragma unroll
     for (int t = 0; t < S; ++t) {
@@ -397,13 +399,21 @@ __device__ __forceinline__ V down_members(int E, const int *__restrict__ mem, co
     return acc;
 }
 
-template <int G, int S, typename V, typename VB, bool Tier>
+// Mode: a level's rows.  kLegShort: none longer than its group of G lanes (the
+// rest loop is left out); kLegTiers: mid or long rows (Tiers); kLegPlain: others.
+enum : int { kLegPlain = 0, kLegTiers = 1, kLegShort = 2 };
+inline int leg_mode(const Level &L, const Tiers &T) {
+    return T.off > 0 ? kLegTiers : (L.A.dmax > 0 && L.A.dmax <= L.G ? kLegShort : kLegPlain);
+}
+
+template <int G, int S, typename V, typename VB, int Mode>
 __global__ void __launch_bounds__(kBlock)
 k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, const int *__restrict__ ci,
            const V *__restrict__ a, const V *__restrict__ dinv, const V *__restrict__ p,
            const VB *__restrict__ b, V *__restrict__ bc, const double *__restrict__ done, Tiers T) {
     // small levels: the solve-ended flag is only tested before the store, so
     // its load overlaps the row loads instead of preceding them
+    constexpr bool Tier = Mode == kLegTiers;
     LongView<V> lv;
     int blk = blockIdx.x, nb = gridDim.x;
     if (Tier) {
@@ -429,7 +439,7 @@ k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, cons
     const bool live = E < nc;
     if (!live) E = nc - 1;
     int lgm = 0;
-    const V acc = down_members<G, S>(E, mem, rp, ci, a, dinv, p, b, lv, &lgm);
+    const V acc = down_members<G, S, Mode != kLegShort>(E, mem, rp, ci, a, dinv, p, b, lv, Tier ? &lgm : nullptr);
     if (lane == 0 && live && !(Tier && lgm) && !(done && *done != 0.0)) bc[E] = acc;
 }
 
@@ -497,11 +507,12 @@ k_restrict(int nc, const int *__restrict__ mem, const V *__restrict__ pr, V *__r
 //   x_j = dinv_j b_j + p_j xc[agg_j]          (pre-smoothed x plus P x_c)
 //   x_i <- x_i + dinv_i (b_i - sum_j a_ij x_j)
 // ----------------------------------------------------------------------------
-template <int G, int R, typename V, typename VB, typename VX, bool Tier>
+template <int G, int R, typename V, typename VB, typename VX, int Mode>
 __global__ void __launch_bounds__(kBlock)
 k_up(int n, const int *__restrict__ rp, const int *__restrict__ ci, const V *__restrict__ a,
      const V *__restrict__ dinv, const V *__restrict__ p, const int *__restrict__ agg,
      const VB *__restrict__ b, const V *__restrict__ xc, VX *__restrict__ x, const double *__restrict__ done, Tiers T) {
+    constexpr bool Tier = Mode == kLegTiers;
     const FProlonged<V, VB> f{dinv, p, agg, b, xc};
     auto put = [&](int i, V s) {
         const V bi = (V)b[i];
@@ -539,7 +550,7 @@ k_up(int n, const int *__restrict__ rp, const int *__restrict__ ci, const V *__r
     for (int k = 0; k < R; ++k) rows[k] = base + k * NG < n ? base + k * NG : -1;
     V s[R];
     int lgm = 0;
-    rows_dot<G, R, V>(rp, ci, a, rows, s, f, lv, &lgm);
+    rows_dot<G, R, V, Mode != kLegShort>(rp, ci, a, rows, s, f, lv, Tier ? &lgm : nullptr);
     if (lane == 0 && !(done && *done != 0.0)) {
 #pragma unroll
         for (int k = 0; k < R; ++k)
@@ -1233,6 +1244,7 @@ k_resid(int n, const int *__restrict__ rp, const int *__restrict__ ci, const dou
                 const double bi = b[rows[k]];
                 const double ri = bi - s[k];
                 r[rows[k]] = ri;
+                if (r32) r32[rows[k]] = (float)ri;
                 acc[0] += ri * ri;
                 acc[1] += bi * bi;
             }
@@ -1244,7 +1256,6 @@ k_resid(int n, const int *__restrict__ rp, const int *__restrict__ ci, const dou
 // v = A w with partials of alpha = w.r, beta = w.v, gamma = w.q in the same pass
 template <int G, typename W>
 __global__ void __launch_bounds__(kBlock)
-                if (r32) r32[rows[k]] = (float)ri;
 k_spmv_dots(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
             const W *__restrict__ w, const double *__restrict__ r, const double *__restrict__ q,
             double *__restrict__ v, double *__restrict__ partials, const double *__restrict__ done,
@@ -1401,12 +1412,14 @@ void down_dispatch(hipStream_t s, const Level &L, const V *a, const V *dinv, con
         constexpr int SS = decltype(sc)::value;
         const Tiers T = tiers_of(L, true);
         grid.x += T.off;
-        if (T.off > 0)
-            launch_k((k_down_seq<G, SS, V, VB, true>), grid, dim3(kBlock), s, L.nc, L.mem, L.A.rp, L.A.ci, a, dinv, p,
-                     b, bc, done, T);
-        else
-            launch_k((k_down_seq<G, SS, V, VB, false>), grid, dim3(kBlock), s, L.nc, L.mem, L.A.rp, L.A.ci, a, dinv, p,
-                     b, bc, done, T);
+        auto go = [&](auto mc) {
+            launch_k((k_down_seq<G, SS, V, VB, decltype(mc)::value>), grid, dim3(kBlock), s, L.nc, L.mem, L.A.rp,
+                     L.A.ci, a, dinv, p, b, bc, done, T);
+        };
+        const int mode = leg_mode(L, T);
+        if (mode == kLegTiers) go(std::integral_constant<int, kLegTiers>{});
+        else if (mode == kLegShort) go(std::integral_constant<int, kLegShort>{});
+        else go(std::integral_constant<int, kLegPlain>{});
     };
     if (S == 1) seq(std::integral_constant<int, 1>{});
     else if (S == 2) seq(std::integral_constant<int, 2>{});
@@ -1513,12 +1526,14 @@ void up_t(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p, 
         dim3 grid(blocks_for(((long long)L.A.n * g + R - 1) / R));
         const Tiers T = tiers_of(L, false);
         grid.x += T.off;
-        if (T.off > 0)
-            launch_k((k_up<g, R, V, VB, VX, true>), grid, dim3(kBlock), s, L.A.n, L.A.rp, L.A.ci, a, dinv, p, L.agg, b,
-                     xc, x, done, T);
-        else
-            launch_k((k_up<g, R, V, VB, VX, false>), grid, dim3(kBlock), s, L.A.n, L.A.rp, L.A.ci, a, dinv, p, L.agg,
-                     b, xc, x, done, T);
+        auto go = [&](auto mc) {
+            launch_k((k_up<g, R, V, VB, VX, decltype(mc)::value>), grid, dim3(kBlock), s, L.A.n, L.A.rp, L.A.ci, a,
+                     dinv, p, L.agg, b, xc, x, done, T);
+        };
+        const int mode = leg_mode(L, T);
+        if (mode == kLegTiers) go(std::integral_constant<int, kLegTiers>{});
+        else if (mode == kLegShort) go(std::integral_constant<int, kLegShort>{});
+        else go(std::integral_constant<int, kLegPlain>{});
     });
 }
 
@@ -1537,6 +1552,11 @@ void coarse_t(hipStream_t s, const Level &L, int sweeps, const VB *b, VX *x, dou
     }
     if (L.chain.hub >= 0) {  // a star: the sweeps as one linear map (two launches instead of one per sweep)
         launch_chain(s, L.chain, b, x, std::is_same<VB, double>::value, std::is_same<VX, double>::value, done);
+        return;
+    }
+    if (L.power.p > 0) {
+        launch_power(s, L.power, n, sweeps, L.dinv, b, x, std::is_same<VB, double>::value,
+                     std::is_same<VX, double>::value, done);
         return;
     }
     double *xo = ta, *xn = tb;
@@ -1726,6 +1746,12 @@ void launch_fold_w(hipStream_t s, const Level &L, const double *T, double *M, do
                        (const double *)nullptr, W);
 }
 
+// Doubling needs three products on the matrix cores for 20 sweeps (0.03 ps for
+// each of the n^3 multiply-adds, by symmetry) and saves 16 sparse ones (0.5 ps,
+// n nnz): from n^2 / 80 entries on.  A 7-point level of 2000 rows stays with its 20
+// launches of about 14 us (setup of an 80^3 W-cycle: 2.4 ms; doubling took 3.0).
+bool sweep_doubling(const Level &L) { return 80LL * L.A.nnz > (long long)L.A.n * L.A.n; }
+
 // S_k = sum_{t < k} (I - D A)^t D = (I - (I - D A)^k) A^-1, so S_(2k) = 2 S_k - S_k A S_k
 // and S_(k+1) = D + (I - D A) S_k: k is reached from 2 by the bits of `sweeps`
 // (20: 2, 4, 5, 10, 20), where one launch per sweep took 20 products with A.
@@ -1853,6 +1879,12 @@ static void spmv_dots_t(hipStream_t s, const Level &L, int nb, const W *w, const
     });
 }
 
+void launch_spmv_dots(hipStream_t s, const Level &L, int nb, const void *w, int w_f32, const double *r,
+                      const double *q, double *v, double *partials, double *scal) {
+    if (w_f32) spmv_dots_t(s, L, nb, (const float *)w, r, q, v, partials, scal);
+    else spmv_dots_t(s, L, nb, (const double *)w, r, q, v, partials, scal);
+}
+
 // Up to kSpmvBlocks product partials every update workgroup adds them itself
 // (24 KB of L2-resident loads each) instead of a one-block finalize launch; the
 // one-workgroup-per-slice product's thousands of partials keep that launch.
@@ -1882,12 +1914,6 @@ void launch_finalize(hipStream_t s, int mode, int nb, int first, const double *p
 void launch_sampled_outer(hipStream_t s, const Level &L, const double *lam, const double *x, double *G) {
     with_G(L.G, [&](auto gc) {
         constexpr int g = decltype(gc)::value;
-void launch_spmv_dots(hipStream_t s, const Level &L, int nb, const void *w, int w_f32, const double *r,
-                      const double *q, double *v, double *partials, double *scal) {
-    if (w_f32) spmv_dots_t(s, L, nb, (const float *)w, r, q, v, partials, scal);
-    else spmv_dots_t(s, L, nb, (const double *)w, r, q, v, partials, scal);
-}
-
         constexpr int R = 4;
         hipLaunchKernelGGL((k_sampled_outer<g, R>), dim3(blocks_for(((long long)L.A.n + R - 1) / R * g)),
                            dim3(kBlock), 0, s, L.A.n, L.A.rp, L.A.ci, lam, x, G,
