@@ -1952,14 +1952,35 @@ const void *y0_dinv(const bcm_handle *h) {
 const void *cycle_in(const bcm_handle *h) { return h->r32 ? (const void *)h->r32 : (const void *)h->r; }
 void *cycle_out(const bcm_handle *h) { return h->w32 ? (void *)h->w32 : (void *)h->w; }
 
-// The flexible-CG stop test after an update is taken by workgroup 0 of the
-// next cycle's first kernel where that is a sliced-ELL residual kernel (it
-// hides behind the other workgroups); elsewhere a one-block finalize launch
-// after the update takes it.
-bool cycle_takes_stop(const bcm_handle *h) { return h->nl > 1 && down_on_sell(h->lv[0]); }
+// The flexible-CG stop test after an update is taken by the next cycle's first
+// kernel, beside its rows, where that is the finest level's down leg.
+// (Elsewhere a one-block finalize launch after the update takes it: 2 us and
+// its gap an iteration on levels of a few thousand rows.)
+bool cycle_takes_stop(const bcm_handle *h) {
+    // (with kf, kc or kt at level 0 the cycle would start with another kernel: they are >= 1)
+    return h->nl > 1 && down_takes_stop(h->lv[0]);
+}
 
 StopTest stop_test_of(const bcm_handle *h) {
     return cycle_takes_stop(h) ? StopTest{h->partials, h->scal, h->red_blocks} : StopTest{};
+}
+
+// One iteration after its cycle: the product with its dot products, the update
+// and (where the next cycle does not take it) the stop test.
+void fcg_step(bcm_handle *h, hipStream_t s, Prof &pf, int first, int iter) {
+    const Level &L0 = h->lv[0];
+    const int n = L0.A.n, nb = h->red_blocks, w32 = h->w32 != nullptr;
+    const int nbs = spmv_dots_grid(L0, nb);
+    int e = pf.begin(2);
+    launch_spmv_dots(s, L0, nbs, cycle_out(h), w32, h->r, h->q, h->v, h->spart, h->scal);
+    pf.end(2, e, bytes_spmv_dots(h), iter);
+    const bool fuse = update_takes_dots(nbs);
+    if (!fuse) launch_finalize(s, 1, nbs, first, h->spart, h->scal);
+    e = pf.begin(3);
+    launch_update(s, n, nb, first, cycle_out(h), w32, h->v, h->d, h->u, h->q, h->r, h->r32, h->partials, h->scal,
+                  y0_dinv(h), h->y0, h->prm.precision == BCM_FP32_CYCLE, fuse ? h->spart : nullptr, nbs);
+    pf.end(3, e, bytes_update(h), iter);
+    if (!cycle_takes_stop(h)) launch_finalize(s, 2, nb, 0, h->partials, h->scal);
 }
 
 void destroy_iteration_graphs(bcm_handle *h) {
@@ -1981,17 +2002,7 @@ int capture_iteration(bcm_handle *h, int prof_cls) {
     h->s = h->cap;
     sc.begin();
     vcycle(h, gp, cycle_in(h), cycle_out(h), !h->w32, h->scal + 10, 0, h->y0, stop_test_of(h));
-    int e = gp.begin(2);
-    const int nbs = spmv_dots_grid(L0, nb);
-    launch_spmv_dots(h->cap, L0, nbs, cycle_out(h), h->w32 != nullptr, h->r, h->q, h->v, h->spart, h->scal);
-    gp.end(2, e, 0.0, 0);
-    const bool fuse = update_takes_dots(nbs);
-    if (!fuse) launch_finalize(h->cap, 1, nbs, 0, h->spart, h->scal);
-    e = gp.begin(3);
-    launch_update(h->cap, n, nb, 0, cycle_out(h), h->w32 != nullptr, h->v, h->d, h->u, h->q, h->r, h->r32, h->partials,
-                  h->scal, y0_dinv(h), h->y0, h->prm.precision == BCM_FP32_CYCLE, fuse ? h->spart : nullptr, nbs);
-    gp.end(3, e, 0.0, 0);
-    if (!cycle_takes_stop(h)) launch_finalize(h->cap, 2, nb, 0, h->partials, h->scal);
+    fcg_step(h, h->cap, gp, 0, 0);
     sc.end();
     h->s = keep;
     hipError_t err = sc.err;
@@ -2016,7 +2027,7 @@ int capture_iteration(bcm_handle *h, int prof_cls) {
 int fcg_run(bcm_handle *h, const double *b, double *x_user, double tol) {
     hipStream_t s = h->s;
     const Level &L0 = h->lv[0];
-    const int n = L0.A.n, nb = h->red_blocks, nbs = spmv_dots_grid(L0, nb);
+    const int n = L0.A.n, nb = h->red_blocks;
     Prof pf{h, h->prm.profile};
     // graph mode: a profile mask of one class bracketed once per iteration
     // (down0, up0, spmv_dots, update, coarse) is timed by events recorded
@@ -2085,17 +2096,7 @@ int fcg_run(bcm_handle *h, const double *b, double *x_user, double tol) {
                 // the first iteration's r comes from the residual kernel: no y0 yet
                 vcycle(h, pf, cycle_in(h), cycle_out(h), !h->w32, done, launched, first ? nullptr : h->y0,
                        stop_test_of(h));
-                int e = pf.begin(2);
-                launch_spmv_dots(s, L0, nbs, cycle_out(h), h->w32 != nullptr, h->r, h->q, h->v, h->spart, h->scal);
-                pf.end(2, e, bytes_spmv_dots(h), launched);
-                const bool fuse = update_takes_dots(nbs);
-                if (!fuse) launch_finalize(s, 1, nbs, first, h->spart, h->scal);
-                e = pf.begin(3);
-                launch_update(s, n, nb, first, cycle_out(h), h->w32 != nullptr, h->v, h->d, x, h->q, h->r, h->r32,
-                              h->partials, h->scal, y0_dinv(h), h->y0, h->prm.precision == BCM_FP32_CYCLE,
-                              fuse ? h->spart : nullptr, nbs);
-                pf.end(3, e, bytes_update(h), launched);
-                if (!cycle_takes_stop(h)) launch_finalize(s, 2, nb, 0, h->partials, h->scal);
+                fcg_step(h, s, pf, first, launched);
                 first = 0;
                 ++launched;
             }

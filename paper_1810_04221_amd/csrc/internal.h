@@ -534,17 +534,24 @@ void scan_exclusive(hipStream_t s, const int *in, int *out, int n, int *total_de
 // kernel: that kernel is part 1 of the down leg and part 2 of the up leg)
 // true when level L's down leg runs as the sliced-ELL residual + restriction
 inline bool down_on_sell(const Level &L) { return L.E.sp && L.xp && (L.mstride == 2 || L.mstride == 4); }
+// true when the down leg's first kernel can take the stop test: the sliced-ELL
+// residual, or the fused kernel of one, two or four members
+inline bool down_takes_stop(const Level &L) {
+    return down_on_sell(L) || L.mstride == 1 || L.mstride == 2 || L.mstride == 4;
+}
 // yr (part 0 or 1 of a sliced-ELL level's down leg): dinv o b already formed,
 // in the cycle's type; null: formed here when the level needs it.  next (part
 // 0 or 2 of such a leg): the coarser level, whose dinv o b the restriction
 // then also writes into next->yb; null: it does not.
-// st (part 1 of a sliced-ELL level's leg): the flexible-CG stop test that
-// workgroup 0 of its residual kernel takes first (StopTest); default: none.
+// st (part 0 or 1): the flexible-CG stop test taken by the leg's first kernel
+// (StopTest; on levels where down_takes_stop); default: none.
 void launch_down(hipStream_t s, const Level &L, int fp32, const void *b, void *bc, int b_is_f64,
                  const double *done, int part = 0, const void *yr = nullptr, const Level *next = nullptr,
                  StopTest st = {});
+// add: a vector of x's type that the leg adds to its result (fused legs only,
+// levels without xp), or null
 void launch_up(hipStream_t s, const Level &L, int fp32, const void *b, const void *xc, void *x,
-               int b_is_f64, int x_is_f64, const double *done, int part = 0);
+               int b_is_f64, int x_is_f64, const double *done, int part = 0, const void *add = nullptr);
 void launch_coarse(hipStream_t s, const Level &L, int sweeps, const void *b, void *x, int b_f64,
                    int x_f64, void *tmp_a, void *tmp_b, const double *done);
 // true when the coarsest level (without a dense operator) runs in one workgroup

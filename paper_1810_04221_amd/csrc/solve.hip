@@ -410,12 +410,22 @@ template <int G, int S, typename V, typename VB, int Mode>
 __global__ void __launch_bounds__(kBlock)
 k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, const int *__restrict__ ci,
            const V *__restrict__ a, const V *__restrict__ dinv, const V *__restrict__ p,
-           const VB *__restrict__ b, V *__restrict__ bc, const double *__restrict__ done, Tiers T) {
+           const VB *__restrict__ b, V *__restrict__ bc, const double *__restrict__ done, Tiers T, StopTest st) {
     // small levels: the solve-ended flag is only tested before the store, so
-    // its load overlaps the row loads instead of preceding them
+    // its load overlaps the row loads instead of preceding them.  st (finest
+    // level): the stop test of the update before this cycle, by a workgroup of
+    // its own after the others (a level of a few waves would wait for it in a
+    // workgroup that also holds rows)
     constexpr bool Tier = Mode == kLegTiers;
     LongView<V> lv;
     int blk = blockIdx.x, nb = gridDim.x;
+    if (st.part) {
+        if (blk == nb - 1) {
+            (void)stop_test(st.part, st.scal, st.nb);
+            return;
+        }
+        --nb;
+    }
     if (Tier) {
         if (blk < T.nch) {
             if (done && *done != 0.0) return;
@@ -1405,16 +1415,16 @@ Tiers tiers_of(const Level &L, bool aggregates) {
 
 template <int G, typename V, typename VB>
 void down_dispatch(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p, const VB *b, V *bc,
-                   const double *done) {
+                   const double *done, StopTest st) {
     const int S = L.mstride;
     dim3 grid(blocks_for((long long)L.nc * G));
     auto seq = [&](auto sc) {
         constexpr int SS = decltype(sc)::value;
         const Tiers T = tiers_of(L, true);
-        grid.x += T.off;
+        grid.x += T.off + (st.part ? 1 : 0);
         auto go = [&](auto mc) {
             launch_k((k_down_seq<G, SS, V, VB, decltype(mc)::value>), grid, dim3(kBlock), s, L.nc, L.mem, L.A.rp,
-                     L.A.ci, a, dinv, p, b, bc, done, T);
+                     L.A.ci, a, dinv, p, b, bc, done, T, st);
         };
         const int mode = leg_mode(L, T);
         if (mode == kLegTiers) go(std::integral_constant<int, kLegTiers>{});
@@ -1481,7 +1491,7 @@ void down_t(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p
     if (part == 2) return;
     with_G(L.G, [&](auto gc) {
         constexpr int g = decltype(gc)::value;
-        down_dispatch<g, V, VB>(s, L, a, dinv, p, b, bc, done);
+        down_dispatch<g, V, VB>(s, L, a, dinv, p, b, bc, done, st);
     });
 }
 
