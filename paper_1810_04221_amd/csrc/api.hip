@@ -1418,11 +1418,19 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
                     launch_fold_w(s, C, Tc, M, W, P.check != 0);
                     Tc = W;
                 }
-                double *T = k == kf ? h->persist.get_n<double>(nn2) : tmp.get_n<double>(nn2);
+                double *T = k == kf && !wcyc ? h->persist.get_n<double>(nn2) : tmp.get_n<double>(nn2);
                 double *H = tmp.get_n<double>(nn2);
                 NOMEM(T && H);
                 launch_fold_level(s, L, Tc, C.A.n, H, T);
                 Tc = T;
+            }
+            if (wcyc) {
+                // only level kf - 1 applies the map, twice per visit: W = 2T - T A T at once
+                const size_t nn2 = (size_t)h->lv[kf].A.n * h->lv[kf].A.n;
+                double *M = tmp.get_n<double>(nn2), *W = h->persist.get_n<double>(nn2);
+                NOMEM(M && W);
+                launch_fold_w(s, h->lv[kf], Tc, M, W, P.check != 0);
+                Tc = W;
             }
             h->kf = kf;
             h->fold = const_cast<double *>(Tc);
@@ -1655,7 +1663,7 @@ double bytes_cycle(const bcm_handle *h) {
         if (kcycle_at(h, k)) {
             total += visits * (2 * (spmv + 3 * sv * n) + 6 * sv * n);
             visits *= 2;
-        } else if (h->prm.cycle == BCM_WCYCLE) {
+        } else if (h->prm.cycle == BCM_WCYCLE && k + 1 != h->kf) {
             total += visits * (spmv + 6 * sv * n);
             visits *= 2;
         }
@@ -1796,7 +1804,8 @@ void prof_collect(bcm_handle *h, int iters) {
 // coarse residual and written to the level's save buffer (W); or two
 // flexible-CG iterations preconditioned by the coarse cycle (K, on levels
 // k < kcycle_levels).
-void cycle_level(bcm_handle *h, Prof &pf, int k, const double *done, int iter);
+// add: a vector of the level's type added to the cycle's result (or null).
+void cycle_level(bcm_handle *h, Prof &pf, int k, const double *done, int iter, const void *add = nullptr);
 
 void coarse_solve(bcm_handle *h, Prof &pf, int k, const double *done, int iter) {
     hipStream_t s = h->s;
@@ -1810,16 +1819,14 @@ void coarse_solve(bcm_handle *h, Prof &pf, int k, const double *done, int iter) 
         cycle_level(h, pf, k + 1, done, iter);
         std::swap(C.x, C.xs);
         launch_kcycle_step2(s, C, fp32, C.xs, C.b, C.kv, C.x, h->kpart, ks, done);
-    } else if (h->prm.cycle == BCM_WCYCLE) {
+    } else if (h->prm.cycle == BCM_WCYCLE && k + 1 != h->kf) {  // (at kf both cycles are one operator)
         launch_resid_inplace(s, C, fp32, C.x, C.b, done);
         std::swap(C.x, C.xs);
-        cycle_level(h, pf, k + 1, done, iter);
-        std::swap(C.x, C.xs);
-        launch_add(s, C.A.n, fp32, C.xs, C.x, done);
+        cycle_level(h, pf, k + 1, done, iter, C.xs);
     }
 }
 
-void cycle_level(bcm_handle *h, Prof &pf, int k, const double *done, int iter) {
+void cycle_level(bcm_handle *h, Prof &pf, int k, const double *done, int iter, const void *add) {
     hipStream_t s = h->s;
     const int fp32 = h->prm.precision == BCM_FP32_CYCLE;
     Level &L = h->lv[k];
@@ -1827,26 +1834,26 @@ void cycle_level(bcm_handle *h, Prof &pf, int k, const double *done, int iter) {
         int e = pf.begin(5);
         launch_dense(s, L.A.n, h->fold, L.b, L.x, !fp32, !fp32, done);
         pf.end(5, e, bytes_fold(h), iter);
-        return;
-    }
-    if (k == h->kt) {  // this level and every coarser one in one workgroup
+    } else if (k == h->kt) {  // this level and every coarser one in one workgroup
         int e = pf.begin(5);
         launch_tail(s, fp32, k, h->nl, h->tail, h->lv[h->nl - 1], h->prm.coarse_sweeps, h->tail_ops, h->n_tail_ops,
                     L.x, done);
         pf.end(5, e, 0.0, iter);
-        return;
-    }
-    if (k == h->nl - 1) {
+    } else if (k == h->nl - 1) {
         int e = pf.begin(5);
         launch_coarse(s, L, h->prm.coarse_sweeps, L.b, L.x, !fp32, !fp32, h->ctmp[0], h->ctmp[1], done);
         pf.end(5, e, bytes_coarse(h), iter);
-        return;
+    } else {
+        Level &C = h->lv[k + 1];
+        const int f64io = !fp32;
+        launch_down(s, L, fp32, L.b, C.b, f64io, done);
+        // (x of this level: taken after the coarse solve, whose own levels swap theirs only)
+        coarse_solve(h, pf, k, done, iter);
+        const bool fused = add && !L.xp;  // the fused up leg adds it itself
+        launch_up(s, L, fp32, L.b, C.x, L.x, f64io, f64io, done, 0, fused ? add : nullptr);
+        if (fused) return;
     }
-    Level &C = h->lv[k + 1];
-    const int f64io = !fp32;
-    launch_down(s, L, fp32, L.b, C.b, f64io, done);
-    coarse_solve(h, pf, k, done, iter);
-    launch_up(s, L, fp32, L.b, C.x, L.x, f64io, f64io, done);
+    if (add) launch_add(s, L.A.n, fp32, add, L.x, done);
 }
 
 // --------------------------------------------------------------- V-cycle
@@ -1993,8 +2000,6 @@ int capture_iteration(bcm_handle *h, int prof_cls) {
     if (h->n_exec > 0 && h->graph_prof_cls == prof_cls) return BCM_OK;
     destroy_iteration_graphs(h);
     if (!h->cap) HIPCHK(hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking));
-    const Level &L0 = h->lv[0];
-    const int n = L0.A.n, nb = h->red_blocks;
     SegCapture sc;
     sc.st = h->cap;
     Prof gp{h, 0, prof_cls, &sc};

@@ -521,14 +521,17 @@ template <int G, int R, typename V, typename VB, typename VX, int Mode>
 __global__ void __launch_bounds__(kBlock)
 k_up(int n, const int *__restrict__ rp, const int *__restrict__ ci, const V *__restrict__ a,
      const V *__restrict__ dinv, const V *__restrict__ p, const int *__restrict__ agg,
-     const VB *__restrict__ b, const V *__restrict__ xc, VX *__restrict__ x, const double *__restrict__ done, Tiers T) {
+     const VB *__restrict__ b, const V *__restrict__ xc, VX *x, const VX *add, const double *__restrict__ done,
+     Tiers T) {
+    // add (or null): added to the result, the W-cycle's first coarse result
     constexpr bool Tier = Mode == kLegTiers;
     const FProlonged<V, VB> f{dinv, p, agg, b, xc};
     auto put = [&](int i, V s) {
         const V bi = (V)b[i];
         const V di = dinv[i];
         const V xi = di * bi + p[i] * xc[agg[i]];
-        x[i] = (VX)(xi + di * (bi - s));
+        const VX v = (VX)(xi + di * (bi - s));
+        x[i] = add ? v + add[i] : v;
     };
     LongView<V> lv;
     int blk = blockIdx.x, nb = gridDim.x;
@@ -1497,7 +1500,7 @@ void down_t(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p
 
 template <typename V, typename VB, typename VX>
 void up_t(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p, const VB *b, const V *xc,
-          VX *x, const double *done, int part) {
+          VX *x, const double *done, int part, const VX *add) {
     if (L.xp) {
         V *xp = (V *)L.xp;
         if (part != 2)
@@ -1538,7 +1541,7 @@ void up_t(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p, 
         grid.x += T.off;
         auto go = [&](auto mc) {
             launch_k((k_up<g, R, V, VB, VX, decltype(mc)::value>), grid, dim3(kBlock), s, L.A.n, L.A.rp, L.A.ci, a,
-                     dinv, p, L.agg, b, xc, x, done, T);
+                     dinv, p, L.agg, b, xc, x, add, done, T);
         };
         const int mode = leg_mode(L, T);
         if (mode == kLegTiers) go(std::integral_constant<int, kLegTiers>{});
@@ -1615,16 +1618,16 @@ void launch_down(hipStream_t s, const Level &L, int fp32, const void *b, void *b
 }
 
 void launch_up(hipStream_t s, const Level &L, int fp32, const void *b, const void *xc, void *x, int b_is_f64,
-               int x_is_f64, const double *done, int part) {
+               int x_is_f64, const double *done, int part, const void *add) {
     if (!fp32) {
         up_t<double, double, double>(s, L, L.A.v, L.dinv, L.p, (const double *)b, (const double *)xc, (double *)x,
-                                     done, part);
+                                     done, part, (const double *)add);
     } else if (b_is_f64 && x_is_f64) {
         up_t<float, double, double>(s, L, L.A.v32, L.dinv32, L.p32, (const double *)b, (const float *)xc,
-                                    (double *)x, done, part);
+                                    (double *)x, done, part, (const double *)add);
     } else {
         up_t<float, float, float>(s, L, L.A.v32, L.dinv32, L.p32, (const float *)b, (const float *)xc, (float *)x,
-                                  done, part);
+                                  done, part, (const float *)add);
     }
 }
 
