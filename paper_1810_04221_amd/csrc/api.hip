@@ -1386,7 +1386,9 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
     // is applied as it is once its two passes cost less than the dense product
     // (2 M n against n^2 entries; beyond 1024 rows with the default sweeps).
     const int kb = chain ? ks : h->nl - 1;
-    bool fold = P.fold && kb >= 2 && (chain ? h->lv[ks].A.n <= kFoldRows : h->lv[kb].S != nullptr);
+    // (W-cycle: the coarsest level alone is worth it, its parent applies it twice)
+    const bool wcyc = P.cycle == BCM_WCYCLE;
+    bool fold = P.fold && kb >= (wcyc ? 1 : 2) && (chain ? h->lv[ks].A.n <= kFoldRows : h->lv[kb].S != nullptr);
     if (fold && chain && h->lv[ks - 1].A.n > kFoldRows && h->lv[ks].A.n > 1024) fold = false;
     if (chain && !fold) h->kc = ks;
     if (fold) {
@@ -1396,9 +1398,8 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
         // Krylov coarse solves all sit above that level.
         int kf = kb;
         while (kf > 1 && h->lv[kf - 1].A.n <= kFoldRows) --kf;
-        const bool wcyc = P.cycle == BCM_WCYCLE;
         const bool linear = P.cycle != BCM_KCYCLE || (P.kcycle_levels > 0 && P.kcycle_levels <= kf);
-        if (kf < h->nl - 1 && linear) {
+        if ((kf < h->nl - 1 || wcyc) && linear) {
             const double *Tc = h->lv[h->nl - 1].S;
             if (chain) {
                 const size_t nn2 = (size_t)h->lv[ks].A.n * h->lv[ks].A.n;
