@@ -1294,8 +1294,9 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             uni[t] = h->persist.get_n<int>(ns);
             void *stmp = keep.get(scan_tmp_bytes(ns));
             NOMEM(L.E.sp && uni[t] && stmp);
-            launch_sell_width(s, L.A.n, L.A.rp, L.A.ci, L.A.v, L.E.sp, uni[t], tot + 32 + t, tot + 64 + t,
-                              tot + 96 + t);
+            // (several unknowns per node: only the given matrix keeps a node's rows together)
+            launch_sell_width(s, L.A.n, L.A.rp, L.A.ci, L.A.v, lv_sell[t] == 0 && L.A.nnz >= (long long)kGatherRow * L.A.n ? 3 : 1,
+                              L.E.sp, uni[t], tot + 32 + t, tot + 64 + t, tot + 96 + t);
             scan_exclusive(s, L.E.sp, L.E.sp, ns, L.E.sp + ns, stmp);  // sp[ns] = total slots
             HIPCHK(hipMemcpyAsync(tot + t, L.E.sp + ns, sizeof(int), hipMemcpyDeviceToDevice, s));
         }

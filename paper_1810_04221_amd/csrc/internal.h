@@ -180,8 +180,9 @@ struct Sell {
     int nslices = 0;
     int *sp = nullptr, *sc = nullptr;
     short *sd = nullptr;
-    // int16 copies only: uni[s] = 1 when the rows of slice s share one list of
-    // column offsets, held in su from index sp[s] / 64 (one per slot column)
+    // int16 copies only: uni[s] = B > 0 when the rows of slice s share one list of
+    // column offsets from the first row of their block of B (1, 2 or 3 unknowns per
+    // node), held in su from index sp[s] / 64 (one per slot column)
     int *uni = nullptr;
     int *su = nullptr;
     double *sv = nullptr;
@@ -465,11 +466,14 @@ void launch_compose(hipStream_t s, int n, int nc_new, const int *agg_prev, const
 void launch_diag_l1(hipStream_t s, int G, int n, const int *rp, const double *v, double *dinv,
                     float *dinv32, float *v32, const LongRows &lr = LongRows(), const double *part = nullptr);
 void launch_cast(hipStream_t s, size_t n, const double *src, float *dst);
+// widest slice whose rows may share one list of column offsets
+constexpr int kUniWidth = 128;
 // slice widths (64 * longest row of each slice) -> cnt[nslices]; *maxoff is
 // raised to the largest |col - row| of the matrix, *inexact to 1 if a value is
 // not exactly a float32 (start both at 0)
-void launch_sell_width(hipStream_t s, int n, const int *rp, const int *ci, const double *v, int *cnt, int *uni,
-                       int *maxoff, int *inexact, int *mixed);
+// (blocks: the largest block size of rows tried for shared offsets, 1 to 3)
+void launch_sell_width(hipStream_t s, int n, const int *rp, const int *ci, const double *v, int blocks, int *cnt,
+                       int *uni, int *maxoff, int *inexact, int *mixed);
 // fills the slots: int32 columns into sc, or int16 offsets into sd (one is null)
 void launch_sell_fill(hipStream_t s, int n, const int *rp, const int *ci, const double *v, const int *sp,
                       const int *uni, int *su, int *sc, short *sd, double *sv, float *sv32);

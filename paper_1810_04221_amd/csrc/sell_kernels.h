@@ -8,6 +8,9 @@
 #include "device.h"
 #include "internal.h"
 
+// First row of row i's block of B rows (the base of a uniform slice's offsets).
+__device__ __forceinline__ int block_row(int i, int B) { return B == 1 ? i : i - i % B; }
+
 // Column of a sliced-ELL slot: int32 columns, or int16 offsets col - row.
 __device__ __forceinline__ int sell_col(int c, int) { return c; }
 __device__ __forceinline__ int sell_col(short d, int i) { return i + (int)d; }
@@ -20,7 +23,9 @@ __device__ __forceinline__ int sell_col(short d, int i) { return i + (int)d; }
 // are loaded non-temporally (streamed past the L2, which then keeps more of
 // the gathered vector).
 template <int kB, bool Uni, typename V, typename S, typename I, typename F, bool NT = false>
-__device__ __forceinline__ V sell_slots(const S *a, const int *u, const I *c, int n, int i, int w, V s, F f) {
+__device__ __forceinline__ V sell_slots(const S *a, const int *u, const I *c, int n, int i, int ib, int w, V s,
+                                        F f) {
+    // ib: the row that the shared offsets start from
     for (int k0 = 0; k0 < w; k0 += kB) {
         S av[kB];
         V fv[kB];
@@ -30,7 +35,7 @@ __device__ __forceinline__ V sell_slots(const S *a, const int *u, const I *c, in
             if (NT) av[t] = __builtin_nontemporal_load(&a[k * kSlice]);
             else av[t] = a[k * kSlice];
             if (Uni) {
-                const int cc = i + u[k];
+                const int cc = ib + u[k];
                 fv[t] = f((unsigned)cc < (unsigned)n ? cc : i);
             } else {
                 fv[t] = f(sell_col(c[k * kSlice], i));
@@ -49,8 +54,8 @@ __device__ __forceinline__ V sell_slots(const S *a, const int *u, const I *c, in
 // (64 x 2, 4 or 8 B); the caller's waves are aligned to slices.  Values are
 // stored as S and multiplied as V (S = float under V = double only when every
 // value of the level is exactly a float: the conversion is exact).
-// A uniform slice (uni[s] = 1: every row's offsets are a subsequence of one
-// list) reads its column offsets from that list (su, from sp[s] / 64), one per
+// A uniform slice (uni[s] = B > 0: every row's offsets, counted from the first row
+// of its block of B, are a subsequence of one list) reads its column offsets from that list (su, from sp[s] / 64), one per
 // slot for the whole wave, instead of one per entry; a slot a row does not
 // have holds the value 0 (its column clamped into the matrix when it would
 // leave it).
@@ -66,8 +71,8 @@ __device__ __forceinline__ V sell_row(int n, const int *__restrict__ sp, const i
     const S *a = sv + beg + lane;
     const int *u = su + beg / kSlice;
     const I *c = sc + beg + lane;
-    if (uf) return sell_slots<kB, true, V, S, I, F, NT>(a, u, c, n, i, w, V(0), f);
-    return sell_slots<kB, false, V, S, I, F, NT>(a, u, c, n, i, w, V(0), f);
+    if (uf) return sell_slots<kB, true, V, S, I, F, NT>(a, u, c, n, i, block_row(i, uf), w, V(0), f);
+    return sell_slots<kB, false, V, S, I, F, NT>(a, u, c, n, i, i, w, V(0), f);
 }
 
 

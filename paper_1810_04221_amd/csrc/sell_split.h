@@ -18,7 +18,8 @@
 constexpr int kParts = kBlock / kSlice;
 
 template <int kB, bool Uni, typename V, typename S, typename I, typename F, bool NT = false>
-__device__ __forceinline__ V sell_part(const S *a, const int *u, const I *c, int n, int i, int w, int q, F f) {
+__device__ __forceinline__ V sell_part(const S *a, const int *u, const I *c, int n, int i, int ib, int w, int q,
+                                       F f) {
     V s = V(0);
     for (int k0 = q; k0 < w; k0 += kB * kParts) {
         S av[kB];
@@ -29,7 +30,7 @@ __device__ __forceinline__ V sell_part(const S *a, const int *u, const I *c, int
             if (NT) av[t] = __builtin_nontemporal_load(&a[k * kSlice]);
             else av[t] = a[k * kSlice];
             if (Uni) {
-                const int cc = i + u[k];
+                const int cc = ib + u[k];
                 fv[t] = f((unsigned)cc < (unsigned)n ? cc : i);
             } else {
                 fv[t] = f(sell_col(c[k * kSlice], i));
@@ -47,14 +48,16 @@ template <typename V, typename S, typename I, int kB, typename F, bool NT = fals
 __device__ __forceinline__ V sell_row_part(int n, const int *__restrict__ sp, const int *__restrict__ uni,
                                            const int *__restrict__ su, const I *__restrict__ sc,
                                            const S *__restrict__ sv, int sl, F f) {
-    const int q = threadIdx.x / kSlice, lane = threadIdx.x % kSlice, i = sl * kSlice + lane;
+    // (q is the wave's: the shared offsets are then scalar loads)
+    const int q = __builtin_amdgcn_readfirstlane(threadIdx.x / kSlice), lane = threadIdx.x % kSlice,
+              i = sl * kSlice + lane;
     if (i >= n) return V(0);
     const int uf = uni[sl], beg = sp[sl], w = (sp[sl + 1] - beg) / kSlice;
     const S *a = sv + beg + lane;
     const int *u = su + beg / kSlice;
     const I *c = sc + beg + lane;
-    if (uf) return sell_part<kB, true, V, S, I, F, NT>(a, u, c, n, i, w, q, f);
-    return sell_part<kB, false, V, S, I, F, NT>(a, u, c, n, i, w, q, f);
+    if (uf) return sell_part<kB, true, V, S, I, F, NT>(a, u, c, n, i, block_row(i, uf), w, q, f);
+    return sell_part<kB, false, V, S, I, F, NT>(a, u, c, n, i, i, w, q, f);
 }
 
 // The P partial sums of each row of the slice, added in wave order (valid in wave 0).

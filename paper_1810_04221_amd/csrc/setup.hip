@@ -770,21 +770,25 @@ k_diag_l1(int n, const int *__restrict__ rp, const double *__restrict__ v, doubl
 }
 
 // Sliced ELL: width of slice s (times 64) = 64 * max row length over its rows.
-// A slice of width at most 64 is uniform when every row's column offsets
-// (col - row, ascending) are a subsequence of those of its first full-width
-// row, the template: uni[s] = 1; the slots of the slices that are not add up in
-// *mixed.  The template's offsets are staged in LDS and each row's are loaded
-// eight at a time, so the comparison waits on few memory round trips.
+// A slice of width at most kUniWidth is uniform when every row's column offsets
+// (ascending) are a subsequence of those of its first full-width row, the
+// template.  Offsets count from the row itself, or from the first row of its block
+// of B = 2 or 3 rows (matrices of B unknowns per node, whose rows share a node's
+// columns): uni[s] = B for the smallest that fits; the slots of the slices that
+// fit none add up in *mixed.  The template's offsets are staged in LDS and each
+// row's are loaded eight at a time, so the comparison waits on few memory round
+// trips.
+__device__ __forceinline__ int block_first(int i, int B) { return B == 1 ? i : i - i % B; }
 __global__ void __launch_bounds__(kBlock)
 k_sell_width(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ v,
-             int *__restrict__ cnt, int *__restrict__ uni, int *__restrict__ maxoff, int *__restrict__ inexact,
+             int blocks, int *__restrict__ cnt, int *__restrict__ uni, int *__restrict__ maxoff, int *__restrict__ inexact,
              int *__restrict__ mixed) {
     // one wave per slice (lane l on row 64 s + l), waves striding over slices;
     // the largest offset is reduced per block, then one atomic per block
     static_assert(kBlock % kSlice == 0, "a block must hold whole slices");
     constexpr int kWaves = kBlock / kSlice;
     __shared__ int red[kWaves], redx[kWaves], redm[kWaves];
-    __shared__ int tmpl[kWaves][kSlice];
+    __shared__ int tmpl[kWaves][kUniWidth];
     const int ns = (n + kSlice - 1) / kSlice;
     const int lane = threadIdx.x % kSlice, wv = threadIdx.x / kSlice;
     int off = 0, inx = 0, mix = 0;
@@ -803,30 +807,34 @@ k_sell_width(int n, const int *__restrict__ rp, const int *__restrict__ ci, cons
         const int t = __ffsll((unsigned long long)__ballot(len == w)) - 1;
         const int it = sl * kSlice + t, qt = rp[it];
         int *T = tmpl[wv];
-        if (lane < w) T[lane] = ci[qt + lane] - it;
-        wave_sync();
-        int ok = w <= kSlice ? 1 : 0;
-        if (i < n && ok) {
-            // merge walk: each offset of this row must appear in the template, in order
-            int k = 0;
-            for (int j0 = 0; j0 < len && ok; j0 += 8) {
-                int o[8];
+        int u = 0;
+        for (int B = 1; B <= blocks && !u && w <= kUniWidth; ++B) {
+            const int tb = block_first(it, B), ib = block_first(i, B);
+            for (int k = lane; k < w; k += kSlice) T[k] = ci[qt + k] - tb;
+            wave_sync();
+            int ok = 1;
+            if (i < n) {
+                // merge walk: each offset of this row must appear in the template, in order
+                int k = 0;
+                for (int j0 = 0; j0 < len && ok; j0 += 8) {
+                    int o[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) o[u] = j0 + u < len ? ci[q0 + j0 + u] - i : 0;
+                    for (int t8 = 0; t8 < 8; ++t8) o[t8] = j0 + t8 < len ? ci[q0 + j0 + t8] - ib : 0;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    if (j0 + u >= len || !ok) continue;
-                    while (k < w && T[k] != o[u]) ++k;
-                    if (k == w) ok = 0;
-                    ++k;
+                    for (int t8 = 0; t8 < 8; ++t8) {
+                        if (j0 + t8 >= len || !ok) continue;
+                        while (k < w && T[k] != o[t8]) ++k;
+                        if (k == w) ok = 0;
+                        ++k;
+                    }
                 }
             }
+            wave_sync();  // the template slots are rewritten by the next block size or slice
+            if (__ballot(!ok) == 0) u = B;
         }
-        wave_sync();  // the template slots are rewritten by this wave's next slice
-        const bool u = __ballot(!ok) == 0;
         if (lane == 0) {
             cnt[sl] = w * kSlice;
-            uni[sl] = u ? 1 : 0;
+            uni[sl] = u;
             if (!u) mix += w * kSlice;
         }
     }
@@ -869,15 +877,16 @@ k_sell_fill(int n, const int *__restrict__ rp, const int *__restrict__ ci, const
         if (i >= n) return;
         const int q0 = rp[i], len = rp[i + 1] - q0;
         // the slice's template: its first row of full width (rows past n are
-        // inactive); uniform slices have w <= 64
-        __shared__ int tmpl[kBlock / kSlice][kSlice];
+        // inactive); uniform slices have w <= kUniWidth
+        __shared__ int tmpl[kBlock / kSlice][kUniWidth];
+        const int B = uni[sl], ib = block_first(i, B);
         const int t = __ffsll((unsigned long long)__ballot(len == w)) - 1;
         const int it = sl * kSlice + t, qt = rp[it];
         int *T = tmpl[(threadIdx.x % kBlock) / kSlice];
         if (lane == t) {  // the template row is always active; the slice's last rows may not be
             int *u = su + sp[sl] / kSlice;
             for (int k = 0; k < w; ++k) {
-                const int o = ci[qt + k] - it;
+                const int o = ci[qt + k] - block_first(it, B);
                 u[k] = o;
                 T[k] = o;
             }
@@ -897,8 +906,8 @@ k_sell_fill(int n, const int *__restrict__ rp, const int *__restrict__ ci, const
                 if (j0 + u >= len) continue;
                 // slots before this entry's offset hold zeros (the offset is in
                 // the template: the slice was checked uniform with the same one)
-                for (; k < w && T[k] != c[u] - i; ++k) {
-                    int col = i + T[k];
+                for (; k < w && T[k] != c[u] - ib; ++k) {
+                    int col = ib + T[k];
                     if ((unsigned)col >= (unsigned)n) col = i;
                     put(k, col, 0.0);
                 }
@@ -906,7 +915,7 @@ k_sell_fill(int n, const int *__restrict__ rp, const int *__restrict__ ci, const
             }
         }
         for (; k < w; ++k) {
-            int col = i + T[k];
+            int col = ib + T[k];
             if ((unsigned)col >= (unsigned)n) col = i;
             put(k, col, 0.0);
         }
@@ -1836,11 +1845,12 @@ void launch_diag_l1(hipStream_t s, int G, int n, const int *rp, const double *v,
     });
 }
 
-void launch_sell_width(hipStream_t s, int n, const int *rp, const int *ci, const double *v, int *cnt, int *uni,
-                       int *maxoff, int *inexact, int *mixed) {
+void launch_sell_width(hipStream_t s, int n, const int *rp, const int *ci, const double *v, int blocks, int *cnt,
+                       int *uni, int *maxoff, int *inexact, int *mixed) {
     const int ns = (n + kSlice - 1) / kSlice;
     const int nb = std::min(blocks_for((long long)ns * kSlice), 512);
-    hipLaunchKernelGGL(k_sell_width, dim3(nb), dim3(kBlock), 0, s, n, rp, ci, v, cnt, uni, maxoff, inexact, mixed);
+    hipLaunchKernelGGL(k_sell_width, dim3(nb), dim3(kBlock), 0, s, n, rp, ci, v, blocks, cnt, uni, maxoff, inexact,
+                       mixed);
 }
 
 void launch_sell_fill(hipStream_t s, int n, const int *rp, const int *ci, const double *v, const int *sp,

@@ -1898,10 +1898,11 @@ void launch_spmv_dots(hipStream_t s, const Level &L, int nb, const void *w, int 
     else spmv_dots_t(s, L, nb, (const double *)w, r, q, v, partials, scal);
 }
 
-// Up to kSpmvBlocks product partials every update workgroup adds them itself
-// (24 KB of L2-resident loads each) instead of a one-block finalize launch; the
-// one-workgroup-per-slice product's thousands of partials keep that launch.
-bool update_takes_dots(int nbs) { return nbs <= kSpmvBlocks; }
+// Up to 2048 product partials every update workgroup adds them itself (48 KB of
+// L2-resident loads each) instead of a one-block finalize launch (elasticity,
+// 104,544 rows, 1,634 slices: 4.3 us and its gap); the one-workgroup-per-slice
+// product's partials beyond that keep that launch.
+bool update_takes_dots(int nbs) { return nbs <= 2 * kSpmvBlocks; }
 
 void launch_update(hipStream_t s, int n, int nb, int first, const void *w, int w_f32, const double *v, double *d,
                    double *u, double *q, double *r, float *r32, double *partials, double *scal, const void *dinv,
