@@ -1325,17 +1325,19 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             NOMEM((L.E.sc || L.E.sd) && (L.E.sv || L.E.sv32));
             launch_sell_fill(s, L.A.n, L.A.rp, L.A.ci, L.A.v, L.E.sp, uni[t], L.E.su, L.E.sc, L.E.sd, L.E.sv,
                              L.E.sv32);
-            // FP32 cycle, levels whose down leg is the sliced-ELL residual with
-            // one thread per row: the values of A D for it (the long-row levels
-            // gather dinv o b instead, the slot-split ones keep dinv and b).
+            // Levels whose down leg is the sliced-ELL residual with one thread per
+            // row: the values of A D for it (the long-row levels gather dinv o b
+            // instead, the slot-split ones keep dinv and b; an FP64 cycle on values
+            // that are exact float32 reads 4 bytes instead of the product's 8).
             // Below 2^19 rows the residual runs near its latency either way
             // (250k rows: 4.6 against 4.7 us a launch, less over a solve than
-            // the scaling costs the setup), so only larger levels take it.
-            if (fp32 && down_on_sell(L) && !L.yb && !slot_split_level(L) && (lv_sell[t] == 0 || L.A.n >= (1 << 19))) {
-                L.E.svd = h->persist.get_n<float>(ne);
+            // the scaling costs the setup), so only larger levels and the FP32
+            // cycle's finest take it.
+            if (down_on_sell(L) && !L.yb && !slot_split_level(L) && (fp32 || L.E.sv) &&
+                ((fp32 && lv_sell[t] == 0) || L.A.n >= (1 << 19))) {
+                L.E.svd = h->persist.get((fp32 ? sizeof(float) : sizeof(double)) * ne);
                 NOMEM(L.E.svd);
-                launch_sell_scale_cols(s, L.A.n, L.E.nslices, L.E.sp, L.E.uni, L.E.su, L.E.sc, L.E.sd, L.E.sv32,
-                                       L.dinv32, L.E.svd);
+                launch_sell_scale_cols(s, L.A.n, L.E, fp32, fp32 ? (const void *)L.dinv32 : (const void *)L.dinv);
             }
         }
         // the values one solve iteration reads: both legs of every sliced-ELL

@@ -76,23 +76,23 @@ __device__ __forceinline__ V sell_row(int n, const int *__restrict__ sp, const i
 }
 
 
-// FP32 cycle, finest level: the same residual with the values of A D (each
-// slot's value times its column's inverse l1 diagonal, formed at setup), so
-// each term gathers one vector:  pr_i = p_i (b_i - sum_j (a_ij dinv_j) b_j).
-template <typename VB, typename I, int kB, bool NT>
+// The same residual with the values of A D (each slot's value times its column's
+// inverse l1 diagonal, formed at setup, in the cycle's type), so each term
+// gathers one vector:  pr_i = p_i (b_i - sum_j (a_ij dinv_j) b_j).
+template <typename V, typename VB, typename I, int kB, bool NT>
 __global__ void __launch_bounds__(kBlock)
 k_down_res_sell_ad(int n, const int *__restrict__ sp, const int *__restrict__ uni, const int *__restrict__ su,
-                   const I *__restrict__ sc, const float *__restrict__ svd, const float *__restrict__ p,
-                   const VB *__restrict__ b, float *__restrict__ pr, const double *__restrict__ done,
+                   const I *__restrict__ sc, const V *__restrict__ svd, const V *__restrict__ p,
+                   const VB *__restrict__ b, V *__restrict__ pr, const double *__restrict__ done,
                    StopTest st) {
     if (st.part && blockIdx.x == 0) {
         if (stop_test(st.part, st.scal, st.nb)) return;
     } else if (done && *done != 0.0) return;
     const int i = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     if (i >= n) return;
-    const float pi = p[i], bi = (float)b[i];  // loaded first, to overlap the product's loads
-    auto g = [&](int j) { return (float)b[j]; };
-    const float s = sell_row<float, float, I, kB, decltype(g), NT>(n, sp, uni, su, sc, svd, i, g);
+    const V pi = p[i], bi = (V)b[i];  // loaded first, to overlap the product's loads
+    auto g = [&](int j) { return (V)b[j]; };
+    const V s = sell_row<V, V, I, kB, decltype(g), NT>(n, sp, uni, su, sc, svd, i, g);
     pr[i] = pi * (bi - s);
 }
 

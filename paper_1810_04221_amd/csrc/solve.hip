@@ -1470,10 +1470,9 @@ void down_t(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p
                     if (split_slots(L, B))
                         launch_k((k_down_res_sell_p<V, VB, I, S, 8, NT>), dim3(L.E.nslices), dim3(kBlock), s, L.A.n,
                                  L.E.sp, L.E.uni, L.E.su, ix, vals, dinv, p, b, pr, (const V *)y, done, st);
-                    else if (std::is_same<V, float>::value && L.E.svd && !y)  // values of A D: one gather per term
-                        launch_k((k_down_res_sell_ad<VB, I, B, NT>), dim3(blocks_for(L.A.n)), dim3(kBlock), s, L.A.n,
-                                 L.E.sp, L.E.uni, L.E.su, ix, (const float *)L.E.svd, (const float *)p, b, (float *)pr,
-                                 done, st);
+                    else if (L.E.svd && !y)  // values of A D: one gather per term
+                        launch_k((k_down_res_sell_ad<V, VB, I, B, NT>), dim3(blocks_for(L.A.n)), dim3(kBlock), s, L.A.n,
+                                 L.E.sp, L.E.uni, L.E.su, ix, (const V *)L.E.svd, p, b, pr, done, st);
                     else
                         launch_k((k_down_res_sell<V, VB, I, S, B, NT>), dim3(blocks_for(L.A.n)), dim3(kBlock), s,
                                  L.A.n, L.E.sp, L.E.uni, L.E.su, ix, vals, dinv, p, b, pr, (const V *)y, done, st);
