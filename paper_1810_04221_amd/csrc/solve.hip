@@ -1167,11 +1167,11 @@ k_tail(int kt, int nl, const TailLevel *__restrict__ tl, const double *__restric
 }
 
 // One l1-Jacobi sweep of a coarsest level too large for one workgroup's LDS:
-// xn = xo + D (b - A xo) (first: xo = 0, so xn = D b).  G lanes per row and R
-// rows per group, as in the cycle kernels.  The last sweep of a solve writes
+// xn = xo + D (b - A xo) (first: xo = 0, so xn = D b).  G lanes per row (one row:
+// a cycle ending in 20 sweeps of 31,688 rows took 281 us with two, 272 with one).  The last sweep of a solve writes
 // the caller's x (type VX) instead of xn.  The solve-ended flag is tested
 // before the stores only (as in k_down_seq).
-template <int G, int R, typename VB, typename VX, bool Tier>
+template <int G, typename VB, typename VX, bool Tier>
 __global__ void __launch_bounds__(kBlock)
 k_jacobi_sweep(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
                const double *__restrict__ dinv, const VB *__restrict__ b, const double *__restrict__ xo,
@@ -1204,22 +1204,12 @@ k_jacobi_sweep(int n, const int *__restrict__ rp, const int *__restrict__ ci, co
         lv.lmin = T.tm;
     }
     const int lane = threadIdx.x % G;
-    const int g = (xcd_block(blk, nb) * kBlock + threadIdx.x) / G;
-    int rows[R];
-#pragma unroll
-    for (int k = 0; k < R; ++k) rows[k] = g * R + k < n ? g * R + k : -1;
-    double s[R];
+    const int i = (xcd_block(blk, nb) * kBlock + threadIdx.x) / G;
+    const int row[1] = {i < n ? i : -1};
+    double s[1] = {0.0};
     int lgm = 0;
-    if (first) {
-#pragma unroll
-        for (int k = 0; k < R; ++k) s[k] = 0.0;
-    } else {
-        rows_dot<G, R, double>(rp, ci, a, rows, s, f, lv, Tier ? &lgm : nullptr);
-    }
-    const bool live = !(done && *done != 0.0);
-#pragma unroll
-    for (int k = 0; k < R; ++k)
-        if (lane == k % G && rows[k] >= 0 && live && !(Tier && ((lgm >> k) & 1))) put(rows[k], s[k]);
+    if (!first) rows_dot<G, 1, double>(rp, ci, a, row, s, f, lv, Tier ? &lgm : nullptr);
+    if (lane == 0 && i < n && !(done && *done != 0.0) && !(Tier && lgm)) put(i, s[0]);
 }
 
 // ----------------------------------------------------------------------------
@@ -1549,6 +1539,11 @@ void up_t(hipStream_t s, const Level &L, const V *a, const V *dinv, const V *p, 
     });
 }
 
+// threads of a full chip: 256 CUs of 2,048.  Coarsest levels of 9 entries a row on
+// average and at most 50 (16 lanes by the rule), one sweep: 81,942 rows 8.5 us with
+// 16 lanes and two rows a group, 7.0 with 4 lanes; 40,455 rows 6.0 us, 5.6 with 8.
+constexpr long long kResident = 256LL * 2048;
+
 template <typename VB, typename VX>
 void coarse_t(hipStream_t s, const Level &L, int sweeps, const VB *b, VX *x, double *ta, double *tb,
               const double *done) {
@@ -1572,20 +1567,23 @@ void coarse_t(hipStream_t s, const Level &L, int sweeps, const VB *b, VX *x, dou
         return;
     }
     double *xo = ta, *xn = tb;
-    with_G(L.G, [&](auto gc) {
+    // A sweep lasts as long as its waves' dependent loads: fewer lanes a row where
+    // those of the rule for L.G would not all be resident at once
+    int lanes = L.G;
+    while (lanes > 4 && (long long)n * lanes > kResident) lanes >>= 1;
+    with_G(lanes, [&](auto gc) {
         constexpr int g = decltype(gc)::value;
-        constexpr int R = 2;
         for (int t = 0; t < sweeps; ++t) {
-            dim3 grid(blocks_for(((long long)n + R - 1) / R * g));
+            dim3 grid(blocks_for((long long)n * g));
             // (the first sweep, from zero, has no products)
             const Tiers T = t > 0 ? tiers_of(L, false) : Tiers();
             grid.x += T.off;
             VX *xl = t == sweeps - 1 ? x : (VX *)nullptr;
             if (T.off > 0)
-                hipLaunchKernelGGL((k_jacobi_sweep<g, R, VB, VX, true>), grid, dim3(kBlock), 0, s, n, L.A.rp, L.A.ci,
+                hipLaunchKernelGGL((k_jacobi_sweep<g, VB, VX, true>), grid, dim3(kBlock), 0, s, n, L.A.rp, L.A.ci,
                                    L.A.v, L.dinv, b, xo, xn, xl, 0, done, T);
             else
-                hipLaunchKernelGGL((k_jacobi_sweep<g, R, VB, VX, false>), grid, dim3(kBlock), 0, s, n, L.A.rp, L.A.ci,
+                hipLaunchKernelGGL((k_jacobi_sweep<g, VB, VX, false>), grid, dim3(kBlock), 0, s, n, L.A.rp, L.A.ci,
                                    L.A.v, L.dinv, b, xo, xn, xl, t == 0 ? 1 : 0, done, T);
             double *tmp = xo; xo = xn; xn = tmp;
         }
