@@ -113,7 +113,8 @@ __device__ __forceinline__ bool stop_norm(double rr, double *scal) {
     return end;
 }
 
-// The stop test taken by workgroup 0 of the first kernel of a cycle (all its
+// The stop test taken by one workgroup of the first kernel of a cycle (workgroup 0
+// of the sliced-ELL residual, an extra last one of the fused down leg; all its
 // threads call it, before any returns): when the update left partials not yet
 // taken (scal[7] != 0), adds its nb partials in the order of the one-block
 // finalize with kBlock threads and applies stop_norm.  True when the loop has

@@ -96,8 +96,8 @@ struct LongRows {
     int nchunks = 0;  // chunks over them
     const int *rows = nullptr, *cb = nullptr, *idx = nullptr;
     void *part = nullptr;  // nchunks partial sums (cycle precision; float64 for the flexible-CG kernels)
-    // Row-wise cycle legs in one launch (chunk blocks after the row blocks):
-    // per long row, an arrival counter of its chunks (zero between launches).
+    // Cycle legs in one launch (chunk blocks before the others): per long row,
+    // an arrival counter of its chunks (zero between launches).
     int *cnt = nullptr;
     const ChunkInfo *chunk = nullptr;  // nchunks (levels on the single-launch legs)
     const AggInfo *agg = nullptr;      // n (aggregates of up to four rows)

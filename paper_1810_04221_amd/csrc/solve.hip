@@ -1168,9 +1168,9 @@ k_tail(int kt, int nl, const TailLevel *__restrict__ tl, const double *__restric
 
 // One l1-Jacobi sweep of a coarsest level too large for one workgroup's LDS:
 // xn = xo + D (b - A xo) (first: xo = 0, so xn = D b).  G lanes per row (one row:
-// a cycle ending in 20 sweeps of 31,688 rows took 281 us with two, 272 with one).  The last sweep of a solve writes
-// the caller's x (type VX) instead of xn.  The solve-ended flag is tested
-// before the stores only (as in k_down_seq).
+// a cycle ending in 20 sweeps of 31,688 rows took 281 us with two, 272 with one).
+// The last sweep of a solve writes the caller's x (type VX) instead of xn.  The
+// solve-ended flag is tested before the stores only (as in k_down_seq).
 template <int G, typename VB, typename VX, bool Tier>
 __global__ void __launch_bounds__(kBlock)
 k_jacobi_sweep(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ a,
