@@ -341,11 +341,16 @@ __device__ __forceinline__ void long_chunk(int c, const LongRows &lr, const int 
 // ----------------------------------------------------------------------------
 // Down-leg chunk c of the long rows: the block that brings the last chunk of an
 // aggregate's long rows writes b_c.  Every block of the aggregate sums its other
-// members' rows itself, one wave each, beside its own chunk.
+// members' rows itself, one wave each, beside its own chunk.  Every block counts
+// its arrival whatever the solve-ended flag says, which is tested before the
+// store only: in a launch that takes the stop test the flag may rise while the
+// chunk blocks run, and a block that left on it would leave its row's counter off
+// zero for every later launch.
 template <int S, typename V, typename VB>
 __device__ __forceinline__ void down_chunk(int c, const LongRows &lr, const int *__restrict__ ci,
                                            const V *__restrict__ a, const V *__restrict__ dinv,
-                                           const V *__restrict__ p, const VB *__restrict__ b, V *__restrict__ bc) {
+                                           const V *__restrict__ p, const VB *__restrict__ b, V *__restrict__ bc,
+                                           const double *__restrict__ done) {
     __shared__ double lds[16];
     __shared__ V ms[S];
     static_assert(S <= kWaves && S <= 4, "one wave per member");
@@ -374,7 +379,7 @@ __device__ __forceinline__ void down_chunk(int c, const LongRows &lr, const int 
         else s = (V)d[0];
         acc += p[A.m[u]] * ((V)b[A.m[u]] - s);
     }
-    if (threadIdx.x == 0) bc[A.E] = acc;
+    if (threadIdx.x == 0 && !(done && *done != 0.0)) bc[A.E] = acc;
 }
 
 // S members (template) of one aggregate, all rows in flight at once; summed
@@ -428,8 +433,9 @@ k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, cons
     }
     if (Tier) {
         if (blk < T.nch) {
-            if (done && *done != 0.0) return;
-            down_chunk<S>(blk, T.lr, ci, a, dinv, p, b, bc);
+            // (the flag rises in a launch with st only: elsewhere all blocks read the same)
+            if (!st.part && done && *done != 0.0) return;
+            down_chunk<S>(blk, T.lr, ci, a, dinv, p, b, bc, done);
             return;
         }
         if (blk < T.off) {
