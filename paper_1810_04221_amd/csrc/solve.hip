@@ -341,11 +341,13 @@ __device__ __forceinline__ void long_chunk(int c, const LongRows &lr, const int 
 // ----------------------------------------------------------------------------
 // Down-leg chunk c of the long rows: the block that brings the last chunk of an
 // aggregate's long rows writes b_c.  Every block of the aggregate sums its other
-// members' rows itself, one wave each, beside its own chunk.  Every block counts
-// its arrival whatever the solve-ended flag says, which is tested before the
-// store only: in a launch that takes the stop test the flag may rise while the
-// chunk blocks run, and a block that left on it would leave its row's counter off
-// zero for every later launch.
+// members' rows itself, one wave each, beside its own chunk.  The solve-ended flag
+// spares a block its loads, never its arrival: in a launch that takes the stop
+// test the flag may rise while the chunk blocks run, and a block that left on it
+// would leave its row's counter off zero for every later launch.  (What is then
+// summed is of no account: nothing reads b_c before the next cycle writes it.
+// A matrix of 2100 full rows, 9 iterations and the launches after the end: solve
+// 1.75 ms with the loads, 1.72 without.)
 template <int S, typename V, typename VB>
 __device__ __forceinline__ void down_chunk(int c, const LongRows &lr, const int *__restrict__ ci,
                                            const V *__restrict__ a, const V *__restrict__ dinv,
@@ -358,10 +360,12 @@ __device__ __forceinline__ void down_chunk(int c, const LongRows &lr, const int 
     const ChunkInfo C = lr.chunk[c];
     const AggInfo A = lr.agg[C.t];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    double d[1] = {chunk_share<V>(C, ci, a, f)};
+    const bool ended = done && *done != 0.0;
+    double d[1] = {0.0};
+    if (!ended) d[0] = chunk_share<V>(C, ci, a, f);
 #pragma unroll
     for (int u = 0; u < S; ++u) {
-        if (u != wv || A.m[u] < 0 || A.lg[u]) continue;
+        if (u != wv || A.m[u] < 0 || A.lg[u] || ended) continue;
         V s = row_rest<64>(ci, a, A.beg[u] + lane, A.end[u], V(0), f);
         s = group_sum<64>(s);
         if (lane == 0) ms[u] = s;
@@ -379,7 +383,7 @@ __device__ __forceinline__ void down_chunk(int c, const LongRows &lr, const int 
         else s = (V)d[0];
         acc += p[A.m[u]] * ((V)b[A.m[u]] - s);
     }
-    if (threadIdx.x == 0 && !(done && *done != 0.0)) bc[A.E] = acc;
+    if (threadIdx.x == 0 && !ended) bc[A.E] = acc;
 }
 
 // S members (template) of one aggregate, all rows in flight at once; summed
@@ -433,8 +437,6 @@ k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, cons
     }
     if (Tier) {
         if (blk < T.nch) {
-            // (the flag rises in a launch with st only: elsewhere all blocks read the same)
-            if (!st.part && done && *done != 0.0) return;
             down_chunk<S>(blk, T.lr, ci, a, dinv, p, b, bc, done);
             return;
         }
