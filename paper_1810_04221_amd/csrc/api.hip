@@ -45,6 +45,7 @@ void *Arena::raw_alloc(size_t bytes) {
     } else if (hipMalloc(&p, bytes) != hipSuccess) {
         p = nullptr;
     }
+    if (!p) (void)hipGetLastError();  // (the caller reports the failure, or does without)
     return p;
 }
 
@@ -79,6 +80,15 @@ void Arena::reserve(size_t bytes) {
     chunks.push_back({p, bytes});
     cur = static_cast<char *>(p);
     left = bytes;
+}
+
+void Arena::back(const Mark &m) {
+    while (chunks.size() > m.chunks) {
+        raw_free(chunks.back().first, chunks.back().second);
+        chunks.pop_back();
+    }
+    cur = m.cur;
+    left = m.left;
 }
 
 void Arena::rewind() {
@@ -693,61 +703,83 @@ int build_coarsest_star(bcm_handle *h, hipStream_t s, Arena &tmp, HostTables &ho
 }
 
 // Powers of the coarsest level's sweep matrix, while they stay sparse enough
-// (PowerOp); the sweeps must be a multiple of the power.
+// (PowerOp); the sweeps must be a multiple of the power.  Whether the square is
+// taken is settled, as far as its products tell, on the level's own matrix before
+// anything is allocated; what is allocated and then not taken is given back, and
+// so is all of it when it cannot be had (the sweeps need none of it).
 int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
     Level &L = h->lv[h->nl - 1];
     const int n = L.A.n, sweeps = h->prm.coarse_sweeps;
     if (sweeps % 2 || L.lr.n > 0 || L.A.dmax > power_row_limit() || n > (1 << 17)) return BCM_OK;
+    if ((long long)n * power_stride(L.A.dmax) > kPowerPad * kPower2) return BCM_OK;
     tmp.rewind();
     int *ctl = tmp.get_n<int>(2), *cnt = tmp.get_n<int>(n), *pre = tmp.get_n<int>(n);
     void *stmp = tmp.get(scan_tmp_bytes(n));
-    NOMEM(ctl && cnt && pre && stmp);
+    if (!(ctl && cnt && pre && stmp)) return BCM_OK;
     // sum and maximum of n counts
     int r[2];
     auto totals = [&](const int *in) {
         scan_exclusive(s, in, pre, n, ctl, stmp, ctl + 1);
         return read_back(s, ctl, sizeof(r), r);
     };
-    auto matrix = [&](Arena &a, int longest, PowerMat &M) {
+    auto matrix = [&](int longest, PowerMat &M) {
         M.W = power_stride(longest);
-        M.col = a.get_n<int>((size_t)n * M.W);
-        M.val = a.get_n<double>((size_t)n * M.W);
+        M.col = h->persist.get_n<int>((size_t)n * M.W);
+        M.val = h->persist.get_n<double>((size_t)n * M.W);
         return M.col && M.val;
     };
+    const Arena::Mark before = h->persist.mark();
     PowerOp P;
-    P.m[0].len = h->persist.get_n<int>(n);
-    P.m[0].nnz = L.A.nnz;
-    NOMEM(P.m[0].len && matrix(h->persist, L.A.dmax, P.m[0]));
-    launch_power_first(s, L, P.m[0]);
     for (int t = 0; t < (sweeps % 4 ? 1 : 2); ++t) {
-        const PowerMat &M = P.m[t];
         const long long most = t == 0 ? kPower2 : kPower4;
         if (t > 0 && r[1] > power_row_limit()) break;  // (r: M's entries and longest row)
-        launch_power_products(s, n, M, cnt);
+        if (t == 0) launch_power_products(s, L.A, cnt);
+        else launch_power_products(s, n, P.m[t], cnt);
         int rc = totals(cnt);
         if (rc) return rc;
         // (a square keeps about 6 of 10 products of a first power, 1 of 5 of a second)
         const int cand = r[1];
         if (cand > power_cand_limit() || r[0] > (t == 0 ? 5 * most / 2 : 8 * most)) break;
+        const Arena::Mark mk = h->persist.mark();
+        if (t == 0) {
+            P.m[0].len = h->persist.get_n<int>(n);
+            P.m[0].nnz = L.A.nnz;
+            bool got = P.m[0].len && matrix(L.A.dmax, P.m[0]);
+            for (auto &b : P.buf) got = got && (b = h->persist.get_n<double>(n));
+            if (!got) {
+                h->persist.back(before);
+                return BCM_OK;
+            }
+            launch_power_first(s, L, P.m[0]);
+        }
+        const PowerMat &M = P.m[t];
+        // (sweeps that are one application of the power: M^2 is never applied for 2
+        // sweeps, nor M^4 for 4)
+        const bool needed = (2 << t) != sweeps;
+        const Arena::Mark mq = h->persist.mark();
         PowerMat Q;
         Q.len = h->persist.get_n<int>(n);
-        NOMEM(Q.len);
-        launch_power_square(s, 0, n, M, Q, cnt, cand);
-        rc = totals(Q.len);
-        if (rc) return rc;
-        if (r[0] > most || (long long)n * power_stride(r[1]) > 8 * most) break;
+        if (Q.len) {
+            launch_power_square(s, 0, n, M, Q, cnt, cand);
+            rc = totals(Q.len);
+            if (rc) return rc;
+        }
+        if (!Q.len || r[0] > most || (long long)n * power_stride(r[1]) > kPowerPad * most ||
+            (needed && !matrix(r[1], Q))) {
+            HIPCHK(hipStreamSynchronize(s));
+            h->persist.back(mk);
+            break;
+        }
+        P.p = 2 << t;
+        if (!needed) {
+            h->persist.back(mq);
+            break;
+        }
         Q.nnz = r[0];
-        NOMEM(matrix(h->persist, r[1], Q));
         launch_power_square(s, 1, n, M, Q, cnt, cand);
         P.m[t + 1] = Q;
-        P.p = 2 << t;
     }
-    if (P.p == 0) return BCM_OK;
-    for (auto &b : P.buf) {
-        b = h->persist.get_n<double>(n);
-        NOMEM(b);
-    }
-    L.power = P;
+    if (P.p > 0) L.power = P;
     return BCM_OK;
 }
 

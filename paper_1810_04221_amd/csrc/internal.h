@@ -146,6 +146,15 @@ struct Arena {
     template <typename T>
     T *get_n(size_t n) { return static_cast<T *>(get(n * sizeof(T))); }
     void reserve(size_t bytes);
+    // What was taken after mark() is given back by back(): memory for a form of the
+    // hierarchy that is then not taken, or that could not be had in full.
+    struct Mark {
+        size_t chunks;
+        char *cur;
+        size_t left;
+    };
+    Mark mark() const { return {chunks.size(), cur, left}; }
+    void back(const Mark &m);
     void rewind();   // forget all sub-allocations, keep the chunks
     void release();  // free every chunk
 };
@@ -267,8 +276,10 @@ struct PowerOp {
     double *buf[3] = {nullptr, nullptr, nullptr};
 };
 // Entries of M^2 and of M^4 up to which they are applied: one application then
-// costs little more than the launch that it saves (12 B an entry: 24 and 12 MB).
-constexpr long long kPower2 = 2LL << 20, kPower4 = 1LL << 20;
+// costs little more than the launch that it saves (12 B an entry: 24 and 12 MB
+// read).  Rows are padded to the longest one's stride: a matrix of more than
+// kPowerPad slots per such entry is not formed, M^2 and M below 201 MB, M^4 below 101.
+constexpr long long kPower2 = 2LL << 20, kPower4 = 1LL << 20, kPowerPad = 8;
 
 // One level of the hierarchy.  Row i of A^k, its l1 inverse diagonal, the
 // composed prolongator P^k (one nonzero per row: column agg[i], value p[i]),
@@ -490,7 +501,8 @@ int power_row_limit();   // longest row of a matrix that is squared
 int power_cand_limit();  // most products that form one row of the square
 int power_stride(int longest);
 void launch_power_first(hipStream_t s, const Level &L, const PowerMat &M);
-// cnt[i] = products that form row i of M M
+// cnt[i] = products that form row i of A A (the pattern of M) and of M M
+void launch_power_products(hipStream_t s, const Csr &A, int *cnt);
 void launch_power_products(hipStream_t s, int n, const PowerMat &M, int *cnt);
 // pass 0: Q.len (the columns of each row of M M); pass 1: Q's entries
 // (products: launch_power_products' counts, most: their maximum)

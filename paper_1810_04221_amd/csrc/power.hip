@@ -42,15 +42,30 @@ k_power_first(int n, int W, const int *__restrict__ rp, const int *__restrict__ 
     if (lane == 0) len[i] = l;
 }
 
+// Rows of a CSR matrix, and of a power
+struct RowsCsr {
+    const int *rp;
+    __device__ size_t begin(int i) const { return rp[i]; }
+    __device__ int length(int i) const { return rp[i + 1] - rp[i]; }
+};
+struct RowsPadded {
+    const int *len;
+    int W;
+    __device__ size_t begin(int i) const { return (size_t)i * W; }
+    __device__ int length(int i) const { return len[i]; }
+};
+
 // products that form row i of the square
+template <typename Rows>
 __global__ void __launch_bounds__(kBlock)
-k_power_products(int n, int W, const int *__restrict__ len, const int *__restrict__ col, int *__restrict__ cnt) {
+k_power_products(int n, Rows R, const int *__restrict__ col, int *__restrict__ cnt) {
     constexpr int G = 16;
     const int i = (blockIdx.x * kBlock + threadIdx.x) / G, lane = threadIdx.x % G;
     if (i >= n) return;
-    const int l = len[i];
+    const int l = R.length(i);
+    const size_t o = R.begin(i);
     int c = 0;
-    for (int k = lane; k < l; k += G) c += len[col[(size_t)i * W + k]];
+    for (int k = lane; k < l; k += G) c += R.length(col[o + k]);
     c = group_sum<G>(c);
     if (lane == 0) cnt[i] = c;
 }
@@ -283,8 +298,14 @@ void launch_power_first(hipStream_t s, const Level &L, const PowerMat &M) {
                        L.A.v, L.dinv, M.len, M.col, M.val);
 }
 
+void launch_power_products(hipStream_t s, const Csr &A, int *cnt) {
+    hipLaunchKernelGGL(k_power_products<RowsCsr>, dim3(blocks_for(16LL * A.n)), dim3(kBlock), 0, s, A.n,
+                       RowsCsr{A.rp}, A.ci, cnt);
+}
+
 void launch_power_products(hipStream_t s, int n, const PowerMat &M, int *cnt) {
-    hipLaunchKernelGGL(k_power_products, dim3(blocks_for(16LL * n)), dim3(kBlock), 0, s, n, M.W, M.len, M.col, cnt);
+    hipLaunchKernelGGL(k_power_products<RowsPadded>, dim3(blocks_for(16LL * n)), dim3(kBlock), 0, s, n,
+                       RowsPadded{M.len, M.W}, M.col, cnt);
 }
 
 void launch_power_square(hipStream_t s, int pass, int n, const PowerMat &M, const PowerMat &Q, const int *products,

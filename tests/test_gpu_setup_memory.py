@@ -1,0 +1,94 @@
+"""Device memory of the setup's optional forms (the coarsest sweeps by powers):
+what is tried and not taken is given back, and a form that cannot be allocated
+leaves the levels' own kernels, with the same results."""
+import numpy as np
+import pytest
+
+from paper_1810_04221_amd import problems as P
+from test_gpu_parity import ENTRY_FP64, B, _close_entries, say  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def meter(B, monkeypatch):  # noqa: F811
+    """The library's allocator with a count of what it holds and, when set, a limit."""
+    base = B._TorchAllocator
+
+    class Meter(base):
+        limit = None
+
+        def __init__(self, device, stream):
+            super().__init__(device, stream)
+            self.live = self.peak = 0
+            take, give = self.alloc, self.dealloc
+
+            def alloc(size, ctx):
+                if Meter.limit is not None and self.live + size > Meter.limit:
+                    return None
+                p = take(size, ctx)
+                if p:
+                    self.live += size
+                    self.peak = max(self.peak, self.live)
+                return p
+
+            def dealloc(ptr, size, ctx):
+                self.live -= size
+                give(ptr, size, ctx)
+
+            self.alloc, self.dealloc = B.ALLOC_FN(alloc), B.DEALLOC_FN(dealloc)
+            self.keep = take, give
+
+    monkeypatch.setattr(B, "_TorchAllocator", Meter)
+    return Meter
+
+
+def test_refused_powers_hold_no_memory(B, meter):  # noqa: F811
+    # one level of 125,000 rows: the square has too many entries.  An odd number of
+    # sweeps never tries it: the two handles hold the same memory
+    rp, ci, va = P.poisson3d(50)
+    say("refused powers: poisson3d 50^3, one level")
+    held, peak = [], []
+    for sweeps in (21, 20):
+        h = B.Hierarchy(rp, ci, va, max_levels=1, coarse_sweeps=sweeps)
+        held.append(h._alloc.live)
+        peak.append(h._alloc.peak)
+        h.close()
+        assert h._alloc.live == 0
+    assert held[0] == held[1] and peak[0] == peak[1], (held, peak)
+
+
+def test_powers_without_memory_for_them(B, ora, meter):  # noqa: F811
+    # 129,600 rows, whose square is taken: with just the memory of a setup that does
+    # not try it, the sweeps stay one by one
+    rp, ci, va = P.poisson2d(360)
+    n = len(rp) - 1
+    say(f"powers without memory: poisson2d 360^2 n={n}, one level")
+    r = P.uniform_rhs(n, 8)
+    h = B.Hierarchy(rp, ci, va, max_levels=1, coarse_sweeps=21)
+    bare, limit = h._alloc.live, h._alloc.peak
+    h.close()
+    zo = ora.Hierarchy(rp, ci, va, np.ones(n), max_levels=1, coarse_sweeps=20).vcycle(r)
+    for lim in (None, limit):
+        meter.limit = lim
+        h = B.Hierarchy(rp, ci, va, max_levels=1, coarse_sweeps=20)
+        assert (h._alloc.live == bare) == (lim is not None)
+        _close_entries(h.precond(r).cpu().numpy(), zo, ENTRY_FP64)
+        h.close()
+
+
+@pytest.mark.parametrize("sweeps", [2, 4])
+def test_powers_hold_what_they_apply(B, meter, sweeps):  # noqa: F811
+    # 2 sweeps are one application of M, 4 one of M and one of M^2: the power of
+    # `sweeps` itself is not formed.  The rows of M and of M^2 (5 and 13 entries of
+    # 12 bytes) stand at a stride of 64 entries.
+    rp, ci, va = P.poisson2d(250)
+    n = len(rp) - 1
+    say(f"powers held: poisson2d 250^2 n={n}, {sweeps} sweeps")
+    live = []
+    for s in (sweeps + 1, sweeps):
+        h = B.Hierarchy(rp, ci, va, max_levels=1, coarse_sweeps=s)
+        live.append(h._alloc.live)
+        h.close()
+    # (device memory comes in chunks of 64 MiB at least)
+    assert live[1] - live[0] <= (sweeps // 2) * 64 * 12 * n + (64 << 20), live
