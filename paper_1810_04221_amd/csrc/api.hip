@@ -665,7 +665,7 @@ int build_chain(bcm_handle *h, hipStream_t s, Arena &tmp, HostTables &host, int 
     const size_t nch = (n + kChainChunk - 1) / kChainChunk;
     double *A = h->persist.get_n<double>((size_t)C.M * n), *V = h->persist.get_n<double>((size_t)(C.M + 1) * n);
     double *delta = h->persist.get_n<double>(n), *scr = tmp.get_n<double>(chain_scratch(n, L, S));
-    C.E = h->persist.get_n<double>((size_t)C.M * nch);
+    C.E = h->persist.get_n<double>((size_t)C.M * (nch + 1));
     NOMEM(A && V && delta && scr && C.E);
     launch_chain_build(s, dt, n, L, S, scr, A, V, delta);
     C.A = A;

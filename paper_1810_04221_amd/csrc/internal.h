@@ -223,11 +223,16 @@ constexpr long long kStreamSolve = 192LL << 20;
 // the leaves that the hub's recurrence takes (M of them: two per star level
 // above the coarsest and one per coarsest sweep after the first).
 constexpr int kChainChunk = 4096;  // rows per workgroup of the pass that forms E
+// Up to this many chunks every workgroup of the second pass adds the sums' partials
+// itself; beyond, a launch of one wave a sum does so once (the adding grew with the
+// square of the rows).  One cycle: 80,000 rows (20 chunks) 28 us either way, on 40
+// levels 64.5; 160,000 rows on 40 levels 99 -> 90 us, 40,000 rows 47.6 -> 49.
+constexpr int kChainFew = 20;
 constexpr int kStarMaxSweeps = 32;  // coarsest sweeps beyond this keep the sweep kernels
 struct ChainOp {
     int n = 0, M = 0, hub = -1;  // hub -1: no such operator
     const double *A = nullptr, *V = nullptr, *delta = nullptr;  // M x n, (M + 1) x n, n
-    double *E = nullptr;  // M x chunks partial sums
+    double *E = nullptr;  // M x chunks partial sums, then M sums
 };
 // One star level as the chain kernels see it (agg, p: null on the coarsest).
 struct ChainLevel {

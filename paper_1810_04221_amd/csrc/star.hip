@@ -571,13 +571,15 @@ k_chain_dense(int n, int M, int hub, const double *__restrict__ A, const double 
 
 // First pass: E_m = sum_j A[m][j] b_j, one sum and kChainChunk rows per
 // workgroup (partials in chunk order).  A pass over A once: bandwidth from the
-// caches (87 sums over 39,001 rows are 27 MB).
+// caches (87 sums over 39,001 rows are 27 MB).  All sums of a chunk go to one XCD,
+// one after the other, so that its b comes from beyond the L2 once (3,000,000
+// rows, coarsest star alone: cycle 264 -> 232 us).
 constexpr int kChainU = kChainChunk / kBlock;
 template <typename VB>
 __global__ void __launch_bounds__(kBlock)
-k_chain_sums(int n, int nch, const double *__restrict__ A, const VB *__restrict__ b, double *__restrict__ E,
+k_chain_sums(int n, int M, int nch, const double *__restrict__ A, const VB *__restrict__ b, double *__restrict__ E,
              const double *__restrict__ done) {
-    const int ch = blockIdx.x % nch, m = blockIdx.x / nch;
+    const int l = xcd_block(blockIdx.x, gridDim.x), ch = l / M, m = l % M;
     const double *a = A + (size_t)m * n;
     double av[kChainU], bv[kChainU];
 #pragma unroll
@@ -593,6 +595,20 @@ k_chain_sums(int n, int nch, const double *__restrict__ A, const VB *__restrict_
     block_sum<1>(s, lds);
     // (the solve-ended flag is tested before the store only: its load overlaps the sum)
     if (threadIdx.x == 0 && !(done && *done != 0.0)) E[(size_t)m * nch + ch] = s[0];
+}
+
+// The sums from their partials, one wave each (more than kChainFew chunks).  The
+// cycle of a coarsest star of 1,000,000 rows: 341 us with every workgroup of the
+// second pass adding 19 x 245 partials, 94 with this launch; 40 levels of as many
+// rows 1049 -> 430.
+__global__ void __launch_bounds__(64)
+k_chain_fin(int nch, const double *__restrict__ E, double *__restrict__ Es, const double *__restrict__ done) {
+    const int m = blockIdx.x, lane = threadIdx.x;
+    double s = 0.0;
+#pragma unroll 4
+    for (int c = lane; c < nch; c += 64) s += E[(size_t)m * nch + c];
+    s = group_sum<64>(s);
+    if (lane == 0 && !(done && *done != 0.0)) Es[m] = s;
 }
 
 // Second pass: x = delta b + V E.  64 rows per workgroup, its four waves
@@ -711,9 +727,13 @@ template <typename VB, typename VX>
 static void chain_t(hipStream_t s, const ChainOp &C, const VB *b, VX *x, const double *done) {
     const int nch = (C.n + kChainChunk - 1) / kChainChunk;
     if (C.M > 0)
-        hipLaunchKernelGGL((k_chain_sums<VB>), dim3(nch * C.M), dim3(kBlock), 0, s, C.n, nch, C.A, b, C.E, done);
-    hipLaunchKernelGGL((k_chain_apply<VB, VX>), dim3((C.n + 63) / 64), dim3(kBlock), 0, s, C.n, C.M, nch, C.hub, C.V,
-                       C.delta, C.E, b, x, done);
+        hipLaunchKernelGGL((k_chain_sums<VB>), dim3(nch * C.M), dim3(kBlock), 0, s, C.n, C.M, nch, C.A, b,
+                           C.E, done);
+    const bool fin = C.M > 0 && nch > kChainFew;
+    double *Es = C.E + (size_t)C.M * nch;
+    if (fin) hipLaunchKernelGGL(k_chain_fin, dim3(C.M), dim3(64), 0, s, nch, C.E, Es, done);
+    hipLaunchKernelGGL((k_chain_apply<VB, VX>), dim3((C.n + 63) / 64), dim3(kBlock), 0, s, C.n, C.M, fin ? 1 : nch,
+                       C.hub, C.V, C.delta, fin ? Es : C.E, b, x, done);
 }
 
 void launch_chain(hipStream_t s, const ChainOp &C, const void *b, void *x, int b_f64, int x_f64, const double *done) {
