@@ -639,10 +639,47 @@ struct HostTables {
     std::vector<std::vector<ChainLevel>> chains;
 };
 
+// Memory of the chain operator of L star levels above the coarsest (n rows on the
+// first): what the handle keeps, and what forming it needs.
+struct ChainMem {
+    double *A = nullptr, *V = nullptr, *delta = nullptr, *E = nullptr;
+    double *scratch = nullptr, *part = nullptr;
+    ChainLevel *tab = nullptr;
+};
+
+// Beyond kChainBytes of both together the levels keep their own kernels: about
+// 1,200,000 rows of 40 levels, 3,400,000 of 12 (one cycle, FP64, operator against
+// legs, setup in brackets: 40 levels of 1,000,000 rows 0.43 against 4.7 ms [57
+// against 11], 12 levels 0.26 against 1.6 [10 against 6]; of 5,000 rows 0.036
+// against 0.53 [1.8 against 2.6]).  A coarsest star alone needs an eighth of that a
+// row and has 20 passes of its own as the alternative: four times the bytes.
+constexpr size_t kChainBytes = size_t(5) << 30;
+bool chain_fits(int n, int L, int sweeps) {
+    if (sweeps < 1 || sweeps > kStarMaxSweeps) return false;
+    const size_t kept = (2 * (size_t)chain_sums(L, sweeps) + 2) * n;
+    return sizeof(double) * (kept + chain_scratch(n, L, sweeps)) <= (L == 0 ? 4 * kChainBytes : kChainBytes);
+}
+
+// False, with nothing taken, when the memory cannot be had: the levels' own
+// kernels need none of it.
+bool chain_alloc(bcm_handle *h, Arena &tmp, int n, int L, int sweeps, ChainMem &m) {
+    const size_t M = chain_sums(L, sweeps), nch = (n + kChainChunk - 1) / kChainChunk;
+    const Arena::Mark pm = h->persist.mark(), tm = tmp.mark();
+    if ((m.tab = static_cast<ChainLevel *>(tmp.get(sizeof(ChainLevel) * (L + 1)))) &&
+        (m.part = tmp.get_n<double>((size_t)(L + 1) * star_blocks(n))) &&
+        (m.scratch = tmp.get_n<double>(chain_scratch(n, L, sweeps))) && (m.A = h->persist.get_n<double>(M * n)) &&
+        (m.V = h->persist.get_n<double>((M + 1) * n)) && (m.delta = h->persist.get_n<double>(n)) &&
+        (m.E = h->persist.get_n<double>(M * (nch + 1))))
+        return true;
+    h->persist.back(pm);
+    tmp.back(tm);
+    return false;
+}
+
 // The operator of a chain of star levels k0 .. nl - 1 (hubs: one per level)
-// into lv[k0].chain; its scratch comes from tmp.
-int build_chain(bcm_handle *h, hipStream_t s, Arena &tmp, HostTables &host, int k0, const std::vector<int> &hubs,
-                bool diagonals) {
+// into lv[k0].chain; diagonals: form the levels' l1 diagonals first.
+int build_chain(bcm_handle *h, hipStream_t s, const ChainMem &m, HostTables &host, int k0,
+                const std::vector<int> &hubs, bool diagonals) {
     const int L = (int)hubs.size() - 1, n = h->lv[k0].A.n, S = h->prm.coarse_sweeps;
     host.chains.emplace_back();
     std::vector<ChainLevel> &tab = host.chains.back();
@@ -650,36 +687,19 @@ int build_chain(bcm_handle *h, hipStream_t s, Arena &tmp, HostTables &host, int 
         const Level &V = h->lv[k0 + t];
         tab.push_back({V.A.n, hubs[t], V.A.rp, V.A.ci, V.A.v, V.dinv, t < L ? V.agg : nullptr, t < L ? V.p : nullptr});
     }
-    ChainLevel *dt = static_cast<ChainLevel *>(tmp.get(sizeof(ChainLevel) * tab.size()));
-    NOMEM(dt);
-    HIPCHK(hipMemcpyAsync(dt, tab.data(), sizeof(ChainLevel) * tab.size(), hipMemcpyHostToDevice, s));
-    if (diagonals) {
-        double *part = tmp.get_n<double>((size_t)(L + 1) * star_blocks(n));
-        NOMEM(part);
-        launch_star_dinv(s, dt, L + 1, n, part);
-    }
+    HIPCHK(hipMemcpyAsync(m.tab, tab.data(), sizeof(ChainLevel) * tab.size(), hipMemcpyHostToDevice, s));
+    if (diagonals) launch_star_dinv(s, m.tab, L + 1, n, m.part);
+    launch_chain_build(s, m.tab, n, L, S, m.scratch, m.A, m.V, m.delta);
     ChainOp C;
     C.n = n;
     C.M = chain_sums(L, S);
     C.hub = hubs[0];
-    const size_t nch = (n + kChainChunk - 1) / kChainChunk;
-    double *A = h->persist.get_n<double>((size_t)C.M * n), *V = h->persist.get_n<double>((size_t)(C.M + 1) * n);
-    double *delta = h->persist.get_n<double>(n), *scr = tmp.get_n<double>(chain_scratch(n, L, S));
-    C.E = h->persist.get_n<double>((size_t)C.M * (nch + 1));
-    NOMEM(A && V && delta && scr && C.E);
-    launch_chain_build(s, dt, n, L, S, scr, A, V, delta);
-    C.A = A;
-    C.V = V;
-    C.delta = delta;
+    C.A = m.A;
+    C.V = m.V;
+    C.delta = m.delta;
+    C.E = m.E;
     h->lv[k0].chain = C;
     return BCM_OK;
-}
-
-// Bytes of the chain operator of L star levels above the coarsest (n rows on
-// the first); beyond kChainBytes the levels keep their own kernels.
-constexpr size_t kChainBytes = size_t(4) << 30;
-bool chain_fits(int n, int L, int sweeps) {
-    return sweeps >= 1 && sweeps <= kStarMaxSweeps && 16 * (size_t)n * (chain_sums(L, sweeps) + 1) <= kChainBytes;
 }
 
 // The coarsest level's sweeps as a chain operator when it is a star (one hub
@@ -698,8 +718,9 @@ int build_coarsest_star(bcm_handle *h, hipStream_t s, Arena &tmp, HostTables &ho
     launch_star_verify(s, L.A.n, L.A.rp, L.A.ci, L.A.v, f[1], ctl);
     rc = read_back(s, ctl, sizeof(f), f);
     if (rc) return rc;
-    if (f[2]) return BCM_OK;
-    return build_chain(h, s, tmp, host, h->nl - 1, std::vector<int>{f[1]}, false);
+    ChainMem m;
+    if (f[2] || !chain_alloc(h, tmp, L.A.n, 0, h->prm.coarse_sweeps, m)) return BCM_OK;
+    return build_chain(h, s, m, host, h->nl - 1, std::vector<int>{f[1]}, false);
 }
 
 // Powers of the coarsest level's sweep matrix, while they stay sparse enough
@@ -1176,8 +1197,13 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
     h->nl = k + 1;
     // The star levels as one operator (V-cycle): on their own, or, when small,
     // inside the folded operator of the small levels.
-    const bool chain = ks > 0 && P.cycle == BCM_VCYCLE && P.fold && ks + (int)hubs.size() == h->nl &&
-                       chain_fits(h->lv[ks].A.n, (int)hubs.size() - 1, P.coarse_sweeps);
+    bool chain = ks > 0 && P.cycle == BCM_VCYCLE && P.fold && ks + (int)hubs.size() == h->nl &&
+                 chain_fits(h->lv[ks].A.n, (int)hubs.size() - 1, P.coarse_sweeps);
+    ChainMem chain_mem;  // (its scratch lies in tmp, which is not rewound before build_chain)
+    if (chain) {
+        tmp.rewind();
+        chain = chain_alloc(h, tmp, h->lv[ks].A.n, (int)hubs.size() - 1, P.coarse_sweeps, chain_mem);
+    }
     // levels without kernels of their own
     auto in_chain = [&](int l) { return chain && l >= ks; };
     {
@@ -1384,8 +1410,7 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
         for (size_t t = 0; t < lv_sell.size(); ++t) h->lv[lv_sell[t]].E.stream = vb > kStreamSolve;
     }
     if (chain) {
-        tmp.rewind();
-        const int rc = build_chain(h, s, tmp, host, ks, hubs, true);
+        const int rc = build_chain(h, s, chain_mem, host, ks, hubs, true);
         if (rc) return rc;
     } else {
         // coarsest level: precompute the sweep operator when it is small

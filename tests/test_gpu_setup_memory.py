@@ -1,11 +1,12 @@
-"""Device memory of the setup's optional forms (the coarsest sweeps by powers):
-what is tried and not taken is given back, and a form that cannot be allocated
+"""Device memory of the setup's optional forms (the coarsest sweeps by powers, star
+levels as one operator): what is tried and not taken is given back, and a form that cannot be allocated
 leaves the levels' own kernels, with the same results."""
 import numpy as np
 import pytest
 
 from paper_1810_04221_amd import problems as P
 from test_gpu_parity import ENTRY_FP64, B, _close_entries, say  # noqa: F401
+from test_gpu_star import _star
 
 pytestmark = pytest.mark.gpu
 
@@ -92,3 +93,24 @@ def test_powers_hold_what_they_apply(B, meter, sweeps):  # noqa: F811
         h.close()
     # (device memory comes in chunks of 64 MiB at least)
     assert live[1] - live[0] <= (sweeps // 2) * 64 * 12 * n + (64 << 20), live
+
+
+@pytest.mark.parametrize("n,levels,bare", [(160000, 12, dict(fold=False)), (300000, 1, dict(coarse_sweeps=33))])
+def test_chain_without_memory_for_it(B, ora, meter, n, levels, bare):  # noqa: F811
+    # a chain of stars, and a coarsest star alone: with just the memory of a setup that
+    # does not form their operator (33 sweeps are beyond it) the levels keep their own
+    # kernels
+    rp, ci, va = _star(n, 5, n)
+    say(f"chain without memory: n={n} levels={levels}")
+    h = B.Hierarchy(rp, ci, va, max_coarse=20, max_levels=levels, **bare)
+    live, limit = h._alloc.live, h._alloc.peak
+    h.close()
+    r = P.uniform_rhs(n, 9)
+    zo = ora.Hierarchy(rp, ci, va, np.ones(n), max_coarse=20, max_levels=levels).vcycle(r)
+    for lim in (None, limit):
+        meter.limit = lim
+        h = B.Hierarchy(rp, ci, va, max_coarse=20, max_levels=levels)
+        if lim is not None:
+            assert h._alloc.live == live
+        _close_entries(h.precond(r).cpu().numpy(), zo, ENTRY_FP64)
+        h.close()
