@@ -1016,7 +1016,10 @@ int find_mid_rows(bcm_handle *h, hipStream_t s, Arena &tmp) {
     return BCM_OK;
 }
 
-int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
+// lean: none of the forms that only save time at the price of memory (star chains,
+// powers, values of A D in FP64, doubling's scratch, the W-cycle's dense operator, the
+// cycle's float32 vectors).
+int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win, bool lean) {
     hipStream_t s = h->s;
     const bcm_params &P = h->prm;
     const int n = Ain->n, nnz = Ain->nnz;
@@ -1197,7 +1200,7 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
     h->nl = k + 1;
     // The star levels as one operator (V-cycle): on their own, or, when small,
     // inside the folded operator of the small levels.
-    bool chain = ks > 0 && P.cycle == BCM_VCYCLE && P.fold && ks + (int)hubs.size() == h->nl &&
+    bool chain = !lean && ks > 0 && P.cycle == BCM_VCYCLE && P.fold && ks + (int)hubs.size() == h->nl &&
                  chain_fits(h->lv[ks].A.n, (int)hubs.size() - 1, P.coarse_sweeps);
     ChainMem chain_mem;  // (its scratch lies in tmp, which is not rewound before build_chain)
     if (chain) {
@@ -1390,12 +1393,13 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             // Below 2^19 rows the residual runs near its latency either way
             // (250k rows: 4.6 against 4.7 us a launch, less over a solve than
             // the scaling costs the setup), so only larger levels and the FP32
-            // cycle's finest take it.
-            if (down_on_sell(L) && !L.yb && !slot_split_level(L) && (fp32 || L.E.sv) &&
+            // cycle's finest take it.  Without memory for it the level gathers
+            // dinv and b as the others do.
+            if (down_on_sell(L) && !L.yb && !slot_split_level(L) && (fp32 || (L.E.sv && !lean)) &&
                 ((fp32 && lv_sell[t] == 0) || L.A.n >= (1 << 19))) {
                 L.E.svd = h->persist.get((fp32 ? sizeof(float) : sizeof(double)) * ne);
-                NOMEM(L.E.svd);
-                launch_sell_scale_cols(s, L.A.n, L.E, fp32, fp32 ? (const void *)L.dinv32 : (const void *)L.dinv);
+                if (L.E.svd)
+                    launch_sell_scale_cols(s, L.A.n, L.E, fp32, fp32 ? (const void *)L.dinv32 : (const void *)L.dinv);
             }
         }
         // the values one solve iteration reads: both legs of every sliced-ELL
@@ -1419,10 +1423,10 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
             const size_t nn2 = (size_t)C.A.n * C.A.n;
             C.S = h->persist.get_n<double>(nn2);
             NOMEM(C.S);
-            if (coarse_in_lds(C.A.n, C.A.nnz, C.lr.n > 0)) {
+            if (lean || coarse_in_lds(C.A.n, C.A.nnz, C.lr.n > 0)) {
                 // one workgroup per unit vector runs the sweeps on the matrix in
                 // its LDS (without it, each would stream the matrix through one
-                // CU: 866 rows with 362,762 entries took 55 ms)
+                // CU: 866 rows with 362,762 entries took 55 ms, but no memory)
                 launch_coarse_build(s, C, P.coarse_sweeps, C.S);
             } else {
                 tmp.rewind();
@@ -1448,7 +1452,7 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
     const int kb = chain ? ks : h->nl - 1;
     // (W-cycle: the coarsest level alone is worth it, its parent applies it twice)
     const bool wcyc = P.cycle == BCM_WCYCLE;
-    bool fold = P.fold && kb >= (wcyc ? 1 : 2) && (chain ? h->lv[ks].A.n <= kFoldRows : h->lv[kb].S != nullptr);
+    bool fold = P.fold && !(lean && wcyc) && kb >= (wcyc ? 1 : 2) && (chain ? h->lv[ks].A.n <= kFoldRows : h->lv[kb].S != nullptr);
     if (fold && chain && h->lv[ks - 1].A.n > kFoldRows && h->lv[ks].A.n > 1024) fold = false;
     if (chain && !fold) h->kc = ks;
     if (fold) {
@@ -1552,12 +1556,12 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
         h->ctmp[0] = h->persist.get_n<double>(h->lv[h->nl - 1].A.n);
         h->ctmp[1] = h->persist.get_n<double>(h->lv[h->nl - 1].A.n);
         NOMEM(h->ctmp[0] && h->ctmp[1]);
-        if (h->lv[h->nl - 1].lr.n == 1) {
+        if (!lean && h->lv[h->nl - 1].lr.n == 1) {
             tmp.rewind();
             const int rc = build_coarsest_star(h, s, tmp, host);
             if (rc) return rc;
         }
-        if (h->lv[h->nl - 1].chain.hub < 0) {
+        if (!lean && h->lv[h->nl - 1].chain.hub < 0) {
             const int rc = build_power(h, s, tmp);
             if (rc) return rc;
         }
@@ -1574,7 +1578,7 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win) {
     h->red_blocks = reduce_blocks(n);
     h->partials = h->persist.get_n<double>(4 * (size_t)h->red_blocks);
     NOMEM(h->r && h->w && h->d && h->v && h->q && h->u && h->scal && h->partials);
-    if (fp32 && h->nl > 1) {  // (a single level's cycle is the coarsest solve, in float64)
+    if (fp32 && h->nl > 1 && !lean) {  // (a single level's cycle is the coarsest solve, in float64)
         h->r32 = h->persist.get_n<float>(n);
         h->w32 = h->persist.get_n<float>(n);
         NOMEM(h->r32 && h->w32);
@@ -2315,17 +2319,22 @@ int bcm_setup(const bcm_csr *A, const double *w, const bcm_params *p, bcm_handle
         return BCM_EINVAL;
     }
     const double t0 = now_ms();
-    bcm_handle *h = new bcm_handle();
-    h->prm = prm;
-    h->s = (hipStream_t)prm.stream;
-    h->persist.alloc = prm.alloc;
-    h->persist.dealloc = prm.dealloc;
-    h->persist.ctx = prm.alloc_ctx;
-    int rc = build_hierarchy(h, A, w);
-    if (rc) {
-        bcm_free(h);
-        return rc;
+    bcm_handle *h = nullptr;
+    // A setup that runs out of memory is done again without the forms that only
+    // save time: they may have taken what the rest then lacked.
+    int rc = BCM_ENOMEM;
+    for (int lean = 0; lean < 2 && rc == BCM_ENOMEM; ++lean) {
+        h = new bcm_handle();
+        h->prm = prm;
+        h->s = (hipStream_t)prm.stream;
+        h->persist.alloc = prm.alloc;
+        h->persist.dealloc = prm.dealloc;
+        h->persist.ctx = prm.alloc_ctx;
+        rc = build_hierarchy(h, A, w, lean != 0);
+        if (rc) bcm_free(h);
     }
+    if (rc) return rc;
+    g_err.clear();
     h->t_setup_ms = now_ms() - t0;
     *out = h;
     return BCM_OK;

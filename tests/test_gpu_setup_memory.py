@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_1810_04221_amd import problems as P
-from test_gpu_parity import ENTRY_FP64, B, _close_entries, say  # noqa: F401
+from test_gpu_parity import ENTRY_FP32, ENTRY_FP64, B, _close_entries, say  # noqa: F401
 from test_gpu_star import _star
 
 pytestmark = pytest.mark.gpu
@@ -113,4 +113,37 @@ def test_chain_without_memory_for_it(B, ora, meter, n, levels, bare):  # noqa: F
         if lim is not None:
             assert h._alloc.live == live
         _close_entries(h.precond(r).cpu().numpy(), zo, ENTRY_FP64)
+        h.close()
+
+
+@pytest.mark.parametrize("case,bare", [("diffusion fp64", dict(coarse_sweeps=21)), ("diffusion fp32", dict(coarse_sweeps=21)),
+                                       ("star", dict(fold=False)), ("dense W", None)])
+def test_setup_between_the_bare_and_the_full_memory(B, ora, meter, case, bare):  # noqa: F811
+    # whatever the optional forms have taken before the memory ends: a setup that has
+    # room for the levels' own kernels succeeds, with the same cycle
+    rp, ci, va, kw = {
+        "diffusion fp64": lambda: P.diffusion3d(84, 1.0, 3)[:3] + (dict(min_ratio=2.0),),
+        "diffusion fp32": lambda: P.diffusion3d(84, 1.0, 3)[:3] + (dict(min_ratio=2.0, precision="fp32"),),
+        "star": lambda: _star(160000, 5, 1) + (dict(max_levels=12, max_coarse=20),),
+        "dense W": lambda: P.poisson2d(89)[:3] + (dict(max_levels=2, cycle="W"),)}[case]()
+    n = len(rp) - 1
+    say(f"setup between the bare and the full memory: {case} n={n}")
+    r = P.uniform_rhs(n, 10)
+    h = B.Hierarchy(rp, ci, va, **kw)
+    full, z0, sizes = h._alloc.peak, h.precond(r).cpu().numpy(), h.info()["n"]
+    h.close()
+    if bare is not None:
+        h = B.Hierarchy(rp, ci, va, **{**kw, **bare})
+        low = h._alloc.peak
+        h.close()
+    else:  # without the three arrays of the doubling's scratch
+        low = full - 3 * 8 * sizes[-1] ** 2
+    assert low < full
+    for k in range(9):
+        meter.limit = low + (full - low) * k // 8
+        h = B.Hierarchy(rp, ci, va, **kw)
+        assert h.info()["n"] == sizes
+        _close_entries(h.precond(r).cpu().numpy(), z0, ENTRY_FP32 if kw.get("precision") == "fp32" else ENTRY_FP64)
+        x = h.solve(r, tol=1e-8)
+        assert h.info()["relres"] <= 1e-8 and bool(x.isfinite().all())
         h.close()
