@@ -808,9 +808,11 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
 // whose hub is coupled to every row: `sweeps` launches per level, run ahead
 // without a read-back (every sweep forms one pair, so all sizes are known).
 // appended: levels added (0: not such a star, or it forms no pair); hubs: the
-// hub row of level k and of each level added.
+// hub row of level k and of each level added; refused: set when level k has a
+// star's pattern but not its symmetry (an input that was not checked) or forms
+// no pair, as the levels below it would again.
 int star_levels(bcm_handle *h, hipStream_t s, Arena &tmp, Arena &keep, int k, int max_coarse, int &appended,
-                std::vector<int> &hubs) {
+                std::vector<int> &hubs, bool &refused) {
     const bcm_params &P = h->prm;
     constexpr int kStarMin = 16;  // rows: smaller stars take the general sweeps
     Level &L0 = h->lv[k];
@@ -857,7 +859,9 @@ int star_levels(bcm_handle *h, hipStream_t s, Arena &tmp, Arena &keep, int k, in
     NOMEM(pc[0] && pc[1] && pi[0] && pi[1]);
     launch_star_best(s, n0, L0.A.v, L0.w, hub0, hubd, pc[0], pi[0]);
     int np = nb0, it = 0, levels = 0;
+    std::vector<Arena::Mark> marks;  // before each level's arrays
     for (;; ++levels) {
+        marks.push_back(h->persist.mark());
         Level &L = h->lv[k + levels];
         const int nk = L.A.n;
         if (nk <= max_coarse || k + levels + 1 >= P.max_levels || k + levels + 1 >= kMaxLevels ||
@@ -949,6 +953,8 @@ int star_levels(bcm_handle *h, hipStream_t s, Arena &tmp, Arena &keep, int k, in
         L.p = nullptr;
         h->lv[k + t + 1] = Level();
     }
+    h->persist.back(marks[done]);
+    refused = done == 0 && levels > 0;
     appended = done;
     hubs = hv;
     return BCM_OK;
@@ -1097,15 +1103,16 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win, bool l
     } pend;
     // a stalled hierarchy's star levels: the first, and the hubs of all of them
     int ks = -1;
+    bool no_star = false;
     std::vector<int> hubs;
     for (;;) {
         Level &L = h->lv[k];
         const int nk = L.A.n;
         if (nk <= max_coarse || k + 1 >= P.max_levels || k + 1 >= kMaxLevels) break;
         // the last level lost two rows a sweep at most: it may be a star from here on
-        if (ks < 0 && k > 0 && rmin <= 1.0 && h->lv[k - 1].A.n - nk <= 2 * P.sweeps) {
+        if (ks < 0 && !no_star && k > 0 && rmin <= 1.0 && h->lv[k - 1].A.n - nk <= 2 * P.sweeps) {
             int added = 0;
-            const int rc = star_levels(h, s, tmp, keep, k, max_coarse, added, hubs);
+            const int rc = star_levels(h, s, tmp, keep, k, max_coarse, added, hubs, no_star);
             if (rc) return rc;
             if (pend.idx >= 0) {
                 sp.set_bytes(pend.idx, bytes_setup_galerkin(pend.m, pend.z, pend.nc, L.A.nnz));

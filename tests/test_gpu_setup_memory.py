@@ -147,3 +147,24 @@ def test_setup_between_the_bare_and_the_full_memory(B, ora, meter, case, bare): 
         x = h.solve(r, tol=1e-8)
         assert h.info()["relres"] <= 1e-8 and bool(x.isfinite().all())
         h.close()
+
+
+def test_unsymmetric_star_holds_no_trial_levels(B, meter):  # noqa: F811
+    # a star's pattern with one entry that differs from its transposed one by an ulp, not
+    # checked: the general sweeps take every level, and what the star's sweeps had
+    # allocated for it is given back
+    n = 20000
+    rp, ci, va = _star(n, 5, 7)
+    say(f"unsymmetric star n={n}")
+    live = []
+    for odd in (False, True):
+        v = va.copy()
+        if odd:
+            q = rp[n // 2 + 1] - 2  # row n / 2: its hub entry
+            assert ci[q] == 5
+            v[q] = np.nextafter(v[q], 0.0)
+        h = B.Hierarchy(rp, ci, v, max_coarse=20, check=False, fold=False)
+        assert h.info()["nl"] == 40
+        live.append(h._alloc.live)
+        h.close()
+    assert live[1] <= live[0] + (64 << 20), live
