@@ -732,7 +732,7 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
     Level &L = h->lv[h->nl - 1];
     const int n = L.A.n, sweeps = h->prm.coarse_sweeps;
     if (sweeps % 2 || L.lr.n > 0 || L.A.dmax > power_row_limit() || n > (1 << 17)) return BCM_OK;
-    if ((long long)n * power_stride(L.A.dmax) > kPowerPad * kPower2) return BCM_OK;
+    if ((long long)n * power_stride(L.A.dmax) > kPowerPad * kPower2Long) return BCM_OK;
     tmp.rewind();
     int *ctl = tmp.get_n<int>(2), *cnt = tmp.get_n<int>(n), *pre = tmp.get_n<int>(n);
     void *stmp = tmp.get(scan_tmp_bytes(n));
@@ -752,7 +752,7 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
     const Arena::Mark before = h->persist.mark();
     PowerOp P;
     for (int t = 0; t < (sweeps % 4 ? 1 : 2); ++t) {
-        const long long most = t == 0 ? kPower2 : kPower4;
+        long long most = t == 0 ? kPower2Long : kPower4;
         if (t > 0 && r[1] > power_row_limit()) break;  // (r: M's entries and longest row)
         if (t == 0) launch_power_products(s, L.A, cnt);
         else launch_power_products(s, n, P.m[t], cnt);
@@ -761,6 +761,8 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
         // (a square keeps about 6 of 10 products of a first power, 1 of 5 of a second)
         const int cand = r[1];
         if (cand > power_cand_limit() || r[0] > (t == 0 ? 5 * most / 2 : 8 * most)) break;
+        // (so many rows may take 16 lanes each at most: 12 entries, of two dozen products or fewer)
+        if (32LL * n > kPowerLanes && r[0] > 24LL * n) break;
         const Arena::Mark mk = h->persist.mark();
         if (t == 0) {
             P.m[0].len = h->persist.get_n<int>(n);
@@ -784,8 +786,10 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
             launch_power_square(s, 0, n, M, Q, cnt, cand);
             rc = totals(Q.len);
             if (rc) return rc;
+            if (t == 0 && r[0] < 256LL * n) most = kPower2;
         }
-        if (!Q.len || r[0] > most || (long long)n * power_stride(r[1]) > kPowerPad * most ||
+        if (!Q.len || r[0] > most || (long long)n * power_lanes(r[0], n) > kPowerLanes ||
+            (long long)n * power_stride(r[1]) > kPowerPad * most ||
             (needed && !matrix(r[1], Q))) {
             HIPCHK(hipStreamSynchronize(s));
             h->persist.back(mk);

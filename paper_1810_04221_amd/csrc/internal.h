@@ -280,11 +280,19 @@ struct PowerOp {
     PowerMat m[3];      // M, M^2, M^4
     double *buf[3] = {nullptr, nullptr, nullptr};
 };
-// Entries of M^2 and of M^4 up to which they are applied: one application then
-// costs little more than the launch that it saves (12 B an entry: 24 and 12 MB
-// read).  Rows are padded to the longest one's stride: a matrix of more than
-// kPowerPad slots per such entry is not formed, M^2 and M below 201 MB, M^4 below 101.
-constexpr long long kPower2 = 2LL << 20, kPower4 = 1LL << 20, kPowerPad = 8;
+// M^2 and M^4 are applied up to so many entries (M^2 of 256 and more a row, whose
+// lanes are all busy, up to kPower2Long) and, where rows are short, lanes of the
+// whole level: beyond, one application takes longer than the launches of the sweeps
+// that it saves.  20 sweeps one by one and by M^2 (a cycle of one level, us): 5-point
+// grid, 57,600 rows 103 and 89, 72,900 rows 100 and 103, 129,600 rows 117 and 161;
+// 7-point, 64,000 rows 112 and 95, 74,088 rows 100 and 105; random graph of 11
+// entries a row, 1.3 M entries of M^2 105 and 96, 1.5 M 105 and 109, 1.8 M 102 and
+// 124; of 21 entries a row, 2.0 M 105 and 91, 2.4 M 105 and 108; coarsest level of
+// diffusion3d, 1.2 M 193 and 180, 1.8 M 315 and 312.  Rows are padded to the longest
+// one's stride: a matrix of more than kPowerPad slots per entry allowed is not
+// formed (12 B a slot: M and M^2 below 202 MB, M^4 below 101).
+constexpr long long kPower2 = 3LL << 19, kPower2Long = 2LL << 20, kPower4 = 1LL << 20;
+constexpr long long kPowerLanes = 2LL << 20, kPowerPad = 8;
 
 // One level of the hierarchy.  Row i of A^k, its l1 inverse diagonal, the
 // composed prolongator P^k (one nonzero per row: column agg[i], value p[i]),
@@ -503,6 +511,7 @@ void launch_copy_f64(hipStream_t s, size_t n, const double *src, double *dst);
 
 // ---- powers of the coarsest sweep matrix (power.hip) ----
 int power_row_limit();   // longest row of a matrix that is squared
+int power_lanes(long long nnz, int n);  // lanes that a row of a power is applied with
 int power_cand_limit();  // most products that form one row of the square
 int power_stride(int longest);
 void launch_power_first(hipStream_t s, const Level &L, const PowerMat &M);

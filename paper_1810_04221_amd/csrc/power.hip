@@ -243,14 +243,14 @@ k_power_apply(int n, int W, const int *__restrict__ len, const int *__restrict__
 
 template <typename VX, typename F, typename C>
 void apply(hipStream_t s, int n, const PowerMat &M, F f, C g, VX *x, const double *done) {
-    const double avg = (double)M.nnz / n;
+    const int lanes = power_lanes(M.nnz, n);
     auto go = [&](auto gc) {
         constexpr int G = decltype(gc)::value;
         hipLaunchKernelGGL((k_power_apply<G, VX, F, C>), dim3(blocks_for((long long)n * G)), dim3(kBlock), 0, s, n, M.W,
                            M.len, M.col, M.val, f, g, x, done);
     };
-    if (avg <= 12.0) go(std::integral_constant<int, 16>{});
-    else if (avg <= 40.0) go(std::integral_constant<int, 32>{});
+    if (lanes == 16) go(std::integral_constant<int, 16>{});
+    else if (lanes == 32) go(std::integral_constant<int, 32>{});
     else go(std::integral_constant<int, 64>{});
 }
 
@@ -291,6 +291,10 @@ void power_t(hipStream_t s, const PowerOp &P, int n, int sweeps, const double *d
 
 int power_row_limit() { return kRowMax; }
 int power_cand_limit() { return kCand; }
+int power_lanes(long long nnz, int n) {
+    const double avg = (double)nnz / n;
+    return avg <= 12.0 ? 16 : (avg <= 40.0 ? 32 : 64);
+}
 int power_stride(int longest) { return (longest + kPad - 1) / kPad * kPad; }
 
 void launch_power_first(hipStream_t s, const Level &L, const PowerMat &M) {

@@ -1,5 +1,6 @@
 """Both sides of the lines at which a path changes, against the oracle: the Suitor
-matching in LDS (up to 4096 vertices), the down leg on the values of A D in FP64
+matching in LDS (up to 4096 vertices), the coarsest sweeps by powers (where the square
+is taken or refused by its lanes and entries), the down leg on the values of A D in FP64
 (levels of 2^19 rows, values that are no float32), the flexible-CG stop test in the
 fused down leg (aggregates of up to four rows) and the W-cycle's second result added
 by the up leg.  Matchings bit for bit; cycles within the entry-wise bounds of one
@@ -127,4 +128,23 @@ def test_second_result_of_the_w_cycle(B, ora, matrix, levels, precision, fold): 
     for seed in (74, 75, 76):  # (the level's two result vectors change places from cycle to cycle)
         r = P.uniform_rhs(n, seed)
         _close_entries(h.precond(r).cpu().numpy(), ho.vcycle(r), ENTRY_FP64 if precision == "fp64" else ENTRY_FP32)
+    h.close()
+
+
+POWERS = {"65,536 rows of 32 lanes": lambda: P.poisson2d(256), "65,792 rows": lambda: P.poisson2d(256, 257),
+          "64,000 rows, 1.5 M entries": lambda: P.poisson3d(40), "1.5 M entries of 110 a row": lambda: P.random_spd(13500, 11 / 13500, 2),
+          "1.8 M entries of 110 a row": lambda: P.random_spd(16000, 11 / 16000, 2),
+          "2.0 M entries of 400 a row": lambda: P.random_spd(5000, 21 / 5000, 2),
+          "2.4 M entries of 400 a row": lambda: P.random_spd(6000, 21 / 6000, 2)}
+
+
+@pytest.mark.parametrize("name", list(POWERS))
+def test_sweeps_where_the_square_is_taken_or_refused(B, ora, name):  # noqa: F811
+    rp, ci, va = POWERS[name]()[:3]
+    n = len(rp) - 1
+    say(f"powers: {name} n={n} nnz={len(ci)}")
+    r = P.uniform_rhs(n, 77)
+    zo = ora.Hierarchy(rp, ci, va, np.ones(n), max_levels=1).vcycle(r)
+    h = B.Hierarchy(rp, ci, va, max_levels=1)
+    _close_entries(h.precond(r).cpu().numpy(), zo, ENTRY_FP64)
     h.close()

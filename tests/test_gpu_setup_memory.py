@@ -60,11 +60,11 @@ def test_refused_powers_hold_no_memory(B, meter):  # noqa: F811
 
 
 def test_powers_without_memory_for_them(B, ora, meter):  # noqa: F811
-    # 129,600 rows, whose square is taken: with just the memory of a setup that does
+    # 62,500 rows, whose square is taken: with just the memory of a setup that does
     # not try it, the sweeps stay one by one
-    rp, ci, va = P.poisson2d(360)
+    rp, ci, va = P.poisson2d(250)
     n = len(rp) - 1
-    say(f"powers without memory: poisson2d 360^2 n={n}, one level")
+    say(f"powers without memory: poisson2d 250^2 n={n}, one level")
     r = P.uniform_rhs(n, 8)
     h = B.Hierarchy(rp, ci, va, max_levels=1, coarse_sweeps=21)
     bare, limit = h._alloc.live, h._alloc.peak
