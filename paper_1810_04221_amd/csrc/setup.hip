@@ -512,8 +512,14 @@ k_suitor(int n, const int *__restrict__ rp, const unsigned long long *__restrict
 // proposal words in LDS: a proposal step is then an LDS atomic and a load from
 // the CU's own caches instead of a device-scope atomic (100^3 Poisson's sweeps on
 // 3,907 to 122 rows: 125 -> 63 us, a graph of 1,792 rows of 400 entries: 162 -> 90).
-// On about 8,000 vertices one workgroup is no faster (35 -> 42 us).
-constexpr int kSuitorLds = 4096;
+// The line is where one workgroup's share of the proposals outweighs their latency.
+// Kernel alone, one sweep on n rows and one on the pairs, us with all CUs / in LDS:
+// 5-point grid of 4,096 rows 111 / 56, 7-point 69 / 52, a path 1586 / 524, random
+// graphs of 5 to 31 entries a row 20-77 / 20-66, diffusion3d 23.5 / 26; about 8,000
+// vertices 35 / 42.  Rows of two dozen entries and more (sorted candidate lists) can
+// hold many equal weights, whose ties cost a proposal each: elasticity of 1,944 rows
+// 84 / 67, 2,700 rows 102 / 100, 3,630 rows 100 / 125.
+constexpr int kSuitorLds = 4096, kSuitorLdsSorted = 2560;
 __global__ void __launch_bounds__(1024)
 k_suitor_lds(int n, const int *__restrict__ rp, const unsigned long long *__restrict__ cand,
              unsigned long long *__restrict__ ws) {
@@ -1532,8 +1538,9 @@ void launch_candidates(hipStream_t s, int G, int n, bool sorted, const int *rp, 
     });
 }
 
-void launch_suitor(hipStream_t s, int n, const int *rp, const unsigned long long *cand, unsigned long long *ws) {
-    if (n <= kSuitorLds) {
+void launch_suitor(hipStream_t s, int n, bool sorted, const int *rp, const unsigned long long *cand,
+                   unsigned long long *ws) {
+    if (n <= (sorted ? kSuitorLdsSorted : kSuitorLds)) {
         const KernelEvents e = g_kernel_events;  // (launch_k has no dynamic LDS)
         g_kernel_events = KernelEvents{};
         const size_t lds = sizeof(unsigned long long) * (size_t)n;

@@ -1,5 +1,5 @@
 """Both sides of the lines at which a path changes, against the oracle: the Suitor
-matching in LDS (up to 4096 vertices), the coarsest sweeps by powers (where the square
+matching in LDS (up to 4096 vertices, 2560 of rows of two dozen entries and more), the coarsest sweeps by powers (where the square
 is taken or refused by its lanes and entries), the down leg on the values of A D in FP64
 (levels of 2^19 rows, values that are no float32), the flexible-CG stop test in the
 fused down leg (aggregates of up to four rows) and the W-cycle's second result added
@@ -15,11 +15,11 @@ from test_gpu_parity import ENTRY_FP32, ENTRY_FP64, B, _bits, _close_entries, sa
 pytestmark = pytest.mark.gpu
 
 
-def _irregular(n, seed, equal):
-    """A random graph Laplacian plus a small diagonal: rows of 2 to about 40 entries,
-    a third of the weights (equal: all of them) the same."""
+def _irregular(n, seed, equal, more=0):
+    """A random graph Laplacian plus a small diagonal: rows of 2 to about 40 entries
+    (and 2 `more`), a third of the weights (equal: all of them) the same."""
     rng = np.random.default_rng(seed)
-    deg = np.minimum(rng.geometric(0.25, n), 30)
+    deg = np.minimum(rng.geometric(0.25, n), 30) + more
     lo = np.repeat(np.arange(n), deg)
     hi = rng.integers(0, n, len(lo))
     keep = lo != hi
@@ -35,9 +35,11 @@ def _irregular(n, seed, equal):
 
 
 @pytest.mark.parametrize("equal", [False, True])
-@pytest.mark.parametrize("n", [2, 1023, 1024, 1025, 4095, 4096, 4097])
-def test_suitor_on_small_graphs(B, ora, n, equal):  # noqa: F811
-    rp, ci, va = _irregular(n, n, equal)
+@pytest.mark.parametrize("n,more", [(2, 0), (1023, 0), (1024, 0), (1025, 0), (4095, 0), (4096, 0), (4097, 0),
+                                    (1024, 20), (2559, 20), (2560, 20), (2561, 20)])
+def test_suitor_on_small_graphs(B, ora, n, more, equal):  # noqa: F811
+    rp, ci, va = _irregular(n, n, equal, more)
+    assert (len(ci) >= 24 * n) == (more > 0)
     w = np.ones(n)
     say(f"suitor n={n} nnz={len(ci)} equal={equal}")
     c_ref = ora.weights(rp, ci, va, w)
