@@ -341,14 +341,15 @@ __device__ __forceinline__ void long_chunk(int c, const LongRows &lr, const int 
 // ----------------------------------------------------------------------------
 // Down-leg chunk c of the long rows: the block that brings the last chunk of an
 // aggregate's long rows writes b_c.  Every block of the aggregate sums its other
-// members' rows itself, one wave each, beside its own chunk.  The solve-ended flag
-// spares a block its loads, never its arrival: in a launch that takes the stop
-// test the flag may rise while the chunk blocks run, and a block that left on it
-// would leave its row's counter off zero for every later launch.  (What is then
-// summed is of no account: nothing reads b_c before the next cycle writes it.
-// A matrix of 2100 full rows, 9 iterations and the launches after the end: solve
-// 1.75 ms with the loads, 1.72 without.)
-template <int S, typename V, typename VB>
+// members' rows itself, one wave each, beside its own chunk.  Stop: a launch that
+// takes the stop test, where the solve-ended flag may rise while the chunk blocks
+// run.  It then spares a block its loads, never its arrival: a block that left on
+// it would leave its row's counter off zero for every later launch.  (What is then
+// summed is of no account: nothing reads b_c before the next cycle writes it.  A
+// matrix of 2100 full rows, 9 iterations and the launches after the end: solve
+// 1.75 ms with the loads, 1.72 without.)  In other launches all blocks read the
+// flag that an earlier kernel left and leave on it before they come here.
+template <int S, bool Stop, typename V, typename VB>
 __device__ __forceinline__ void down_chunk(int c, const LongRows &lr, const int *__restrict__ ci,
                                            const V *__restrict__ a, const V *__restrict__ dinv,
                                            const V *__restrict__ p, const VB *__restrict__ b, V *__restrict__ bc,
@@ -360,15 +361,17 @@ __device__ __forceinline__ void down_chunk(int c, const LongRows &lr, const int 
     const ChunkInfo C = lr.chunk[c];
     const AggInfo A = lr.agg[C.t];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const bool ended = done && *done != 0.0;
+    const bool ended = Stop && done && *done != 0.0;
     double d[1] = {0.0};
-    if (!ended) d[0] = chunk_share<V>(C, ci, a, f);
+    if (!ended) {
+        d[0] = chunk_share<V>(C, ci, a, f);
 #pragma unroll
-    for (int u = 0; u < S; ++u) {
-        if (u != wv || A.m[u] < 0 || A.lg[u] || ended) continue;
-        V s = row_rest<64>(ci, a, A.beg[u] + lane, A.end[u], V(0), f);
-        s = group_sum<64>(s);
-        if (lane == 0) ms[u] = s;
+        for (int u = 0; u < S; ++u) {
+            if (u != wv || A.m[u] < 0 || A.lg[u]) continue;
+            V s = row_rest<64>(ci, a, A.beg[u] + lane, A.end[u], V(0), f);
+            s = group_sum<64>(s);
+            if (lane == 0) ms[u] = s;
+        }
     }
     block_sum<1>(d, lds);  // (its barriers also publish ms)
     V *part = static_cast<V *>(lr.part);
@@ -437,7 +440,12 @@ k_down_seq(int nc, const int *__restrict__ mem, const int *__restrict__ rp, cons
     }
     if (Tier) {
         if (blk < T.nch) {
-            down_chunk<S>(blk, T.lr, ci, a, dinv, p, b, bc, done);
+            if (st.part) {
+                down_chunk<S, true>(blk, T.lr, ci, a, dinv, p, b, bc, done);
+            } else {
+                if (done && *done != 0.0) return;
+                down_chunk<S, false>(blk, T.lr, ci, a, dinv, p, b, bc, done);
+            }
             return;
         }
         if (blk < T.off) {
