@@ -432,7 +432,7 @@ int match_sweep(hipStream_t s, MatchScratch &ms, const Csr &A, const double *w, 
     }
     if (sp) sp->end(pm, false, A.nnz_dev ? 0.0 : bytes_setup_match(m, A.nnz, sorted));
     const int ps = sp ? sp->begin(BCM_PROF_SETUP_SUITOR, true) : -1;
-    launch_suitor(s, m, sorted, A.rp, ms.cand, ms.ws);
+    launch_suitor(s, m, A.nnz, A.rp, ms.cand, ms.ws);
     if (sp) sp->end(ps, true, bytes_setup_suitor(m));
     if (prof_idx) prof_idx[0] = pm;
     // (copy_src: two ints for the caller's next read-back, to flags_dev[17..18])

@@ -470,8 +470,8 @@ void launch_gal_long(hipStream_t s, int pass, const SegList &seg, const unsigned
 // l1 row norms of the long rows of a level: chunk partial sums into part
 // (float64), float32 copies of their values into v32 when given
 void launch_long_abs(hipStream_t s, const LongRows &lr, const int *rp, const double *v, double *part, float *v32);
-// sorted: as for launch_candidates
-void launch_suitor(hipStream_t s, int n, bool sorted, const int *rp, const unsigned long long *cand,
+// (nnz: a bound, it only picks the kernel)
+void launch_suitor(hipStream_t s, int n, long long nnz, const int *rp, const unsigned long long *cand,
                    unsigned long long *ws);
 void launch_mate(hipStream_t s, int n, const int *rp, const int *ci, const unsigned long long *ws, int *mate,
                  int *leader, const int *csrc = nullptr, int *cdst = nullptr);

@@ -516,10 +516,12 @@ k_suitor(int n, const int *__restrict__ rp, const unsigned long long *__restrict
 // Kernel alone, one sweep on n rows and one on the pairs, us with all CUs / in LDS:
 // 5-point grid of 4,096 rows 111 / 56, 7-point 69 / 52, a path 1586 / 524, random
 // graphs of 5 to 31 entries a row 20-77 / 20-66, diffusion3d 23.5 / 26; about 8,000
-// vertices 35 / 42.  Rows of two dozen entries and more (sorted candidate lists) can
-// hold many equal weights, whose ties cost a proposal each: elasticity of 1,944 rows
-// 84 / 67, 2,700 rows 102 / 100, 3,630 rows 100 / 125.
-constexpr int kSuitorLds = 4096, kSuitorLdsSorted = 2560;
+// vertices 35 / 42.  Rows of two to eight dozen entries can hold many equal weights,
+// whose ties cost a proposal each: elasticity (55 to 67 entries a row) of 1,944 rows
+// 84 / 67, 2,700 rows 102 / 100, 3,630 rows 100 / 125.  Longer rows keep the line
+// (their levels are formed ones, with few ties): random graphs of 290 entries a row,
+// 4,096 rows 438 / 249; the 3,500-row level of a graph of 50,000 113 / 84.
+constexpr int kSuitorLds = 4096, kSuitorLdsMid = 2560;
 __global__ void __launch_bounds__(1024)
 k_suitor_lds(int n, const int *__restrict__ rp, const unsigned long long *__restrict__ cand,
              unsigned long long *__restrict__ ws) {
@@ -1538,9 +1540,10 @@ void launch_candidates(hipStream_t s, int G, int n, bool sorted, const int *rp, 
     });
 }
 
-void launch_suitor(hipStream_t s, int n, bool sorted, const int *rp, const unsigned long long *cand,
+void launch_suitor(hipStream_t s, int n, long long nnz, const int *rp, const unsigned long long *cand,
                    unsigned long long *ws) {
-    if (n <= (sorted ? kSuitorLdsSorted : kSuitorLds)) {
+    const bool mid = nnz >= 24LL * n && nnz < 96LL * n;
+    if (n <= (mid ? kSuitorLdsMid : kSuitorLds)) {
         const KernelEvents e = g_kernel_events;  // (launch_k has no dynamic LDS)
         g_kernel_events = KernelEvents{};
         const size_t lds = sizeof(unsigned long long) * (size_t)n;

@@ -1,5 +1,5 @@
 """Both sides of the lines at which a path changes, against the oracle: the Suitor
-matching in LDS (up to 4096 vertices, 2560 of rows of two dozen entries and more), the coarsest sweeps by powers (where the square
+matching in LDS (up to 4096 vertices, 2560 of rows of two to eight dozen entries), the coarsest sweeps by powers (where the square
 is taken or refused by its lanes and entries), the down leg on the values of A D in FP64
 (levels of 2^19 rows, values that are no float32), the flexible-CG stop test in the
 fused down leg (aggregates of up to four rows) and the W-cycle's second result added
@@ -36,10 +36,10 @@ def _irregular(n, seed, equal, more=0):
 
 @pytest.mark.parametrize("equal", [False, True])
 @pytest.mark.parametrize("n,more", [(2, 0), (1023, 0), (1024, 0), (1025, 0), (4095, 0), (4096, 0), (4097, 0),
-                                    (1024, 20), (2559, 20), (2560, 20), (2561, 20)])
+                                    (1024, 20), (2559, 20), (2560, 20), (2561, 20), (4096, 60), (4097, 60)])
 def test_suitor_on_small_graphs(B, ora, n, more, equal):  # noqa: F811
     rp, ci, va = _irregular(n, n, equal, more)
-    assert (len(ci) >= 24 * n) == (more > 0)
+    assert {0: (0, 24), 20: (24, 96), 60: (96, 999)}[more][0] <= len(ci) / n < {0: (0, 24), 20: (24, 96), 60: (96, 999)}[more][1]
     w = np.ones(n)
     say(f"suitor n={n} nnz={len(ci)} equal={equal}")
     c_ref = ora.weights(rp, ci, va, w)
