@@ -46,7 +46,8 @@ enum {
                              relative residual */
     BCM_EINVAL = -1,      /* invalid argument or matrix (see bcm_last_error) */
     BCM_EBREAKDOWN = -2,  /* flexible CG breakdown: rho <= 0 or not finite */
-    BCM_ENOMEM = -3,      /* device allocation failed */
+    BCM_ENOMEM = -3,      /* device allocation failed (bcm_setup: also without the
+                             forms of the levels that only save time) */
     BCM_EHIP = -4         /* HIP runtime error */
 };
 
@@ -121,12 +122,29 @@ typedef struct {
  *   sell           1     sliced-ELL copies (64-row slices) of the finest level
  *                        and of levels >= 65536 rows for the row-parallel solve
  *                        kernels; 0 = CSR row kernels everywhere
- *   fold           1     V-cycle: the cycle from the first level k >= 1 with at
- *                        most 2048 rows down to the coarsest (a fixed linear
- *                        map, pre = post = 1) is formed once in float64 at
- *                        setup and applied as one dense product; the same
- *                        operator as the level-by-level cycle up to rounding,
- *                        also under BCM_FP32_CYCLE.  0 = level by level.
+ *   fold           1     the cycle from the first level k >= 1 with at most 2048
+ *                        rows down to the coarsest (a fixed linear map, pre =
+ *                        post = 1) is formed once in float64 at setup and
+ *                        applied as one dense product (V- and W-cycles, K-cycles
+ *                        below their Krylov levels); in the V-cycle also the
+ *                        cycle from a level on whose every row is coupled to one
+ *                        hub row alone, as a product of a few dozen vectors.
+ *                        The same operators as the level-by-level cycle up to
+ *                        rounding, also under BCM_FP32_CYCLE.  0 = level by
+ *                        level (the coarsest level's sweeps are still taken in
+ *                        the forms below).
+ *
+ * Device memory.  A handle holds the levels and their vectors, and forms of them
+ * that only save time: sliced-ELL copies (sell); on such levels of at least 2^19
+ * rows (FP64: unless every value is exactly a float32) and on the finest of an
+ * FP32 cycle the values scaled by the inverse diagonal (8 or 4 bytes an entry);
+ * the folded operator (at most 32 MB); a chain of star levels (16 bytes a row for each of
+ * its 2 levels + coarse_sweeps vectors; at most 5 GiB with the scratch that forms
+ * it, 20 GiB for a coarsest star alone); of a coarsest level of more than 2048 and
+ * at most 2^17 rows up to two powers of its sweep matrix (at most 500 MB, mostly a
+ * tenth).  A form whose memory cannot be had is left out, and a setup that runs
+ * out of memory is done once more without these forms (the sliced-ELL copies and
+ * the V-cycle's folded operator stay) before it returns BCM_ENOMEM.
  */
 typedef struct {
     int32_t max_levels;

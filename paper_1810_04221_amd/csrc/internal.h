@@ -436,12 +436,12 @@ void launch_candidates(hipStream_t s, int G, int n, bool sorted, const int *rp, 
 void launch_find_long(hipStream_t s, int n, const int *rp, int lmin, const SegList &seg, int *idx);
 // Galerkin coarse rows with more than lmin candidate entries (members' rows)
 void launch_find_long_gal(hipStream_t s, int nc, const int *mem2, const int *rp, int lmin, const SegList &seg);
-// rows of tm < length <= lmin into rows (cnt[0] of them), and the aggregates
-// whose longest member row is one (cnt[1]; mem null: none)
 // the chunk and aggregate infos of a level's long rows (mem null or mstride > 4:
 // no aggregates)
 void launch_long_info(hipStream_t s, const LongRows &lr, const int *rp, const int *agg, const int *mem, int mstride,
                       ChunkInfo *ch, AggInfo *ag);
+// rows of tm < length <= lmin into rows (cnt[0] of them), and the aggregates
+// whose longest member row is one (cnt[1]; mem null: none)
 void launch_find_mid(hipStream_t s, int n, int nc, int mstride, const int *mem, const int *rp, int tm, int lmin,
                      int *rows, int *aggs, int *cnt);
 // offsets, chunk bases and totals of seg (one workgroup)
@@ -508,8 +508,8 @@ void launch_sell_fill(hipStream_t s, int n, const int *rp, const int *ci, const 
 void launch_sell_scale_cols(hipStream_t s, int n, const Sell &E, int f32, const void *dinv);
 void launch_fill_i32(hipStream_t s, size_t n, int *dst, int val);
 void launch_fill_u64(hipStream_t s, size_t n, unsigned long long *dst, unsigned long long val);
+// dst = src as a kernel (safe in a captured graph, as the fills are)
 void launch_copy_f64(hipStream_t s, size_t n, const double *src, double *dst);
-// dst = src on the finest level's vector length; also a graph-safe fill (no memset node)
 
 // ---- powers of the coarsest sweep matrix (power.hip) ----
 int power_row_limit();   // longest row of a matrix that is squared

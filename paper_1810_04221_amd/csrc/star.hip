@@ -49,8 +49,8 @@ k_star_find(int n, const int *__restrict__ rp, const int *__restrict__ ci, int *
     if (odd) atomicMax(&out[2], 1);
 }
 
-// out[2] is raised to 1 where a leaf's other column is not the hub; to 2 where
-// a leaf has no hub entry, the hub row has no entry for it, or the two differ.
+// out[2] is raised where a leaf's other column is not the hub; out[3] where a leaf
+// has no hub entry, the hub row has no entry for it, or the two differ.
 __global__ void __launch_bounds__(kBlock)
 k_star_verify(int n, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ v, int hub,
               int *__restrict__ out) {
