@@ -724,14 +724,18 @@ int build_coarsest_star(bcm_handle *h, hipStream_t s, Arena &tmp, HostTables &ho
 }
 
 // Powers of the coarsest level's sweep matrix, while they stay sparse enough
-// (PowerOp); the sweeps must be a multiple of the power.  Whether the square is
+// (PowerOp); the sweeps must be a multiple of the power.  Fewer than 8 sweeps stay
+// one by one: a cycle saves 2 to 9 us (of 8 sweeps 20 to 38) while forming M^2 takes
+// 50 to 180 us of the setup, 8 to 60 cycles against 2 to 10; M^4 is formed from 16
+// sweeps on (8,000 rows of 7: 0.74 ms of the setup and 28 us a cycle beside M^2 with
+// 20 sweeps, 1 us with 8).  Whether the square is
 // taken is settled, as far as its products tell, on the level's own matrix before
 // anything is allocated; what is allocated and then not taken is given back, and
 // so is all of it when it cannot be had (the sweeps need none of it).
 int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
     Level &L = h->lv[h->nl - 1];
     const int n = L.A.n, sweeps = h->prm.coarse_sweeps;
-    if (sweeps % 2 || L.lr.n > 0 || L.A.dmax > power_row_limit() || n > (1 << 17)) return BCM_OK;
+    if (sweeps % 2 || sweeps < 8 || L.lr.n > 0 || L.A.dmax > power_row_limit() || n > (1 << 17)) return BCM_OK;
     if ((long long)n * power_stride(L.A.dmax) > kPowerPad * kPower2Long) return BCM_OK;
     tmp.rewind();
     int *ctl = tmp.get_n<int>(2), *cnt = tmp.get_n<int>(n), *pre = tmp.get_n<int>(n);
@@ -751,7 +755,7 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
     };
     const Arena::Mark before = h->persist.mark();
     PowerOp P;
-    for (int t = 0; t < (sweeps % 4 ? 1 : 2); ++t) {
+    for (int t = 0; t < (sweeps % 4 || sweeps < 16 ? 1 : 2); ++t) {
         long long most = t == 0 ? kPower2Long : kPower4;
         if (t > 0 && r[1] > power_row_limit()) break;  // (r: M's entries and longest row)
         if (t == 0) launch_power_products(s, L.A, cnt);
@@ -776,10 +780,6 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
             launch_power_first(s, L, P.m[0]);
         }
         const PowerMat &M = P.m[t];
-        // (sweeps that are one application of the power: M^2 is never applied for 2
-        // sweeps, nor M^4 for 4)
-        const bool needed = (2 << t) != sweeps;
-        const Arena::Mark mq = h->persist.mark();
         PowerMat Q;
         Q.len = h->persist.get_n<int>(n);
         if (Q.len) {
@@ -789,20 +789,15 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
             if (t == 0 && r[0] < 256LL * n) most = kPower2;
         }
         if (!Q.len || r[0] > most || (long long)n * power_lanes(r[0], n) > kPowerLanes ||
-            (long long)n * power_stride(r[1]) > kPowerPad * most ||
-            (needed && !matrix(r[1], Q))) {
+            (long long)n * power_stride(r[1]) > kPowerPad * most || !matrix(r[1], Q)) {
             HIPCHK(hipStreamSynchronize(s));
             h->persist.back(mk);
-            break;
-        }
-        P.p = 2 << t;
-        if (!needed) {
-            h->persist.back(mq);
             break;
         }
         Q.nnz = r[0];
         launch_power_square(s, 1, n, M, Q, cnt, cand);
         P.m[t + 1] = Q;
+        P.p = 2 << t;
     }
     if (P.p > 0) L.power = P;
     return BCM_OK;

@@ -254,23 +254,15 @@ void apply(hipStream_t s, int n, const PowerMat &M, F f, C g, VX *x, const doubl
     else go(std::integral_constant<int, 64>{});
 }
 
-// sweeps = p k: c_p, then k - 1 times x <- M^p x + c_p
+// sweeps = p k, k >= 2: c_p, then k - 1 times x <- M^p x + c_p
 template <typename VB, typename VX>
 void power_t(hipStream_t s, const PowerOp &P, int n, int sweeps, const double *dinv, const VB *b, VX *x,
              const double *done) {
     const Scaled<VB> db{dinv, b};
     double *c = P.buf[0], *xa = P.buf[1], *xb = P.buf[2];
     const int steps = sweeps / P.p;
-    if (P.p == 2 && steps == 1) {
-        apply(s, n, P.m[0], db, db, x, done);
-        return;
-    }
     apply(s, n, P.m[0], db, db, c, done);  // c_2
     if (P.p == 4) {
-        if (steps == 1) {
-            apply(s, n, P.m[1], Vector{c}, Vector{c}, x, done);
-            return;
-        }
         apply(s, n, P.m[1], Vector{c}, Vector{c}, xa, done);  // c_4 = M^2 c_2 + c_2
         std::swap(c, xa);
     }
