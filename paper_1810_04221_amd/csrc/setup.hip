@@ -820,19 +820,23 @@ k_sell_width(int n, const int *__restrict__ rp, const int *__restrict__ ci, cons
             const int tb = block_first(it, B), ib = block_first(i, B);
             for (int k = lane; k < w; k += kSlice) T[k] = ci[qt + k] - tb;
             wave_sync();
-            int ok = 1;
-            if (i < n) {
-                // merge walk: each offset of this row must appear in the template, in order
-                int k = 0;
-                for (int j0 = 0; j0 < len && ok; j0 += 8) {
+            int ok = 1, k = 0;
+            // merge walk: each offset of this row must appear in the template, in order
+            // (both ascend); over for the slice with the first row that does not fit (128
+            // rows of 92 entries in no order, three block sizes: 389 us when every row was
+            // walked to its end; setup 555 -> 208 us, 200,000 rows of 61 3.64 -> 3.49 ms)
+            for (int j0 = 0;; j0 += 8) {
+                const bool more = ok && j0 < len;
+                if (__ballot(!ok) != 0 || __ballot(more) == 0) break;
+                if (more) {
                     int o[8];
 #pragma unroll
                     for (int t8 = 0; t8 < 8; ++t8) o[t8] = j0 + t8 < len ? ci[q0 + j0 + t8] - ib : 0;
 #pragma unroll
                     for (int t8 = 0; t8 < 8; ++t8) {
                         if (j0 + t8 >= len || !ok) continue;
-                        while (k < w && T[k] != o[t8]) ++k;
-                        if (k == w) ok = 0;
+                        while (k < w && T[k] < o[t8]) ++k;
+                        if (k == w || T[k] != o[t8]) ok = 0;
                         ++k;
                     }
                 }
