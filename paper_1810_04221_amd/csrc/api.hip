@@ -1429,10 +1429,10 @@ int build_hierarchy(bcm_handle *h, const bcm_csr *Ain, const double *win, bool l
             const size_t nn2 = (size_t)C.A.n * C.A.n;
             C.S = h->persist.get_n<double>(nn2);
             NOMEM(C.S);
-            if (lean || coarse_in_lds(C.A.n, C.A.nnz, C.lr.n > 0)) {
+            if (lean || coarse_in_lds(C.A.n, C.A.nnz, C.lr.n > 0) || unit_sweeps(C, P.coarse_sweeps)) {
                 // one workgroup per unit vector runs the sweeps on the matrix in
-                // its LDS (without it, each would stream the matrix through one
-                // CU: 866 rows with 362,762 entries took 55 ms, but no memory)
+                // its LDS (without it, each streams the matrix through one CU:
+                // 866 rows with 362,762 entries took 55 ms, but no memory)
                 launch_coarse_build(s, C, P.coarse_sweeps, C.S);
             } else {
                 tmp.rewind();

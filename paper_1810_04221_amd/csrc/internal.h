@@ -617,6 +617,9 @@ void launch_fold_level(hipStream_t s, const Level &L, const double *Tc, int nc, 
 void launch_fold_w(hipStream_t s, const Level &L, const double *T, double *M, double *W, bool sym);
 // true when the sweep operator is formed by doubling (launch_sweep_operator)
 bool sweep_doubling(const Level &L);
+// true when small enough for one workgroup a unit vector (launch_coarse_build) though
+// not held in a workgroup's LDS
+bool unit_sweeps(const Level &L, int sweeps);
 // S = sum_{t < sweeps} (I - D A)^t D of the coarsest level, n x n, sweeps >= 2
 // (W, M, Ad: n x n scratch)
 void launch_sweep_operator(hipStream_t s, const Level &L, int sweeps, bool sym, double *S, double *W, double *M,

@@ -1778,6 +1778,19 @@ void launch_fold_w(hipStream_t s, const Level &L, const double *T, double *M, do
 // launches of about 14 us (setup of an 80^3 W-cycle: 2.4 ms; doubling took 3.0).
 bool sweep_doubling(const Level &L) { return 80LL * L.A.nnz > (long long)L.A.n * L.A.n; }
 
+// One workgroup a unit vector (launch_coarse_build) on a matrix that its LDS does not
+// hold, up to one workgroup a CU: each sweep streams the matrix from the L2 for all n
+// of them, against a product of 13 to 20 us for each doubling's two and each odd
+// bit's one.  Measured, us, by unit vectors / by doubling: 20 sweeps, 90 rows of 80
+// entries 55 / 128, 128 of 127 95 / 133, 192 of 103 210 / 162, 256 of 50 172 / 157; 4
+// sweeps, 192 of 103 42 / 74, 256 of 108 70 / 83, 256 of 185 143 / 78.
+bool unit_sweeps(const Level &L, int sweeps) {
+    if (L.A.n > 256) return false;
+    int products = 0;
+    for (int k = sweeps; k > 3; k >>= 1) products += 2 + (k & 1);
+    return sweeps * (0.9 + 2.4e-6 * L.A.n * L.A.nnz) < 40.0 + 14.0 * products;
+}
+
 // S_k = sum_{t < k} (I - D A)^t D = (I - (I - D A)^k) A^-1, so S_(2k) = 2 S_k - S_k A S_k
 // and S_(k+1) = D + (I - D A) S_k: k is reached from 2 by the bits of `sweeps`
 // (20: 2, 4, 5, 10, 20), where one launch per sweep took 20 products with A.

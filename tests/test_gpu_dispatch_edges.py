@@ -150,3 +150,19 @@ def test_sweeps_where_the_square_is_taken_or_refused(B, ora, name):  # noqa: F81
     h = B.Hierarchy(rp, ci, va, max_levels=1)
     _close_entries(h.precond(r).cpu().numpy(), zo, ENTRY_FP64)
     h.close()
+
+
+@pytest.mark.parametrize("n,degree", [(90, 60), (128, 120), (192, 60), (256, 25), (256, 250), (257, 60)])
+@pytest.mark.parametrize("sweeps", [1, 2, 4, 7, 20])
+def test_sweep_operator_of_small_dense_levels(B, ora, n, degree, sweeps):  # noqa: F811
+    # unit vectors or doubling, by sweeps, rows and entries; matrices that no workgroup's
+    # LDS holds
+    rp, ci, va = P.random_spd(n, degree / n, n + degree)
+    assert 16 * n + 12 * len(ci) + 4 * (n + 1) > 65536
+    say(f"small sweep operator n={n} nnz={len(ci)} sweeps={sweeps}")
+    r = P.uniform_rhs(n, 78)
+    zo = ora.Hierarchy(rp, ci, va, np.ones(n), max_coarse=n, coarse_sweeps=sweeps).vcycle(r)
+    for check in (True, False):
+        h = B.Hierarchy(rp, ci, va, max_coarse=n, coarse_sweeps=sweeps, check=check)
+        _close_entries(h.precond(r).cpu().numpy(), zo, ENTRY_FP64)
+        h.close()
