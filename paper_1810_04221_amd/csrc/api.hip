@@ -755,6 +755,7 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
     };
     const Arena::Mark before = h->persist.mark();
     PowerOp P;
+    double kept = 1.0;  // entries of M^2 over its products
     for (int t = 0; t < (sweeps % 4 || sweeps < 16 ? 1 : 2); ++t) {
         long long most = t == 0 ? kPower2Long : kPower4;
         if (t > 0 && r[1] > power_row_limit()) break;  // (r: M's entries and longest row)
@@ -763,7 +764,10 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
         int rc = totals(cnt);
         if (rc) return rc;
         // (a square keeps about 6 of 10 products of a first power, 1 of 5 of a second)
-        const int cand = r[1];
+        const int cand = r[1], products = r[0];
+        // (M^4 keeps about the square of what M^2 kept: 0.2 to 0.25 of the products on grids,
+        // 0.55 of a random graph's, whose columns took 0.2 ms to count before it was refused)
+        if (t > 0 && products * kept * kept > 1.1 * most) break;
         if (cand > power_cand_limit() || r[0] > (t == 0 ? 5 * most / 2 : 8 * most)) break;
         // (so many rows may take 16 lanes each at most: 12 entries, of two dozen products or fewer)
         if (32LL * n > kPowerLanes && r[0] > 24LL * n) break;
@@ -795,6 +799,7 @@ int build_power(bcm_handle *h, hipStream_t s, Arena &tmp) {
             break;
         }
         Q.nnz = r[0];
+        kept = (double)Q.nnz / products;
         launch_power_square(s, 1, n, M, Q, cnt, cand);
         P.m[t + 1] = Q;
         P.p = 2 << t;
