@@ -140,9 +140,9 @@ typedef struct {
  *    every value is exactly a float32) and on the finest of an FP32 cycle also the
  *    values scaled by the inverse diagonal (8 or 4 bytes an entry);
  *  - the folded operator (at most 32 MB);
- *  - a chain of star levels (16 bytes a row for each of its 2 levels +
- *    coarse_sweeps vectors; at most 5 GiB with the scratch that forms it, 20 GiB
- *    for a coarsest star alone);
+ *  - a chain of star levels (16 bytes a row, times twice its levels plus
+ *    coarse_sweeps; at most 5 GiB with the scratch that forms it, 20 GiB for a
+ *    coarsest star alone);
  *  - of a coarsest level of more than 2048 and at most 2^17 rows, from 8 sweeps on,
  *    its sweep matrix and one or two powers of it (at most 500 MB, mostly a tenth).
  * A form whose memory cannot be had is left out, and a setup that runs out of
